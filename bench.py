@@ -43,8 +43,8 @@ def log(msg):
 
 
 KERNEL_OF_KIND = {"atoms": "k_atoms<{t}>", "logic": "k_logic", "near": "k_near", "ccl_local": "k_ccl_local<{tbh}>",
-                  "ccl_merge": "k_ccl_merge<{tbh}>", "ccl_flag": "k_ccl_flag", "ccl_gather": "k_ccl_gather",
-                  "ccl_reseed": "k_ccl_reseed"}
+                  "ccl_merge": "k_ccl_merge", "ccl_flag": "k_ccl_flag", "ccl_gather": "k_ccl_gather<{tbh}>",
+                  "ccl_reseed": "k_ccl_reseed<{tbh}>"}
 
 
 def measured_traffic(workload, kind, tbh, dtype="float"):

@@ -244,18 +244,19 @@ int check_status(vlg_ctx *c) {
 // Workspace layout of one evaluation.
 struct Layout {
     size_t mask_bytes = 0;
-    size_t off_slots = 0, off_stage = 0, off_u8 = 0, off_glab = 0, off_gflag = 0, off_pct = 0,
-           off_pctst = 0, total = 0;
-    size_t lane_bytes = 0;  // labelling workspace of lane l at off_glab / off_gflag + l * lane_bytes
-    bool pj = false;        // pointer-jumping labelling: its arrays (pj_work) start at off_glab
-    bool vol = false;       // volume labelling: voxel parents (4 B) then flag bytes at off_glab
+    size_t off_slots = 0, off_stage = 0, off_u8 = 0, off_ccl = 0, off_pct = 0, off_pctst = 0, total = 0;
+    size_t lane_bytes = 0;  // labelling workspace of lane l at off_ccl + l * lane_bytes
+    bool pj = false;        // pointer-jumping labelling: its arrays (pj_work) start at off_ccl
+    bool vol = false;       // volume labelling: voxel parents (4 B) then flag bytes at off_ccl
 };
 
 // the block parents of a volume labelling (vl_nblocks <= g.BH * g.BW)
 size_t vol_label_bytes(const Geo &g) { return align256((size_t)g.BH * g.BW * 4); }
 
+// batch_tbh: the labelling tile height of a batch (one for all its images, so
+// it may need more than ccl_workspace on some); 0 for a single image
 Layout layout_for(const Plan &P, const Geo &g, bool stage_packed, bool stage_u8, bool pj = false,
-                  bool vol = false) {
+                  bool vol = false, int batch_tbh = 0) {
     Layout L;
     L.mask_bytes = align256((size_t)g.nwords * 8);
     size_t off = 0;
@@ -265,15 +266,15 @@ Layout layout_for(const Plan &P, const Geo &g, bool stage_packed, bool stage_u8,
     if (stage_packed) off += (size_t)P.noutputs * L.mask_bytes;
     L.off_u8 = off;
     if (stage_u8) off += (size_t)P.noutputs * align256((size_t)g.H * g.W);
-    L.off_glab = off;
+    L.off_ccl = off;
     const size_t nb = (size_t)g.BH * g.BW;
     L.pj = pj && !vol;
     L.vol = vol;
     L.lane_bytes = P.ccl_count == 0 ? 0
                    : vol          ? vol_label_bytes(g) + align256((size_t)g.BH * g.BW)
                    : L.pj         ? align256(pj_bytes(g))
-                                  : align256(nb * 4) + align256(nb);
-    L.off_gflag = off + (P.ccl_count > 0 ? align256(nb * 4) : 0);
+                   : batch_tbh    ? std::max(ccl_workspace(g), align256(ccl_bytes(g, batch_tbh)))
+                                  : ccl_workspace(g);
     off += (size_t)std::max(P.ccl_lanes, 1) * L.lane_bytes;
     L.off_pct = off;
     off += align256((size_t)P.npct * 4);
@@ -327,7 +328,45 @@ int tuned_value(const vlg_ctx *c, int which, int H, int W) {
 struct TuningShim {
     int ccl_tbh;
 };
-TuningShim tuning_for(const vlg_ctx *c, int H, int W) { return {tuned_value(c, VLG_TUNE_CCL_TILE_ROWS, H, W)}; }
+// (the tile height that runs: the tunable's, or the next taller that fits the
+// labelling workspace of a narrow image)
+TuningShim tuning_for(const vlg_ctx *c, int H, int W) {
+    return {ccl_fit_tbh(make_geo(H, W), tuned_value(c, VLG_TUNE_CCL_TILE_ROWS, H, W))};
+}
+
+// What the union-find labelling steps of a plan need beyond their own
+// operands, per step: whether the labelling serves several users (a reseed
+// follows before its workspace is labelled again), and for a reseed the
+// passable mask of its labelling (the x of the gather that follows it).
+struct CclPlan {
+    std::vector<uint8_t> multi;
+    std::vector<Ref> b;
+};
+CclPlan ccl_plan(const Plan &P) {
+    const size_t n = P.steps.size();
+    CclPlan c;
+    c.multi.assign(n, 0);
+    c.b.assign(n, Ref());
+    std::vector<std::vector<size_t>> run((size_t)kMaxCclLanes);  // per workspace: steps of its current labelling
+    auto flush = [&](std::vector<size_t> &r) {
+        bool multi = false;
+        for (size_t si : r) multi |= P.steps[si].kind == SK::CclReseed;
+        for (size_t si : r) c.multi[si] = multi;
+        r.clear();
+    };
+    for (size_t si = 0; si < n; si++) {
+        const Step &s = P.steps[si];
+        if (s.kind != SK::CclLocal && s.kind != SK::CclMerge && s.kind != SK::CclFlag && s.kind != SK::CclGather &&
+            s.kind != SK::CclReseed)
+            continue;
+        auto &r = run[(size_t)std::max(s.lane, 0)];
+        if (s.kind == SK::CclLocal) flush(r);
+        if (s.kind == SK::CclGather && !r.empty() && P.steps[r.back()].kind == SK::CclReseed) c.b[r.back()] = s.x;
+        r.push_back(si);
+    }
+    for (auto &r : run) flush(r);
+    return c;
+}
 
 // (ceil(log2 n), ceil(log2 mean pixels per image)) of a batch
 std::pair<int, int> batch_class(int n, int64_t pixels) {
@@ -372,7 +411,8 @@ const char *kind_name(SK k) {
 // read once, its outputs written once (and the labelling arrays it owns).
 double algorithmic_bytes(const Plan &P, const Step &s, const Geo &g, int dtype, int tbh) {
     const double mb = (double)g.nwords * 8.0, npix = (double)g.H * g.W;
-    const double nb = (double)g.BH * g.BW;
+    const CclGeo q = ccl_geo(g, tbh);
+    const double nodes = (double)q.ntx * q.nty * q.np;  // a labelling also writes and reads a label per run
     auto ins = [&](std::initializer_list<Ref> rs) {
         double n = 0;
         for (const Ref &r : rs) n += r.slot != kNone ? mb : 0.0;
@@ -383,13 +423,10 @@ double algorithmic_bytes(const Plan &P, const Step &s, const Geo &g, int dtype, 
     case SK::Atoms: return npix * (dtype == VLG_U8 ? 1.0 : dtype == VLG_U16 ? 2.0 : 4.0) + s.natoms * mb;
     case SK::Logic: return ins({s.x, s.y}) + mb;
     case SK::Near: return ins({s.x, s.z}) + mb;
-    case SK::CclLocal: return ins({s.x, s.y, s.z}) + nb * 5.0;      // labels + flags written
-    case SK::CclMerge: {
-        const double ntiles = std::ceil(g.BH / (double)tbh) * std::ceil(g.BW / (double)kTileBW);
-        return ntiles * (kTileBW + 2 * tbh) * 16.0;                   // border words read
-    }
-    case SK::CclFlag: return nb;                                      // flags read
-    case SK::CclGather: return ins({s.x, s.y, s.z}) + nb * 4.0 + mb;  // labels read
+    case SK::CclLocal: return ins({s.x, s.y, s.z}) + 6.0 * nodes;     // border tables and nodes written
+    case SK::CclMerge: return 6.0 * nodes;                            // both read
+    case SK::CclFlag: return 5.0 * nodes;                             // flags and parents read
+    case SK::CclGather: return ins({s.x, s.y, s.z}) + 4.0 * nodes + mb;
     case SK::CclReseed: return ins({s.x});                            // seed mask read
     case SK::Arith: {
         // every channel the program reads, once, and the mask; in a group
@@ -558,10 +595,12 @@ int enqueue_plan(vlg_ctx *c, const Plan &P, const vlg_image *img, const Layout &
         return m;
     };
     float *pct = (float *)(base + L.off_pct);
-    CclWork w0;
-    w0.counters = c->count_ccl ? c->counters : nullptr;
-    w0.guard = c->guard();
-    w0.tbh = tuning_for(c, img->H, img->W).ccl_tbh;
+    CclMulti m0;
+    std::memset(&m0, 0, sizeof m0);
+    m0.counters = c->count_ccl ? c->counters : nullptr;
+    m0.guard = c->guard();
+    m0.tbh = tuning_for(c, img->H, img->W).ccl_tbh;
+    const CclPlan cp = ccl_plan(P);
     const int near_rows = tuned_value(c, VLG_TUNE_NEAR_ROWS, img->H, img->W);
     const int64_t npix = (int64_t)img->H * img->W;
     // pointer-jumping labellings (L.pj): the label array the current
@@ -577,11 +616,32 @@ int enqueue_plan(vlg_ctx *c, const Plan &P, const vlg_image *img, const Layout &
     // (blockIdx.y = lane), the other steps launch one by one, every lane's
     // steps in their order.  Pointer-jumping and volume labellings run the
     // region's steps in plan order.
-    auto lane_work = [&](int lane) {
-        CclWork w = w0;
-        w.glab = (int32_t *)(base + L.off_glab + (size_t)lane * L.lane_bytes);
-        w.gflag = (uint8_t *)(base + L.off_gflag + (size_t)lane * L.lane_bytes);
-        return w;
+    auto ccl_op = [&](size_t si) {
+        const Step &t = P.steps[si];
+        CclOp o;
+        o.b = mref(t.kind == SK::CclReseed ? cp.b[si] : t.x);
+        o.y = mref(t.kind == SK::CclReseed ? t.x : t.y);
+        o.z = mref(t.z);
+        o.ws = base + L.off_ccl + (size_t)std::max(t.lane, 0) * L.lane_bytes;
+        o.user = t.user;
+        o.multi = cp.multi[si];
+        o.out = slot_ptr(t.out);
+        return o;
+    };
+    auto ccl_launch = [&](SK kind, const CclMulti &m) {
+        switch (kind) {
+        case SK::CclLocal: return launch_ccl_local(c->stream, g, m);
+        case SK::CclMerge: return launch_ccl_merge(c->stream, g, m);
+        case SK::CclFlag: return launch_ccl_flag(c->stream, g, m);
+        case SK::CclReseed: return launch_ccl_reseed(c->stream, g, m);
+        default: return launch_ccl_gather(c->stream, g, m);
+        }
+    };
+    auto ccl_step = [&](size_t si) {  // one labelling's phase
+        CclMulti m = m0;
+        m.n = 1;
+        m.op[0] = ccl_op(si);
+        return ccl_launch(P.steps[si].kind, m);
     };
     auto run_region = [&](size_t r0, size_t r1) -> int {
         std::vector<std::vector<size_t>> q((size_t)kMaxCclLanes);
@@ -593,27 +653,14 @@ int enqueue_plan(vlg_ctx *c, const Plan &P, const vlg_image *img, const Layout &
             bool any = false;
             const std::vector<size_t> at = head;
             for (SK kind : {SK::CclLocal, SK::CclMerge, SK::CclFlag, SK::CclGather}) {
-                CclMulti m;
-                std::memset(&m, 0, sizeof m);
+                CclMulti m = m0;
                 for (size_t l = 0; l < q.size(); l++) {
                     if (at[l] >= q[l].size() || head[l] != at[l] || P.steps[q[l][at[l]]].kind != kind) continue;
-                    const Step &t = P.steps[q[l][head[l]++]];
-                    const CclWork lw = lane_work((int)l);
-                    m.b[m.n] = mref(t.x);
-                    m.y[m.n] = mref(t.y);
-                    m.z[m.n] = mref(t.z);
-                    m.glab[m.n] = lw.glab;
-                    m.gflag[m.n] = lw.gflag;
-                    m.user[m.n] = t.user;
-                    m.out[m.n] = slot_ptr(t.out);
-                    m.n++;
+                    m.op[m.n++] = ccl_op(q[l][head[l]++]);
                 }
                 if (m.n == 0) continue;
                 any = true;
-                hipError_t e = kind == SK::CclLocal   ? launch_ccl_local_multi(c->stream, g, m, w0)
-                               : kind == SK::CclMerge ? launch_ccl_merge_multi(c->stream, g, m, w0)
-                               : kind == SK::CclFlag  ? launch_ccl_flag_multi(c->stream, g, m, w0)
-                                                      : launch_ccl_gather_multi(c->stream, g, m);
+                const hipError_t e = ccl_launch(kind, m);
                 if (e != hipSuccess) return fail(VLG_EHIP, std::string("kernel launch: ") + hipGetErrorString(e));
             }
             for (size_t l = 0; l < q.size(); l++) {
@@ -625,7 +672,7 @@ int enqueue_plan(vlg_ctx *c, const Plan &P, const vlg_image *img, const Layout &
                 else if (t.kind == SK::Near)
                     e = launch_near(c->stream, g, mref(t.x), t.inv_out, mref(t.z), t.op, slot_ptr(t.out), near_rows);
                 else if (t.kind == SK::CclReseed)
-                    e = launch_ccl_reseed(c->stream, g, mref(t.x), lane_work((int)l), t.user);
+                    e = ccl_step(q[l][head[l]]);
                 else
                     continue;  // a labelling phase: next round
                 head[l]++;
@@ -650,9 +697,8 @@ int enqueue_plan(vlg_ctx *c, const Plan &P, const vlg_image *img, const Layout &
         }
         const int lane = s.lane > 0 ? s.lane : 0;
         hipStream_t stream = c->stream;
-        CclWork w = lane_work(lane);
-        const PjWork pw = pj_work(base + L.off_glab + (size_t)lane * L.lane_bytes, g);
-        int *vP = (int *)(base + L.off_glab + (size_t)lane * L.lane_bytes);
+        const PjWork pw = pj_work(base + L.off_ccl + (size_t)lane * L.lane_bytes, g);
+        int *vP = (int *)(base + L.off_ccl + (size_t)lane * L.lane_bytes);
         uint8_t *vflag = (uint8_t *)vP + vol_label_bytes(g);
         if (hook) hook(hook_ctx, si, true);
         hipError_t e = hipSuccess;
@@ -742,7 +788,7 @@ int enqueue_plan(vlg_ctx *c, const Plan &P, const vlg_image *img, const Layout &
         case SK::CclLocal:
             if (L.vol) {
                 // the whole voxel labelling, then the seeds
-                e = launch_vl_label(stream, g, vS, vD, mref(s.x), vP, w.guard);
+                e = launch_vl_label(stream, g, vS, vD, mref(s.x), vP, m0.guard);
                 if (e == hipSuccess) e = launch_vl_clear_flags(stream, g, vS, vD, vflag);
                 if (e == hipSuccess) e = launch_vl_seed(stream, g, vS, vD, mref(s.x), mref(s.y), mref(s.z), vP, vflag, 0);
             } else if (L.pj) {
@@ -752,14 +798,14 @@ int enqueue_plan(vlg_ctx *c, const Plan &P, const vlg_image *img, const Layout &
                 e = launch_pj_clear_flags(stream, g, pw);
                 if (e == hipSuccess) e = launch_pj_seed(stream, g, mref(s.x), mref(s.y), mref(s.z), pw, pj_at, 0);
             } else {
-                e = launch_ccl_local(stream, g, mref(s.x), mref(s.y), mref(s.z), w);
+                e = ccl_step(si);
             }
             break;
         case SK::CclMerge:  // the pointer-jumping and voxel labellings have no merge or flag pass
-            if (!L.pj && !L.vol) e = launch_ccl_merge(stream, g, mref(s.x), w);
+            if (!L.pj && !L.vol) e = ccl_step(si);
             break;
         case SK::CclFlag:
-            if (!L.pj && !L.vol) e = launch_ccl_flag(stream, g, w);
+            if (!L.pj && !L.vol) e = ccl_step(si);
             break;
         case SK::CclGather:
             if (L.vol)
@@ -768,7 +814,7 @@ int enqueue_plan(vlg_ctx *c, const Plan &P, const vlg_image *img, const Layout &
             else if (L.pj)
                 e = launch_pj_gather(stream, g, mref(s.x), mref(s.y), mref(s.z), pw, pj_at, s.user, slot_ptr(s.out));
             else
-                e = launch_ccl_gather(stream, g, mref(s.x), mref(s.y), mref(s.z), w, s.user, slot_ptr(s.out));
+                e = ccl_step(si);
             break;
         case SK::CclReseed:
             if (L.vol)
@@ -776,7 +822,7 @@ int enqueue_plan(vlg_ctx *c, const Plan &P, const vlg_image *img, const Layout &
             else if (L.pj)
                 e = launch_pj_reseed(stream, g, mref(s.x), pw, pj_at, s.user);
             else
-                e = launch_ccl_reseed(stream, g, mref(s.x), w, s.user);
+                e = ccl_step(si);
             break;
         case SK::Segment: {
             if (vol) return fail(VLG_EINVAL, "internal: no fused segments on volumes");
@@ -945,7 +991,7 @@ int run_batch(vlg_ctx *c, vlg_formula *f, const vlg_image *const *imgs, const st
     size_t total = 0;
     for (int k = 0; k < n; k++) {
         geo[k] = make_geo(imgs[idx[k]]->H, imgs[idx[k]]->W);
-        lay[k] = layout_for(P, geo[k], true, stage_u8);
+        lay[k] = layout_for(P, geo[k], true, stage_u8, false, false, tbh);
         off[k] = total;
         total += align256(lay[k].total);
     }
@@ -991,8 +1037,7 @@ int run_batch(vlg_ctx *c, vlg_formula *f, const vlg_image *const *imgs, const st
         d.chan_bytes = (int64_t)im->H * im->pitch * (int64_t)im->esize();
         d.ws = wb + L.off_slots;
         d.mask_bytes = L.mask_bytes;
-        d.off_glab = L.off_glab - L.off_slots;
-        d.off_gflag = L.off_gflag - L.off_slots;
+        d.off_ccl = L.off_ccl - L.off_slots;
         d.off_pct = L.off_pct - L.off_slots;
         d.off_pctst = L.off_pctst - L.off_slots;
         d.outs = (uint64_t *const *)(base + d_outs) + (size_t)k * nout;
@@ -1049,6 +1094,7 @@ int run_batch(vlg_ctx *c, vlg_formula *f, const vlg_image *const *imgs, const st
         for (size_t si = 0; si < P.steps.size(); si++)
             for (int k = 0; k < n; k++) (*bytes)[si] += algorithmic_bytes(P, P.steps[si], geo[k], dtype, tbh);
     }
+    const CclPlan cp = ccl_plan(P);
     auto enqueue_steps = [&]() -> int {
         for (size_t si = 0; si < P.steps.size(); si++) {
             const Step &s = P.steps[si];
@@ -1134,22 +1180,22 @@ int run_batch(vlg_ctx *c, vlg_formula *f, const vlg_image *const *imgs, const st
                 break;
             }
             case SK::CclLocal:
-                e = launch_b_ccl_local(c->stream, args(BK_TILES), units(BK_TILES), tbh, bref(s.x), bref(s.y),
-                                       bref(s.z));
-                break;
             case SK::CclMerge:
-                e = launch_b_ccl_merge(c->stream, args(BK_MERGE), units(BK_MERGE), tbh, bref(s.x));
-                break;
             case SK::CclFlag:
-                e = launch_b_ccl_flag(c->stream, args(BK_FLAG), units(BK_FLAG));
-                break;
-            case SK::CclGather:
-                e = launch_b_ccl_gather(c->stream, args(BK_GATHER), units(BK_GATHER), bref(s.x), bref(s.y),
-                                        bref(s.z), s.user, s.out);
-                break;
             case SK::CclReseed:
-                e = launch_b_ccl_reseed(c->stream, args(BK_BLOCKS), units(BK_BLOCKS), bref(s.x), s.user);
+            case SK::CclGather: {
+                const bool reseed = s.kind == SK::CclReseed;
+                const BCcl o{bref(reseed ? cp.b[si] : s.x), bref(reseed ? s.x : s.y), bref(s.z), s.user,
+                             cp.multi[si], s.out, tbh};
+                const int unit = s.kind == SK::CclMerge ? BK_MERGE : s.kind == SK::CclFlag ? BK_FLAG : BK_TILES;
+                auto launch = s.kind == SK::CclLocal   ? launch_b_ccl_local
+                              : s.kind == SK::CclMerge ? launch_b_ccl_merge
+                              : s.kind == SK::CclFlag  ? launch_b_ccl_flag
+                              : reseed                 ? launch_b_ccl_reseed
+                                                       : launch_b_ccl_gather;
+                e = launch(c->stream, args(unit), units(unit), o);
                 break;
+            }
             case SK::Segment:
                 return fail(VLG_EINVAL, "internal: the batched schedule has no segments");
             case SK::Arith:
@@ -1336,33 +1382,48 @@ int tune_loop(vlg_ctx *c, const std::vector<std::pair<int, std::vector<int>>> &s
 
 namespace {
 
-// Labelling scratch of vlg_ccl_labels: parent pointers (4 B per 2x2 block),
-// flag bytes (1 B per block) and the canonical-label table (4 B per block).
+// Scratch that vlg_ccl_labels is documented to need: 9 bytes per 2x2 block.
 size_t ccl_labels_scratch_bytes(const Geo &g) {
     const size_t nb = (size_t)g.BH * g.BW;
     return 2 * align256(nb * 4) + align256(nb) + 256;
 }
 
-// Labels of the mask into labels_dev, with the labelling arrays in `scratch`
-// (at least ccl_labels_scratch_bytes(g) bytes of device memory).  Every array
-// the kernels read is written first in the same call (the local pass writes
-// every block's parent and flag byte, the table is filled before use), so the
-// scratch needs no clearing between calls.
-int ccl_labels_on(vlg_ctx *c, const Geo &g, const uint64_t *mask_dev, int32_t *labels_dev, void *scratch) {
+// The arrays of vlg_ccl_labels: the labelling's, a canonical label per node
+// and one per block (inner components, at their root block).
+struct LabelScratch {
+    int tbh;
+    size_t off_ncanon, off_icanon, total;
+};
+LabelScratch label_scratch(const Geo &g, int tbh) {
     const size_t nb = (size_t)g.BH * g.BW;
-    CclWork w;
-    w.glab = (int32_t *)scratch;
-    w.gflag = (uint8_t *)scratch + align256(nb * 4);
-    int32_t *canon = (int32_t *)((char *)scratch + align256(nb * 4) + align256(nb));
-    w.counters = c->counters;
-    w.tbh = tuning_for(c, g.H, g.W).ccl_tbh;
-    w.guard = c->guard();
-    MRef b{mask_dev, 0ull}, none{nullptr, 0ull};
-    HIP_TRY(launch_fill_i64(c->stream, c->counters, 2, 0));
-    HIP_TRY(launch_ccl_local(c->stream, g, b, none, none, w));
-    HIP_TRY(launch_ccl_merge(c->stream, g, b, w));
-    HIP_TRY(launch_ccl_flag(c->stream, g, w));
-    HIP_TRY(launch_ccl_labels(c->stream, g, b, w, canon, labels_dev));
+    for (;; tbh *= 2) {
+        const CclGeo q = ccl_geo(g, tbh);
+        LabelScratch s;
+        s.tbh = tbh;
+        s.off_ncanon = align256(ccl_bytes(g, tbh));
+        s.off_icanon = s.off_ncanon + align256(((size_t)q.ntx * q.nty * q.np + 1) * 4);
+        s.total = s.off_icanon + align256(nb * 4);
+        // narrow images take taller tiles, as in ccl_fit_tbh (a small image
+        // may still need a few kilobytes more than the documented figure)
+        if (tbh >= 32 || s.total <= ccl_labels_scratch_bytes(g)) return s;
+    }
+}
+
+// Labels of the mask into labels_dev, with the labelling arrays in `scratch`.
+// Every entry the kernels read is written first in the same call, so the
+// scratch needs no clearing between calls.
+int ccl_labels_on(vlg_ctx *c, const Geo &g, const uint64_t *mask_dev, int32_t *labels_dev, void *scratch,
+                  const LabelScratch &ls) {
+    CclMulti m;
+    std::memset(&m, 0, sizeof m);
+    m.n = 1;
+    m.tbh = ls.tbh;
+    m.guard = c->guard();
+    m.counters = c->counters;
+    m.op[0].b = MRef{mask_dev, 0ull};
+    m.op[0].ws = scratch;
+    HIP_TRY(launch_ccl_labels(c->stream, g, m, (int32_t *)((char *)scratch + ls.off_ncanon),
+                              (int32_t *)((char *)scratch + ls.off_icanon), labels_dev));
     return VLG_OK;
 }
 
@@ -1773,9 +1834,10 @@ int vlg_ccl_labels(vlg_ctx *c, const uint64_t *mask_dev, int height, int width, 
     DeviceGuard dg(c->device);
     const Geo g = make_geo(height, width);
     if (g.nwords == 0) return VLG_OK;
-    int rc = ensure_ws(c, ccl_labels_scratch_bytes(g));
+    const LabelScratch ls = label_scratch(g, tuned_value(c, VLG_TUNE_CCL_TILE_ROWS, height, width));
+    int rc = ensure_ws(c, ls.total);
     if (rc != VLG_OK) return rc;
-    return ccl_labels_on(c, g, mask_dev, labels_dev, c->ws);
+    return ccl_labels_on(c, g, mask_dev, labels_dev, c->ws, ls);
 }
 
 int vlg_ccl_labels_noalloc(vlg_ctx *c, const uint64_t *mask_dev, int height, int width, int32_t *labels_dev) {
@@ -1793,7 +1855,9 @@ int vlg_ccl_labels_noalloc(vlg_ctx *c, const uint64_t *mask_dev, int height, int
     void *scratch_dev = nullptr;
     int rc = noalloc_scratch(c->device, &scratch_dev);
     if (rc != VLG_OK) return rc;
-    return ccl_labels_on(c, g, mask_dev, labels_dev, scratch_dev);
+    const LabelScratch ls = label_scratch(g, tuned_value(c, VLG_TUNE_CCL_TILE_ROWS, height, width));
+    if (ls.total > kNoallocScratchBytes) return fail(VLG_EINVAL, "internal: labelling arrays beyond the fixed array");
+    return ccl_labels_on(c, g, mask_dev, labels_dev, scratch_dev, ls);
 }
 
 int vlg_profile(vlg_ctx *c, const vlg_formula *cf, const vlg_image *img, int iters, vlg_kernel_time *out,
@@ -1823,6 +1887,7 @@ int vlg_profile(vlg_ctx *c, const vlg_formula *cf, const vlg_image *img, int ite
     E.ev.resize(2 * P.steps.size());
     for (auto &e : E.ev) HIP_TRY(hipEventCreate(&e));
     std::vector<double> ms(P.steps.size(), 0.0);
+    const CclPlan cp = ccl_plan(P);
     struct Tr {
         Ev *e;
         hipStream_t s;
@@ -1849,6 +1914,7 @@ int vlg_profile(vlg_ctx *c, const vlg_formula *cf, const vlg_image *img, int ite
     for (size_t si = 0; si < P.steps.size(); si++) {
         const SK kind = P.steps[si].kind;
         if ((pj || vol) && (kind == SK::CclMerge || kind == SK::CclFlag)) continue;  // not run
+        if (kind == SK::CclFlag && !cp.multi[si]) continue;                           // nothing to launch
         const char *nm = vol && kind == SK::CclLocal    ? "vol_label"
                          : vol && kind == SK::CclGather ? "vol_gather"
                          : vol && kind == SK::CclReseed ? "vol_reseed"
@@ -1933,7 +1999,9 @@ int vlg_profile_batch(vlg_ctx *c, const vlg_formula *cf, const vlg_image *const 
         if (e) (void)hipEventDestroy(e);
     if (rc != VLG_OK) return rc;
     std::vector<vlg_kernel_time> kinds;
+    const CclPlan cp = ccl_plan(P);
     for (size_t si = 0; si < P.steps.size(); si++) {
+        if (P.steps[si].kind == SK::CclFlag && !cp.multi[si]) continue;  // nothing to launch
         const char *nm = kind_name(P.steps[si].kind);
         auto it = std::find_if(kinds.begin(), kinds.end(),
                                [&](const vlg_kernel_time &k) { return std::strcmp(k.name, nm) == 0; });
@@ -1985,8 +2053,13 @@ int vlg_profile_step(vlg_ctx *c, const vlg_formula *cf, const vlg_image *img, co
     *bytes = 0.0;
     if (g.nwords == 0) return VLG_OK;
     size_t at = SIZE_MAX;
-    for (size_t si = 0; si < P.steps.size() && at == SIZE_MAX; si++)
-        if (P.steps[si].kind == sk && P.steps[si].group < 0) at = si;
+    const CclPlan cp = ccl_plan(P);
+    for (size_t si = 0; si < P.steps.size(); si++) {
+        // (a flag pass that has something to launch, if there is one)
+        if (P.steps[si].kind != sk || P.steps[si].group >= 0) continue;
+        if (at == SIZE_MAX || (sk == SK::CclFlag && cp.multi[si])) at = si;
+        if (sk != SK::CclFlag || cp.multi[si]) break;
+    }
     if (at == SIZE_MAX) return fail(VLG_EINVAL, "the fused schedule has no single (ungrouped) step of kind " + k);
     const bool pj = !vol && P.ccl_count > 0 && ccl_algo(c, img->H, img->W) == VLG_CCL_POINTER_JUMPING;
     if (pj) return fail(VLG_EINVAL, "not with the pointer-jumping labelling (its rounds wait on the host)");
@@ -2031,7 +2104,7 @@ int vlg_profile_step(vlg_ctx *c, const vlg_formula *cf, const vlg_image *img, co
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (rc != VLG_OK) return rc;
-    *avg_ms = (ms - ms_prefix) / reps;
+    *avg_ms = std::max(0.0f, ms - ms_prefix) / reps;
     *bytes = algorithmic_bytes(P, P.steps[at], g, img->dtype, tuning_for(c, img->H, img->W).ccl_tbh);
     return check_status(c);
 }

@@ -76,14 +76,84 @@ struct LoopGuard {
     int cap;               // iterations per walk (>= 1)
 };
 
-struct CclWork {
-    int32_t *glab;       // [BH*BW] parent pointers (block ids, row-major)
-    uint8_t *gflag;      // [BH*BW] local roots: bit0 touches the tile border,
-                         // bit 1+u meets the seeds of labelling user u
-    unsigned long long *counters; // [2] merge unions, merge retries (may be null)
-    int tbh = kTileBHDefault;     // block rows per labelling tile
-    LoopGuard guard{nullptr, kLoopCapDefault};
+// Arrays of one labelling (ccl.hip), in a workspace of ccl_bytes(g, tbh):
+//   lab   [BH][BW] uint16   label of the k-th run of a tile's block row, at
+//                           the row's k-th block of the tile
+//   par   [1 + nodes] int32 union-find parents of the nodes: node id
+//                           tile * np + rank + 1 is the rank-th component of
+//                           the tile that touches a border shared with
+//                           another tile; node 0 stands for "meets the seeds"
+//   per   [nodes] uint16    the tiles' border blocks: rank | block bits << 8
+//   cnt   [tiles] uint32    nodes of each tile
+//   flag  [1 + nodes] uint8 seed bits of a root node (bit 1+u: labelling user u)
+//   useed [tiles][th][sb]   seeded inner components of the latest user u >= 1,
+//                           one bit per block of the tile
+// with np node slots per tile: one per block on a border that has a neighbour.
+struct CclGeo {
+    int32_t ntx, nty;  // tiles
+    int32_t tbh;       // block rows per tile
+    int32_t tw, th;    // blocks of a full tile of this image
+    int32_t np;        // node slots per tile
+    int32_t sb;        // bytes per useed row
+    int32_t lr, ud;    // tiles have neighbours left/right, above/below
 };
+__host__ __device__ inline CclGeo ccl_geo(const Geo &g, int tbh) {
+    CclGeo q;
+    q.tbh = tbh;
+    q.ntx = (g.BW + kTileBW - 1) / kTileBW;
+    q.nty = (g.BH + tbh - 1) / tbh;
+    q.tw = g.BW < kTileBW ? g.BW : kTileBW;
+    q.th = g.BH < tbh ? g.BH : tbh;
+    q.lr = q.ntx > 1;
+    q.ud = q.nty > 1;
+    q.np = (q.ud ? 2 * q.tw : 0) + (q.lr ? 2 * q.th : 0);
+    q.sb = (q.tw + 7) / 8;
+    return q;
+}
+// A workgroup of the tile passes takes 64 block rows: 64 / tbh tiles side by side.
+__host__ __device__ inline int ccl_groups_x(const CclGeo &q) { return (q.ntx * q.tbh + 63) / 64; }
+struct CclArrays {
+    uint16_t *lab;
+    int32_t *par;
+    uint16_t *per;
+    uint32_t *cnt;
+    uint8_t *flag;
+    uint8_t *useed;
+    size_t bytes;
+};
+__host__ __device__ inline CclArrays ccl_arrays(void *base, const Geo &g, const CclGeo &q) {
+    const size_t nt = (size_t)q.ntx * q.nty, nodes = nt * q.np;
+    CclArrays a;
+    char *p = (char *)base;
+    size_t o = 0;
+    a.useed = (uint8_t *)p;
+    o += (nt * q.th * q.sb + 7) & ~(size_t)7;
+    a.lab = (uint16_t *)(p + o);
+    o += ((size_t)g.BH * g.BW * 2 + 3) & ~(size_t)3;
+    a.par = (int32_t *)(p + o);
+    o += (nodes + 1) * 4;
+    a.cnt = (uint32_t *)(p + o);
+    o += nt * 4;
+    a.flag = (uint8_t *)(p + o);
+    o += (nodes + 1 + 3) & ~(size_t)3;
+    a.per = (uint16_t *)(p + o);
+    o += nodes * 2;
+    a.bytes = o;
+    return a;
+}
+inline size_t ccl_bytes(const Geo &g, int tbh) { return ccl_arrays(nullptr, g, ccl_geo(g, tbh)).bytes; }
+// Workspace reserved for one labelling: 5 bytes per 2x2 block.  Tiles of the
+// wanted height need less on all but narrow or low images, where the shared
+// borders outweigh the inner blocks; those take the next taller tiles that
+// fit (32 block rows always do).
+inline size_t ccl_workspace(const Geo &g) {
+    const size_t nb = (size_t)g.BH * g.BW;
+    return ((nb * 4 + 255) & ~(size_t)255) + ((nb + 255) & ~(size_t)255);
+}
+inline int ccl_fit_tbh(const Geo &g, int tbh) {
+    while (tbh < 32 && ccl_bytes(g, tbh) > ccl_workspace(g)) tbh *= 2;
+    return tbh;
+}
 
 constexpr int kMaxAtomsPerLaunch = 32;
 
@@ -101,30 +171,35 @@ hipError_t launch_logic(hipStream_t s, const Geo &g, MRef x, MRef y, int op, int
 hipError_t launch_near(hipStream_t s, const Geo &g, MRef x, int inv_out, MRef z, int zop, uint64_t *out,
                        int rows = 0);
 hipError_t launch_atoms(hipStream_t s, const Geo &g, const void *chan, int dtype, const AtomLaunch &a);
-hipError_t launch_ccl_local(hipStream_t s, const Geo &g, MRef b, MRef y, MRef z, const CclWork &w);
-hipError_t launch_ccl_merge(hipStream_t s, const Geo &g, MRef b, const CclWork &w);
-hipError_t launch_ccl_flag(hipStream_t s, const Geo &g, const CclWork &w);
-hipError_t launch_ccl_gather(hipStream_t s, const Geo &g, MRef b, MRef y, MRef z, const CclWork &w,
-                             int user, uint64_t *out);
-hipError_t launch_ccl_reseed(hipStream_t s, const Geo &g, MRef sm, const CclWork &w, int user);
 
-// Several independent labellings of one image in each launch (blockIdx.y =
-// labelling): each with its own passable mask b, seeds y & z, workspace
-// (glab, gflag) and, for the gather, its user bit and output.
+// Independent labellings of one image in each launch (blockIdx.y = labelling).
+// A labelling of one user (multi = 0) unites the components that meet its
+// seeds with node 0; with several users (multi = 1) every user u has a flag
+// bit at the roots, set by the flag pass (u = 0) or the reseed pass (u >= 1)
+// before its gather.
 constexpr int kMaxMulti = 8;
-struct CclMulti {
-    int n;
-    MRef b[kMaxMulti], y[kMaxMulti], z[kMaxMulti];
-    int32_t *glab[kMaxMulti];
-    uint8_t *gflag[kMaxMulti];
-    int user[kMaxMulti];
-    uint64_t *out[kMaxMulti];
+struct CclOp {
+    MRef b, y, z;   // passable mask; seeds N(y & z) & b (reseed: y = the seed mask)
+    void *ws;       // workspace
+    int32_t user, multi;
+    uint64_t *out;  // gather: (y & z) | components of b that meet the seeds
 };
-// w supplies the tile height, loop guard and counters (its arrays are unused)
-hipError_t launch_ccl_local_multi(hipStream_t s, const Geo &g, const CclMulti &m, const CclWork &w);
-hipError_t launch_ccl_merge_multi(hipStream_t s, const Geo &g, const CclMulti &m, const CclWork &w);
-hipError_t launch_ccl_flag_multi(hipStream_t s, const Geo &g, const CclMulti &m, const CclWork &w);
-hipError_t launch_ccl_gather_multi(hipStream_t s, const Geo &g, const CclMulti &m);
+struct CclMulti {
+    int n, tbh;     // labellings, block rows per tile
+    LoopGuard guard;
+    unsigned long long *counters;  // [2] merge unions, merge retries (may be null)
+    CclOp op[kMaxMulti];
+};
+hipError_t launch_ccl_local(hipStream_t s, const Geo &g, const CclMulti &m);
+hipError_t launch_ccl_merge(hipStream_t s, const Geo &g, const CclMulti &m);
+hipError_t launch_ccl_flag(hipStream_t s, const Geo &g, const CclMulti &m);    // entries with multi = 1 only
+hipError_t launch_ccl_reseed(hipStream_t s, const Geo &g, const CclMulti &m);
+hipError_t launch_ccl_gather(hipStream_t s, const Geo &g, const CclMulti &m);
+// The whole labelling of op[0].b into int32 labels: the smallest row-major
+// pixel index of each component, -1 for background.  ncanon: one int32 per
+// node and one more, icanon: one per block.
+hipError_t launch_ccl_labels(hipStream_t s, const Geo &g, const CclMulti &m, int32_t *ncanon, int32_t *icanon,
+                             int32_t *labels);
 
 constexpr int kBatchMax = 16;
 struct LogicOp {
@@ -149,9 +224,6 @@ struct NearBatch {
 };
 hipError_t launch_logic_batch(hipStream_t s, const Geo &g, const LogicBatch &b);
 hipError_t launch_near_batch(hipStream_t s, const Geo &g, const NearBatch &b, int rows = 0);
-// canon: [BH*BW] int32 scratch
-hipError_t launch_ccl_labels(hipStream_t s, const Geo &g, MRef b, const CclWork &w, int32_t *canon,
-                             int32_t *labels);
 hipError_t launch_unpack(hipStream_t s, const Geo &g, const uint64_t *mask, uint8_t *out);
 
 // Arithmetic atoms (arith.hip): postfix programs over channel values,
@@ -302,7 +374,7 @@ struct BImg {
     int64_t chan_bytes;     // bytes per channel
     char *ws;               // this image's workspace: mask slots, labelling, percentiles
     uint64_t mask_bytes;    // slot stride
-    uint64_t off_glab, off_gflag, off_pct, off_pctst;
+    uint64_t off_ccl, off_pct, off_pctst;
     uint64_t *const *outs;  // packed output buffer per external slot
     const uint32_t *ranks;  // percentile rank per percentile slot
 };
@@ -314,7 +386,7 @@ struct BRef {
     uint32_t inv;
 };
 
-enum BatchKind { BK_WORDS = 0, BK_LOGIC, BK_NEAR, BK_TILES, BK_MERGE, BK_BLOCKS, BK_FLAG, BK_GATHER, BK_PCTH, BK_ONE, BK_COUNT };
+enum BatchKind { BK_WORDS = 0, BK_LOGIC, BK_NEAR, BK_TILES, BK_MERGE, BK_FLAG, BK_PCTH, BK_ONE, BK_COUNT };
 
 struct BatchArgs {
     int n;
@@ -355,12 +427,16 @@ int64_t batch_units(const Geo &g, int kind, int tbh);
 hipError_t launch_b_atoms(hipStream_t s, const BatchArgs &a, int64_t total, const BAtoms &op);
 hipError_t launch_b_logic(hipStream_t s, const BatchArgs &a, int64_t total, const BLogic &op);
 hipError_t launch_b_near(hipStream_t s, const BatchArgs &a, int64_t total, const BNear &op);
-hipError_t launch_b_ccl_local(hipStream_t s, const BatchArgs &a, int64_t total, int tbh, BRef b, BRef y, BRef z);
-hipError_t launch_b_ccl_merge(hipStream_t s, const BatchArgs &a, int64_t total, int tbh, BRef b);
-hipError_t launch_b_ccl_flag(hipStream_t s, const BatchArgs &a, int64_t total);
-hipError_t launch_b_ccl_gather(hipStream_t s, const BatchArgs &a, int64_t total, BRef b, BRef y, BRef z, int user,
-                               int32_t out);
-hipError_t launch_b_ccl_reseed(hipStream_t s, const BatchArgs &a, int64_t total, BRef sm, int user);
+// a labelling step of a batch (the fields as in CclOp)
+struct BCcl {
+    BRef b, y, z;
+    int32_t user, multi, out, tbh;
+};
+hipError_t launch_b_ccl_local(hipStream_t s, const BatchArgs &a, int64_t total, const BCcl &o);
+hipError_t launch_b_ccl_merge(hipStream_t s, const BatchArgs &a, int64_t total, const BCcl &o);
+hipError_t launch_b_ccl_flag(hipStream_t s, const BatchArgs &a, int64_t total, const BCcl &o);
+hipError_t launch_b_ccl_reseed(hipStream_t s, const BatchArgs &a, int64_t total, const BCcl &o);
+hipError_t launch_b_ccl_gather(hipStream_t s, const BatchArgs &a, int64_t total, const BCcl &o);
 // up to kMaxPctSel quantiles of one channel: rank k[j] (single image; a batch
 // takes each image's ranks from its descriptor) into percentile slot slot[j]
 constexpr int kMaxPctSel = 4;

@@ -1,130 +1,24 @@
 // kernels.hip -- HIP kernels for gfx950 (CDNA4, wave64) on 1-bit-packed masks.
 //
 // Operators (paper "A spatial model checker in GPU", Sect. 2): threshold
-// atoms, pixel-wise Boolean connectives, N (Moore-neighbourhood dilation) and
-// reachability rho a[b].  rho follows the decomposition of Sect. 3: label the
-// 8-connected components of b, keep the components that meet N a, and dilate
-// their union with a.  The labelling is not the paper's iterative
-// pointer-jumping scheme (Alg. CCL) but union-find over 2x2 pixel blocks
-// (every foreground pixel of a 2x2 block lies in one 8-component), run as a
-// tile-local pass in LDS followed by a global merge of tile borders with
-// atomicMin hooking, so it needs a fixed number of launches and no host-side
-// termination check.
+// atoms, pixel-wise Boolean connectives, N (Moore-neighbourhood dilation),
+// fused segments of the last two, and the radix-select
+// percentiles.  The reachability labelling is in ccl.hip.
 //
 // Every operator is written once as a per-unit device function; single-image
 // kernels walk one image's units, batch kernels walk the units of many
 // images of different sizes through per-image descriptors.
-#include "kernels.h"
+#include "dev.h"
 
 #include <algorithm>
 
 namespace vlg {
 namespace {
 
-constexpr int kThreads = 256;
 // channel elements per batched histogram unit: large enough that flushing a
 // workgroup's LDS histograms (up to 8192 bins, global atomics that all units
 // of an image aim at the same addresses) stays small next to the reads
 constexpr int64_t kPctUnit = 262144;
-
-__device__ __forceinline__ uint32_t fdiv(uint32_t n, uint32_t mul, uint32_t shift) {
-    return (uint32_t)(((uint64_t)__umulhi(n, mul) + n) >> shift);
-}
-
-// Pointers read from descriptors in memory have no known address space and
-// would be accessed with flat instructions, which also count against the LDS
-// wait counter; every mask, label and image access therefore goes through a
-// global-qualified pointer.
-#define VLG_GLOBAL __attribute__((address_space(1)))
-template <typename T>
-__device__ __forceinline__ VLG_GLOBAL T *glb(T *p) {
-    return (VLG_GLOBAL T *)p;
-}
-template <typename T>
-__device__ __forceinline__ const VLG_GLOBAL T *glb(const T *p) {
-    return (const VLG_GLOBAL T *)p;
-}
-// Constant address space: for tables that no kernel writes while it runs
-// (the per-image descriptors of a batched launch).  A wave-uniform index into
-// them becomes a scalar load whose result stays in scalar registers.
-#define VLG_CONST __attribute__((address_space(4)))
-
-__device__ __forceinline__ uint64_t ldm(const MRef &r, int64_t i) {
-    return (r.p ? glb(r.p)[i] : 0ull) ^ r.inv;
-}
-
-__device__ __forceinline__ bool is_last_col(const Geo &g, int64_t i) {
-    uint32_t row = fdiv((uint32_t)i, g.wpr_mul, g.wpr_shift);
-    return (uint32_t)i - row * (uint32_t)g.wpr == (uint32_t)(g.wpr - 1);
-}
-
-__device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & 63); }
-
-// Workgroups are dispatched to the 8 XCDs in turn (workgroup i to XCD
-// i mod 8), and each XCD has an L2 of its own.  The work item of workgroup b
-// of n: each XCD takes a contiguous range of items, so that neighbouring
-// tiles, which share the cache lines of their mask words, meet in one L2
-// instead of each line being fetched by several.  A bijection of [0, n).
-__device__ __forceinline__ int xcd_contiguous(int b, int n) {
-    constexpr int X = 8;
-    const int per = n / X, rem = n % X, x = b % X, k = b / X;
-    return x * per + (x < rem ? x : rem) + k;
-}
-
-int grid_for(int64_t n, int per_block, int cap) {
-    int64_t b = (n + per_block - 1) / per_block;
-    if (b < 1) b = 1;
-    if (b > cap) b = cap;
-    return (int)b;
-}
-
-// ------------------------------------------------------------------ batches
-// image of global unit u: the largest i with prefix[i] <= u
-__device__ __forceinline__ int find_img(const int64_t *prefix, int n, int64_t u) {
-    int lo = 0, hi = n;
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (prefix[mid] <= u) lo = mid;
-        else hi = mid;
-    }
-    return lo;
-}
-
-// A workgroup of a persistent batch kernel takes a contiguous range of the
-// launch's global units, finds the image of its first unit by binary search
-// and then only steps forward (units of one image are consecutive).  Kernels
-// copy the image's descriptor into registers per unit: read through a
-// reference into memory, its fields would be reloaded after every LDS store
-// or atomic (a generic pointer may alias LDS).
-struct UnitRange {
-    const int64_t *prefix;
-    int64_t begin, end, next;
-    int ii;
-    __device__ UnitRange(const int64_t *p, int n) : prefix(p) {
-        const int64_t total = p[n];
-        begin = total * blockIdx.x / gridDim.x;
-        end = total * (blockIdx.x + 1) / gridDim.x;
-        ii = begin < end ? find_img(p, n, begin) : 0;
-        next = begin < end ? p[ii + 1] : 0;
-    }
-    __device__ __forceinline__ int img(int64_t u) {
-        while (u >= next) next = prefix[++ii + 1];
-        return ii;
-    }
-};
-
-__device__ __forceinline__ uint64_t *bptr(const BImg &d, int32_t slot) {
-    if (slot == -1) return nullptr;
-    if (slot <= -2) return glb(d.outs)[-2 - slot];
-    return (uint64_t *)(d.ws + (uint64_t)slot * d.mask_bytes);
-}
-
-__device__ __forceinline__ MRef bref(const BImg &d, const BRef &r) {
-    MRef m;
-    m.p = bptr(d, r.slot);
-    m.inv = r.inv ? ~0ull : 0ull;
-    return m;
-}
 
 // ------------------------------------------------------------------ Boolean
 // out = ((x ^ x.inv) OP (y ^ y.inv)) ^ inv_out, OP = and (op 0) / or (op 1).
@@ -359,768 +253,6 @@ __device__ __forceinline__ void atoms_task(const Geo &g, const T *__restrict__ i
     }
 }
 
-// ------------------------------------------------------------------ CCL
-// Blocks: block (by, bx) holds pixels rows 2by..2by+1, cols 2bx..2bx+1.  Its
-// four bits: 1 = top-left, 2 = top-right, 4 = bottom-left, 8 = bottom-right.
-// Any two foreground pixels of one block are 8-adjacent, so a block is a
-// union-find node.  Block ids are row-major, id = by*BW + bx.  Inside a tile
-// the root of a set is its smallest id; across tiles roots are linked by a
-// pseudo-random priority of their ids (see g_unite).  Canonical pixel labels
-// therefore take a minimum over each component.
-//
-// 8-adjacency between a block and its earlier neighbours:
-//   left:       (tl|bl) of the block and (tr|br) of the left block
-//   up:         (tl|tr) and (bl|br) of the upper block
-//   up-left:    tl and br of the upper-left block
-//   up-right:   tr and bl of the upper-right block
-
-__device__ __forceinline__ int lds_ld(int *p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
-// Value of v in the previous lane of the wave (DPP wave shift right by one;
-// lane 0 receives 0).
-__device__ __forceinline__ int lane_prev(int v) {
-    return __builtin_amdgcn_update_dpp(0, v, 0x138, 0xf, 0xf, false);
-}
-// Value of v in the next lane of the wave (DPP wave shift left by one; lane
-// 63 receives 0).
-__device__ __forceinline__ int lane_next(int v) {
-    return __builtin_amdgcn_update_dpp(0, v, 0x130, 0xf, 0xf, false);
-}
-
-// Union of a and b on the LDS forest L (L[x] <= x, a root is the smallest
-// entry of its set).  Both walks advance together, one path-halving step per
-// round, so their LDS latencies overlap; once both reach roots the larger
-// root is hooked under the smaller with atomicMin, and if that root was
-// hooked meanwhile the returned parent is united in its place.  Halving
-// stores may race with other lanes' hooks; the hooking lane then unites the
-// old parent as well, so no connection is lost.  At most `cap` rounds:
-// returns false when the cap stops the walk (the union may be missing).
-__device__ __forceinline__ bool lds_unite(int *L, int a, int b, int cap) {
-    for (int it = 0; a != b; it++) {
-        if (it >= cap) return false;
-        const int pa = lds_ld(&L[a]), pb = lds_ld(&L[b]);
-        if (pa == a && pb == b) {
-            const int hi = a > b ? a : b, lo = a > b ? b : a;
-            const int old = atomicMin(&L[hi], lo);
-            if (old == hi) return true;
-            a = old;
-            b = lo;
-            continue;
-        }
-        const int ga = pa != a ? lds_ld(&L[pa]) : pa, gb = pb != b ? lds_ld(&L[pb]) : pb;
-        if (pa != a) {
-            if (ga != pa) L[a] = ga;
-            a = ga;
-        }
-        if (pb != b) {
-            if (gb != pb) L[b] = gb;
-            b = gb;
-        }
-    }
-    return true;
-}
-
-// Root of x once all unions are done.  Path halving here goes through
-// atomicMin: the root is the smallest entry of its set, so a stale halving
-// store can never replace a root that its owner has already written.  At
-// most `cap` rounds; when the cap stops the walk, ok is cleared and the
-// ancestor reached so far (a block of the same tile) is returned.
-__device__ __forceinline__ int lds_root(int *L, int x, int cap, bool &ok) {
-    for (int it = 0; it < cap; it++) {
-        const int p = lds_ld(&L[x]);
-        if (p == x) return x;
-        const int gp = lds_ld(&L[p]);
-        if (gp == p) return p;
-        __hip_atomic_fetch_min(&L[x], gp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        x = gp;
-    }
-    ok = false;
-    return x;
-}
-
-// Raise the give-up flag of a launch (one vector atomic per wave).
-// Called by every lane of the wave.
-__device__ __forceinline__ void guard_report(const LoopGuard &gd, bool ok) {
-    const uint64_t bad = __ballot(!ok);
-    if (bad && lane_id() == __builtin_ctzll(bad) && gd.status)
-        __hip_atomic_fetch_or(glb(gd.status), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Cross-lane handoff through LDS inside one wave: every lane's LDS writes
-// before this point are complete (and visible to the other lanes) before any
-// lane's LDS reads after it.  The workgroup-scope fences order the accesses
-// for the compiler and wait for the outstanding LDS operations; the wave
-// barrier keeps the lanes together.
-__device__ __forceinline__ void wave_lds_handoff() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-}
-
-// Global union-find for the cross-tile merge.  A root is hooked under the
-// root of smaller priority uf_prio(id), a bijective mix of the id, so the
-// priority strictly falls along every parent path.  Linking by id instead
-// turns a row of tiles whose components join left to right (a corridor
-// crossing the image) into a chain as long as the row, because every tile
-// hooks under its left neighbour at the same time; pseudo-random priorities
-// keep the expected depth logarithmic.  Plain loads and stores may see stale
-// values (the L2 of one XCD is not coherent with another's within a kernel);
-// that costs retries, never correctness: every value ever stored in L[x] is
-// an ancestor of x, sets only grow, and a hook is a compare-and-swap that
-// succeeds only on a current root and otherwise hands back the current
-// parent, which is then united in turn.
-//
-// g_find2: the roots of a and b, walked in lockstep (path halving on both) so
-// that the loads of the two paths overlap.  `budget` counts the rounds left
-// to the caller's walk; returns false when it runs out.
-__device__ __forceinline__ bool g_find2(VLG_GLOBAL int *L, int &a, int &b, int &budget) {
-    while (true) {
-        if (--budget < 0) return false;
-        const int pa = L[a], pb = L[b];
-        if (pa == a && pb == b) return true;
-        const int ga = L[pa], gb = L[pb];
-        if (pa != a) {
-            if (ga == pa) {
-                a = pa;
-            } else {
-                L[a] = ga;  // path halving
-                a = ga;
-            }
-        }
-        if (pb != b) {
-            if (gb == pb) {
-                b = pb;
-            } else {
-                L[b] = gb;
-                b = gb;
-            }
-        }
-    }
-}
-
-__device__ __forceinline__ uint32_t uf_prio(int x) {
-    uint32_t h = (uint32_t)x * 0x9E3779B1u;  // odd multiplier: a bijection
-    return h ^ (h >> 16);                     // invertible xor-shift
-}
-
-// Unite a and b; returns the number of hook attempts, and clears ok when the
-// walk used up `cap` rounds (finds and hooks together) before it finished.
-__device__ int g_unite(VLG_GLOBAL int *L, int a, int b, int cap, bool &ok) {
-    int tries = 0, budget = cap;
-    while (true) {
-        tries++;
-        if (!g_find2(L, a, b, budget)) {
-            ok = false;
-            return tries;
-        }
-        if (a == b) return tries;
-        if (uf_prio(a) < uf_prio(b)) {
-            const int t = a;
-            a = b;
-            b = t;
-        }
-        int old = a;  // hook a (larger priority) under b if a is still a root
-        __hip_atomic_compare_exchange_strong(&L[a], &old, b, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                             __HIP_MEMORY_SCOPE_AGENT);
-        if (old == a) return tries;
-        a = old;
-    }
-}
-
-__device__ __forceinline__ uint32_t block_bits_g(const Geo &g, const MRef &b, int by, int bx) {
-    const int w = bx >> 5, sh = (bx & 31) * 2, y0 = 2 * by;
-    const uint64_t keep = w == g.wpr - 1 ? g.tail : ~0ull;
-    const uint64_t t = ldm(b, (int64_t)y0 * g.wpr + w) & keep;
-    const uint64_t u = y0 + 1 < g.H ? (ldm(b, (int64_t)(y0 + 1) * g.wpr + w) & keep) : 0ull;
-    return (uint32_t)((t >> sh) & 3) | ((uint32_t)((u >> sh) & 3) << 2);
-}
-
-// Threads per workgroup of the tile-local pass: four block rows per wave at
-// most (TBH = 32 takes eight waves), which bounds the per-row state each
-// lane keeps in registers.
-template <int TBH>
-constexpr int ccl_local_threads() {
-    return TBH > 16 ? 512 : 256;
-}
-
-// Tile-local labelling of b: TBH block rows x 64 block columns (2*TBH x 128
-// pixels) per workgroup of NWAVES waves.  Wave v owns the RPW consecutive
-// block rows RPW*v .. RPW*v+RPW-1, one lane per block column, and keeps each
-// row's block state in a register from the first phase to the last.  Horizontally
-// connected blocks form runs, found with a ballot and labelled by their first
-// block without any atomics.  Runs of consecutive rows are then united once
-// per touching pair (a block skips the upper runs its connected left
-// neighbour already touches).  Also computes the seed test: a block meets the
-// seeds when one of its b-pixels lies in N(y & z).
-//
-// Output: glab[id] = global id of the foreground block's tile-local root
-// (background entries are left as they are); gflag[id] of a local root:
-// bit0 = its component touches the tile border (only those can be joined to
-// other tiles), bit1 = it meets the seeds (seed set of labelling user 0;
-// bits 2..7 serve later users, see ccl_reseed).
-template <int TBH>
-__device__ void ccl_local_tile(const Geo &g, const MRef &b, const MRef &y, const MRef &z, int tx, int ty,
-                               int32_t *__restrict__ glab_, uint8_t *__restrict__ gflag_, const LoopGuard &gd) {
-    VLG_GLOBAL int32_t *glab = glb(glab_);
-    VLG_GLOBAL uint8_t *gflag = glb(gflag_);
-    constexpr int NT = ccl_local_threads<TBH>();
-    constexpr int TWW = 2, TR = 2 * TBH, TBW = 64, NB = TBH * TBW, NWAVES = NT / 64;
-    constexpr int RPW = TBH / NWAVES;
-    static_assert(RPW * NWAVES == TBH, "tile rows must split evenly over the waves");
-    constexpr int NSB = TR * TWW, NSA = (TR + 2) * (TWW + 2), NLD = NSB + NSA;
-    constexpr int LIT = (NLD + NT - 1) / NT;
-    __shared__ uint64_t sb[TR][TWW];
-    __shared__ uint64_t sa[TR + 2][TWW + 2];
-    __shared__ int L[NB];
-    __shared__ uint16_t sbr[NB];              // block bits | run start column << 4
-    __shared__ alignas(4) uint8_t sflag[NB];  // bit0 touches the tile border, bit1 seed
-    __shared__ int sany;
-    constexpr int kPairQueue = 192;              // union pairs per wave: me | other << 16
-    __shared__ int spair[NWAVES][kPairQueue];
-    // the thread index is made opaque per tile so that a persistent
-    // workgroup recomputes its per-row addressing in each tile instead of
-    // holding it in registers across the whole tile loop
-    int tid = (int)threadIdx.x;
-    asm volatile("" : "+v"(tid));
-    const int lane = tid & 63, wave = tid >> 6;
-    const int r0 = ty * TR, wc0 = tx * TWW;
-
-    // b words of the tile and (y & z) words of the tile plus a one-pixel halo,
-    // all loads in flight at once; sany: bit0 = some b pixel, bit1 = some seed
-    if (tid == 0) sany = 0;
-    __syncthreads();
-    int any;
-    {
-        uint64_t v[LIT];
-#pragma unroll
-        for (int k = 0; k < LIT; k++) {
-            const int i = tid + k * NT;
-            v[k] = 0;
-            if (i < NSB) {
-                const int yy = r0 + i / TWW, ww = wc0 + i % TWW;
-                if (yy < g.H && ww < g.wpr) v[k] = ldm(b, (int64_t)yy * g.wpr + ww) & (ww == g.wpr - 1 ? g.tail : ~0ull);
-            } else if (i < NLD) {
-                const int j = i - NSB, yy = r0 + j / (TWW + 2) - 1, ww = wc0 + j % (TWW + 2) - 1;
-                if (yy >= 0 && yy < g.H && ww >= 0 && ww < g.wpr) {
-                    const int64_t idx = (int64_t)yy * g.wpr + ww;
-                    v[k] = ldm(y, idx) & ldm(z, idx) & (ww == g.wpr - 1 ? g.tail : ~0ull);
-                }
-            }
-        }
-        bool has_b = false, has_s = false;
-#pragma unroll
-        for (int k = 0; k < LIT; k++) {
-            const int i = tid + k * NT;
-            if (i < NSB) {
-                sb[i / TWW][i % TWW] = v[k];
-                has_b |= v[k] != 0;
-            } else if (i < NLD) {
-                const int j = i - NSB;
-                sa[j / (TWW + 2)][j % (TWW + 2)] = v[k];
-                has_s |= v[k] != 0;
-            }
-        }
-        const int f = (__ballot(has_b) ? 1 : 0) | (__ballot(has_s) ? 2 : 0);
-        if (lane == 0 && f) atomicOr(&sany, f);
-        __syncthreads();
-        any = sany;
-    }
-    // a tile without passable pixels only clears its flag bytes (the flag pass
-    // reads every block's; no pass reads a background block's parent entry)
-    if (!(any & 1)) {
-        for (int i = tid; i < NB; i += NT) {
-            const int by = ty * TBH + i / TBW, bx = tx * TBW + i % TBW;
-            if (by < g.BH && bx < g.BW) gflag[(int64_t)by * g.BW + bx] = 0;
-        }
-        __syncthreads();  // sany is reset by the next tile of a persistent workgroup
-        return;
-    }
-
-    // rows: block bits, runs, seeds.  st[j] (row RPW*wave + j) = bits | run << 4 |
-    // seed << 10 | (connected to the left block) << 11
-    const int w = lane >> 5, sh = (lane & 31) * 2;
-    uint32_t st[RPW];
-#pragma unroll
-    for (int j = 0; j < RPW; j++) {
-        const int lby = RPW * wave + j, i = lby * TBW + lane;
-        const uint32_t bits = (uint32_t)((sb[2 * lby][w] >> sh) & 3) | ((uint32_t)((sb[2 * lby + 1][w] >> sh) & 3) << 2);
-        uint32_t seed = 0;
-        if (any & 2) {
-            // seed pixels in the 4x4 window around the block: rows 2lby-1 ..
-            // 2lby+2, cols 2lbx-1 .. 2lbx+2 (halo coordinates: +1 row, +64 cols)
-            const int c = 64 * (w + 1) + sh - 1, q = c >> 6, s = c & 63;
-            uint32_t win[4];
-#pragma unroll
-            for (int k = 0; k < 4; k++) {
-                const uint64_t lo = sa[2 * lby + k][q] >> s;
-                const uint64_t hi = s > 60 ? (sa[2 * lby + k][q + 1] << (64 - s)) : 0ull;
-                win[k] = (uint32_t)((lo | hi) & 0xF);
-            }
-            const uint32_t top = win[0] | win[1] | win[2], bot = win[1] | win[2] | win[3];
-            const uint32_t nmask = ((top & 0x7) ? 1u : 0u) | ((top & 0xE) ? 2u : 0u) |
-                                   ((bot & 0x7) ? 4u : 0u) | ((bot & 0xE) ? 8u : 0u);
-            seed = (bits & nmask) ? 1u : 0u;
-        }
-        const uint32_t left = (uint32_t)lane_prev((int)bits);
-        const bool conn = lane > 0 && (bits & 5) && (left & 10);
-        const uint64_t starts = __ballot(bits != 0 && !conn);
-        const uint64_t upto = starts & (~0ull >> (63 - lane));
-        const int run = upto ? 63 - __builtin_clzll(upto) : lane;
-        st[j] = bits | ((uint32_t)run << 4) | (seed << 10) | (conn ? 1u << 11 : 0u);
-        if (j == RPW - 1) sbr[i] = (uint16_t)(bits | ((uint32_t)run << 4));  // read by the next wave's row 0
-        sflag[i] = (uint8_t)(seed << 1);
-        L[i] = bits ? lby * TBW + run : i;
-    }
-    auto st_bits = [](uint32_t s) { return s & 15u; };
-    auto st_run = [](uint32_t s) { return (int)((s >> 4) & 63u); };
-
-    // unite the runs of each row with the runs they touch in the row above.
-    // The wave first lists the pairs of all its rows (at most three per lane
-    // and row) in its LDS queue, then every lane takes pairs from the queue:
-    // a row's unions are usually held by a few lanes (the run starts), and
-    // taking them row by row in those lanes would chain the rows' union walks
-    // one after another.  Pairs beyond the queue's capacity are united by
-    // their own lane at once (after the barrier, when every entry of L is
-    // set).  The row above a wave's row j >= 1 is its row j-1, in registers
-    // (its neighbours' entries through DPP lane shifts), so those rows list
-    // their pairs before the barrier; only row 0 reads the row above, the
-    // previous wave's last row, from LDS after it.
-    int npairs = 0;  // wave-uniform
-    bool ok = true;  // no walk of this lane hit the loop cap
-    auto list_pairs = [&](int j, uint32_t ul, uint32_t uc, uint32_t ur) {
-        const int lby = RPW * wave + j;
-        const uint32_t bits = st_bits(st[j]);
-        int c0 = -1, c1 = -1, c2 = -1;
-        if (lby > 0 && bits) {
-            if ((bits & 1) && (ul & 8)) c0 = (int)(ul >> 4);
-            if ((bits & 3) && (uc & 12)) c1 = (int)(uc >> 4);
-            if ((bits & 2) && (ur & 4)) c2 = (int)(ur >> 4);
-        }
-        if (c1 == c0) c1 = -1;
-        if (c2 == c0 || c2 == c1) c2 = -1;
-        const int l0 = lane_prev(c0), l1 = lane_prev(c1), l2 = lane_prev(c2);
-        if (st[j] & (1u << 11)) {
-            // the left block is in this run and already joins its upper runs
-            if (c0 >= 0 && (c0 == l0 || c0 == l1 || c0 == l2)) c0 = -1;
-            if (c1 >= 0 && (c1 == l0 || c1 == l1 || c1 == l2)) c1 = -1;
-            if (c2 >= 0 && (c2 == l0 || c2 == l1 || c2 == l2)) c2 = -1;
-        }
-        const int me = lby * TBW + st_run(st[j]), ub = (lby - 1) * TBW;
-        const int cs[3] = {c0, c1, c2};
-#pragma unroll
-        for (int k = 0; k < 3; k++) {
-            const uint64_t has = __ballot(cs[k] >= 0);
-            if (cs[k] >= 0) {
-                const int q = npairs + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(has >> 32),
-                                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)has, 0u));
-                if (q < kPairQueue)
-                    spair[wave][q] = me | ((ub + cs[k]) << 16);
-                else
-                    ok &= lds_unite(L, me, ub + cs[k], gd.cap);
-            }
-            npairs += __popcll(has);
-        }
-    };
-    // (rows j >= 1 unite only blocks of this wave's rows, whose entries of L
-    // this wave has written: a wave-level handoff makes them visible)
-    wave_lds_handoff();
-#pragma unroll
-    for (int j = 1; j < RPW; j++) {
-        // block state of the row above: bits | run << 4, for lanes l-1, l, l+1
-        const uint32_t uc = st[j - 1] & 0x3FFu;
-        list_pairs(j, (uint32_t)lane_prev((int)uc), uc, (uint32_t)lane_next((int)uc));
-    }
-    __syncthreads();
-    {
-        const int up = (RPW * wave - 1) * TBW + lane;  // the previous wave's last row
-        const bool have = wave > 0;
-        const uint32_t ul = have && lane > 0 ? sbr[up - 1] : 0u, uc = have ? sbr[up] : 0u,
-                       ur = have && lane < 63 ? sbr[up + 1] : 0u;
-        list_pairs(0, ul, uc, ur);
-    }
-    wave_lds_handoff();  // the queue entries of every lane, then the reads
-    for (int q = lane; q < (npairs < kPairQueue ? npairs : kPairQueue); q += 64) {
-        const int pr = spair[wave][q];
-        ok &= lds_unite(L, pr & 0xFFFF, pr >> 16, gd.cap);
-    }
-    __syncthreads();
-
-    // resolve each run start; the other blocks of a run reach their root
-    // through their run start
-#pragma unroll
-    for (int j = 0; j < RPW; j++) {
-        const int i = (RPW * wave + j) * TBW + lane;
-        if (st_bits(st[j]) && st_run(st[j]) == lane) L[i] = lds_root(L, i, gd.cap, ok);
-    }
-    __syncthreads();
-
-    // every block's root (through its run start); carry seed and
-    // border-contact flags to the local roots (32-bit LDS atomics on the flag
-    // bytes)
-    int root[RPW];
-#pragma unroll
-    for (int j = 0; j < RPW; j++) root[j] = L[(RPW * wave + j) * TBW + st_run(st[j])];
-#pragma unroll
-    for (int j = 0; j < RPW; j++) {
-        const int lby = RPW * wave + j;
-        const uint32_t f = ((st[j] >> 9) & 2u) | ((lby == 0 || lby == TBH - 1 || lane == 0 || lane == TBW - 1) ? 1u : 0u);
-        if (st_bits(st[j]) && f) {
-            const int r = root[j];
-            atomicOr((unsigned int *)(sflag + (r & ~3)), f << (8 * (r & 3)));
-        }
-    }
-    __syncthreads();
-
-#pragma unroll
-    for (int j = 0; j < RPW; j++) {
-        const int lby = RPW * wave + j, i = lby * TBW + lane;
-        const int by = ty * TBH + lby, bx = tx * TBW + lane;
-        if (by >= g.BH || bx >= g.BW) continue;
-        const int64_t id = (int64_t)by * g.BW + bx;
-        // background blocks point at themselves: no later pass reads their
-        // parent entry (every lookup starts from a foreground block), but a
-        // wave that writes every entry of its row writes whole cache lines;
-        // leaving the background entries out made the memory side fetch the
-        // lines it had to merge (counters: 34 MB read per launch at 4096^2,
-        // against 6 MB of mask reads)
-        if (st_bits(st[j])) {
-            const int r = root[j];
-            glab[id] = (ty * TBH + r / TBW) * g.BW + tx * TBW + r % TBW;
-            gflag[id] = r == i ? sflag[i] : (uint8_t)0;
-        } else {
-            glab[id] = (int32_t)id;
-            gflag[id] = 0;
-        }
-    }
-    guard_report(gd, ok);
-    __syncthreads();  // the next tile of a persistent workgroup reuses the LDS
-}
-
-// Cross-tile merge, two waves per tile (part 0 the top row, part 1 the side
-// columns, so that the two chains of dependent global accesses run side by
-// side): blocks on the tile's top row, left column and right column unite
-// with their earlier neighbours in other tiles.
-// A block skips a union that its connected predecessor along the same border
-// (left neighbour on the top row, upper neighbour on a side column) already
-// makes with the same tile-local component.
-//
-// The wave first stages the mask words around the tile's border in LDS: pixel
-// rows 2*by0-4 .. 2*by0+2*TBH-1 and word columns 2*tx-1 .. 2*tx+2 (every block
-// any border block or its neighbours and predecessors touch), all loads in
-// flight at once.  Each lane then derives the block bits it needs from LDS and
-// loads the labels of its candidates and predecessors together before uniting.
-template <int TBH>
-constexpr int merge_window_words() {
-    return (2 * TBH + 4) * 4;
-}
-
-template <int TBH>
-__device__ void ccl_merge_tile(const Geo &g, const MRef &b, int ntx, int tile, int part, int32_t *glab_,
-                               uint64_t *win, int &unions, int &tries, const LoopGuard &gd) {
-    constexpr int TBW = 64, WN = merge_window_words<TBH>(), NL = (WN + 63) / 64;
-    VLG_GLOBAL int32_t *glab = glb(glab_);
-    const int lane = lane_id();
-    const int tx = tile % ntx, ty = tile / ntx;
-    const int by0 = ty * TBH, bx0 = tx * TBW;
-    const int r0 = 2 * by0 - 4, w0 = 2 * tx - 1;  // window origin: pixel row, word column
-    {
-        uint64_t v[NL];
-        int64_t idx[NL];
-#pragma unroll
-        for (int k = 0; k < NL; k++) {
-            const int i = lane + 64 * k, r = r0 + i / 4, w = w0 + (i & 3);
-            const bool ok = i < WN && r >= 0 && r < g.H && w >= 0 && w < g.wpr;
-            idx[k] = ok ? (int64_t)r * g.wpr + w : -1;
-            v[k] = b.p ? glb(b.p)[ok ? idx[k] : 0] : 0ull;
-        }
-#pragma unroll
-        for (int k = 0; k < NL; k++) {
-            const int i = lane + 64 * k, w = w0 + (i & 3);
-            if (i < WN) win[i] = idx[k] >= 0 ? ((v[k] ^ b.inv) & (w == g.wpr - 1 ? g.tail : ~0ull)) : 0ull;
-        }
-        wave_lds_handoff();  // every lane's window words, then the reads
-    }
-    // bits of block (by, bx), by in [by0-2, by0+TBH), bx in [bx0-2, bx0+64]
-    auto bits = [&](int by, int bx) -> uint32_t {
-        const int r = 2 * by - r0, p = 2 * bx - 64 * w0, q = p >> 6, sh = p & 63;
-        return (uint32_t)((win[r * 4 + q] >> sh) & 3) | ((uint32_t)((win[(r + 1) * 4 + q] >> sh) & 3) << 2);
-    };
-    bool ok = true;  // no walk of this lane hit the loop cap
-    auto link = [&](int id, int nid) {
-        unions++;
-        tries += g_unite(glab, id, nid, gd.cap, ok);
-    };
-
-    // top row: contacts with the row above (other tile): UL, U, UR
-    if (part == 0 && by0 > 0 && by0 < g.BH) {
-        const int by = by0, bx = bx0 + lane, id = by * g.BW + bx;
-        const uint32_t bb = bx < g.BW ? bits(by, bx) : 0u;
-        int c[3] = {-1, -1, -1}, p[3] = {-1, -1, -1};
-        if (bb) {
-            if (bx > 0 && (bb & 1) && (bits(by - 1, bx - 1) & 8)) c[0] = id - g.BW - 1;
-            if ((bb & 3) && (bits(by - 1, bx) & 12)) c[1] = id - g.BW;
-            if (bx + 1 < g.BW && (bb & 2) && (bits(by - 1, bx + 1) & 4)) c[2] = id - g.BW + 1;
-            // predecessor on this border row: the left block, if connected
-            if (lane > 0) {
-                const uint32_t lb = bits(by, bx - 1);
-                if ((bb & 5) && (lb & 10)) {
-                    if (bx - 1 > 0 && (lb & 1) && (bits(by - 1, bx - 2) & 8)) p[0] = id - g.BW - 2;
-                    if ((lb & 3) && (bits(by - 1, bx - 1) & 12)) p[1] = id - g.BW - 1;
-                    if ((lb & 2) && (bits(by - 1, bx) & 4)) p[2] = id - g.BW;
-                }
-            }
-        }
-        int pl[3], lc[3];
-#pragma unroll
-        for (int j = 0; j < 3; j++) {
-            pl[j] = p[j] >= 0 ? glab[p[j]] : -2;
-            lc[j] = c[j] >= 0 ? glab[c[j]] : -4;
-        }
-        const int my = bb ? glab[id] : -1;  // loaded with the others: the unions start from the labels
-        int done[2] = {-3, -3};
-#pragma unroll
-        for (int j = 0; j < 3; j++) {
-            if (c[j] < 0) continue;
-            if (lc[j] == pl[0] || lc[j] == pl[1] || lc[j] == pl[2] || lc[j] == done[0] || lc[j] == done[1]) continue;
-            done[j < 2 ? j : 1] = lc[j];
-            link(my, lc[j]);
-        }
-    }
-    // side columns: lanes 0..TBH-1 the left column, lanes 32..32+TBH-1 the right
-    const int lby = lane & 31, side = lane >> 5;
-    const int by = by0 + lby;
-    if (part == 1 && lby < TBH && by < g.BH) {
-        if (side == 0 && bx0 > 0 && bx0 < g.BW) {
-            // contacts in the column to the left (other tile): L, and UL below the top row
-            const int bx = bx0, id = by * g.BW + bx;
-            const uint32_t bb = bits(by, bx);
-            int c[2] = {-1, -1}, p[2] = {-1, -1};
-            if (bb) {
-                if ((bb & 5) && (bits(by, bx - 1) & 10)) c[0] = id - 1;
-                if (lby > 0 && (bb & 1) && (bits(by - 1, bx - 1) & 8)) c[1] = id - g.BW - 1;
-                // predecessor on this border column: the upper block, if connected
-                if (lby > 0) {
-                    const uint32_t ub = bits(by - 1, bx);
-                    if ((bb & 3) && (ub & 12)) {
-                        if ((ub & 5) && (bits(by - 1, bx - 1) & 10)) p[0] = id - g.BW - 1;
-                        if (lby > 1 && (ub & 1) && (bits(by - 2, bx - 1) & 8)) p[1] = id - 2 * g.BW - 1;
-                    }
-                }
-            }
-            const int pl0 = p[0] >= 0 ? glab[p[0]] : -2, pl1 = p[1] >= 0 ? glab[p[1]] : -2;
-            const int lc0 = c[0] >= 0 ? glab[c[0]] : -4, lc1 = c[1] >= 0 ? glab[c[1]] : -4;
-            const int my = bb ? glab[id] : -1;
-            int first = -3;
-            if (c[0] >= 0 && lc0 != pl0 && lc0 != pl1) {
-                first = lc0;
-                link(my, lc0);
-            }
-            if (c[1] >= 0 && lc1 != pl0 && lc1 != pl1 && lc1 != first) link(my, lc1);
-        } else if (side == 1 && lby > 0 && bx0 + TBW < g.BW) {
-            // contact UR (tile to the right); redundant when the upper block is
-            // connected to this block and to that same block (its right neighbour)
-            const int bx = bx0 + TBW - 1, id = by * g.BW + bx;
-            const uint32_t bb = bits(by, bx);
-            if ((bb & 2) && (bits(by - 1, bx + 1) & 4)) {
-                const uint32_t ub = bits(by - 1, bx), ur = bits(by - 1, bx + 1);
-                const bool covered = (bb & 3) && (ub & 12) && (ur & 5) && (ub & 10);
-                if (!covered) link(id, id - g.BW + 1);
-            }
-        }
-    }
-    guard_report(gd, ok);
-    wave_lds_handoff();  // the window is rewritten by the wave's next tile
-}
-
-// Point a border-touching tile-local root i (flag byte f) at its final root
-// and carry its seed flag there.  Other local roots are final roots already.
-// A walker writes only its own entry, so concurrent walkers never undo each
-// other.  At most `cap` steps; a walk the cap stops writes nothing and clears
-// ok.
-__device__ __forceinline__ void ccl_flag_walk(VLG_GLOBAL int32_t *glab, VLG_GLOBAL uint8_t *gflag, int i, uint32_t f,
-                                              int cap, bool &ok) {
-    int x = i;
-    for (int it = 0;; it++) {
-        if (it >= cap) {
-            ok = false;
-            return;
-        }
-        const int p = glab[x];
-        if (p == x) break;
-        x = p;
-    }
-    if (x != i) {
-        glab[i] = x;
-        if (f & 2) gflag[x] = 3;  // final roots are border-touching local roots
-    }
-}
-
-// Flag pass over blocks i0 .. i0+15 (i0 a multiple of 16): one 16-byte load
-// of their flag bytes, then a walk for each border-touching local root among
-// them (bit0 of its byte).  A byte that another walker rewrites after the
-// load is either a final root (the walk ends at once) or unchanged.
-template <int N>
-__device__ __forceinline__ void ccl_flag_n(int32_t *glab_, uint8_t *gflag_, int64_t nb, int64_t i0, int cap,
-                                           bool &ok) {
-    static_assert(N == 4 || N == 16, "4 or 16 blocks per thread");
-    VLG_GLOBAL int32_t *glab = glb(glab_);
-    VLG_GLOBAL uint8_t *gflag = glb(gflag_);
-    uint64_t lo = 0, hi = 0;
-    if (N == 16 && i0 + 16 <= nb && ((uintptr_t)(gflag_ + i0) & 7) == 0) {
-        const VLG_GLOBAL uint64_t *q = (const VLG_GLOBAL uint64_t *)(gflag + i0);
-        lo = q[0];
-        hi = q[1];
-    } else if (N == 4 && i0 + 4 <= nb && ((uintptr_t)(gflag_ + i0) & 3) == 0) {
-        lo = *(const VLG_GLOBAL uint32_t *)(gflag + i0);
-    } else {
-        for (int k = 0; k < N && i0 + k < nb; k++) {
-            const uint64_t v = gflag[i0 + k];
-            if (k < 8)
-                lo |= v << (8 * k);
-            else
-                hi |= v << (8 * (k - 8));
-        }
-    }
-    constexpr uint64_t kBit0 = 0x0101010101010101ull;
-    uint64_t mlo = lo & kBit0, mhi = hi & kBit0;
-    while (mlo | mhi) {
-        int bit, k;
-        uint32_t f;
-        if (mlo) {
-            bit = __builtin_ctzll(mlo);
-            mlo &= mlo - 1;
-            k = bit >> 3;
-            f = (uint32_t)(lo >> bit) & 0xFF;
-        } else {
-            bit = __builtin_ctzll(mhi);
-            mhi &= mhi - 1;
-            k = 8 + (bit >> 3);
-            f = (uint32_t)(hi >> bit) & 0xFF;
-        }
-        ccl_flag_walk(glab, gflag, (int)(i0 + k), f, cap, ok);
-    }
-}
-
-// out = (y & z) | Z, Z = the b-pixels whose component meets the seeds.  Every
-// foreground block points at a local root and every local root at its final
-// root, so the root is two loads away; the flag byte of the local root is
-// loaded beside its parent entry and is the final one when the local root is
-// a final root.  A task is 256 blocks of one block row (512 pixels = 8 words
-// of two rows); lane l owns blocks 4l .. 4l+3, i.e. byte l of those 8 words,
-// assembled in LDS (zw: 8 words per task).  A wave takes NT consecutive tasks
-// t0 .. t0+NT-1 (those below ntasks) and walks them together, so their
-// dependent loads overlap.  Lanes 0..15 load the output words' operands up
-// front.
-template <int NT>
-__device__ __forceinline__ void ccl_gather_tasks(const Geo &g, const MRef &b, const MRef &y, const MRef &z,
-                                                 const int32_t *__restrict__ glab_, const uint8_t *__restrict__ gflag_,
-                                                 int user, uint64_t *__restrict__ out_, int64_t t0, int64_t ntasks,
-                                                 uint64_t *zw) {
-    const VLG_GLOBAL int32_t *glab = glb(glab_);
-    const VLG_GLOBAL uint8_t *gflag = glb(gflag_);
-    VLG_GLOBAL uint64_t *out = glb(out_);
-    const int lane = lane_id();
-    const int nq = (g.wpr + 7) / 8;
-    bool ovalid[NT];
-    int64_t oi[NT];
-    uint64_t oyz[NT], ob[NT];
-    uint32_t any[NT];
-    int by[NT], q[NT];
-#pragma unroll
-    for (int k = 0; k < NT; k++) {
-        const int64_t t = t0 + k;
-        const bool valid = t < ntasks;
-        by[k] = valid ? (int)(t / nq) : 0;
-        q[k] = valid ? (int)(t - (int64_t)by[k] * nq) : 0;
-        const int y0 = 2 * by[k];
-        // output word of lanes 0..15: row y0 + lane/8, word 8q + lane%8
-        const int oy = y0 + (lane >> 3), ow = 8 * q[k] + (lane & 7);
-        ovalid[k] = valid && lane < 16 && oy < g.H && ow < g.wpr;
-        oi[k] = ovalid[k] ? (int64_t)oy * g.wpr + ow : 0;
-        oyz[k] = 0;
-        ob[k] = 0;
-        if (ovalid[k]) {
-            oyz[k] = ldm(y, oi[k]) & ldm(z, oi[k]);
-            ob[k] = ldm(b, oi[k]);
-        }
-        const int w = 8 * q[k] + (lane >> 3), sh = (lane & 7) * 8;  // word and bit offset of my byte
-        uint32_t top = 0, bot = 0;
-        if (valid && w < g.wpr) {
-            const uint64_t keep = w == g.wpr - 1 ? g.tail : ~0ull;
-            top = (uint32_t)(((ldm(b, (int64_t)y0 * g.wpr + w) & keep) >> sh) & 0xFF);
-            if (y0 + 1 < g.H) bot = (uint32_t)(((ldm(b, (int64_t)(y0 + 1) * g.wpr + w) & keep) >> sh) & 0xFF);
-        }
-        any[k] = top | bot;
-    }
-    int lr[NT][4];
-#pragma unroll
-    for (int k = 0; k < NT; k++) {
-        const int64_t id0 = (int64_t)by[k] * g.BW + 256 * q[k] + 4 * lane;
-#pragma unroll
-        for (int j = 0; j < 4; j++) lr[k][j] = ((any[k] >> (2 * j)) & 3) ? glab[id0 + j] : -1;
-    }
-    int r[NT][4];
-    uint32_t f[NT][4];
-#pragma unroll
-    for (int k = 0; k < NT; k++)
-#pragma unroll
-        for (int j = 0; j < 4; j++) {
-            r[k][j] = lr[k][j] >= 0 ? glab[lr[k][j]] : -1;
-            f[k][j] = lr[k][j] >= 0 ? gflag[lr[k][j]] : 0u;
-        }
-#pragma unroll
-    for (int k = 0; k < NT; k++)
-#pragma unroll
-        for (int j = 0; j < 4; j++)
-            if (r[k][j] >= 0 && r[k][j] != lr[k][j]) f[k][j] = gflag[r[k][j]];
-#pragma unroll
-    for (int k = 0; k < NT; k++) {
-        uint32_t zbyte = 0;
-#pragma unroll
-        for (int j = 0; j < 4; j++)
-            if (r[k][j] >= 0 && ((f[k][j] >> (1 + user)) & 1)) zbyte |= 3u << (2 * j);
-        ((uint8_t *)zw)[64 * k + lane] = (uint8_t)zbyte;
-    }
-    wave_lds_handoff();  // every lane's Z byte, then the word reads
-#pragma unroll
-    for (int k = 0; k < NT; k++)
-        if (ovalid[k]) {
-            const int ow = 8 * q[k] + (lane & 7);
-            const uint64_t keep = ow == g.wpr - 1 ? g.tail : ~0ull;
-            out[oi[k]] = (oyz[k] | (ob[k] & zw[8 * k + (lane & 7)])) & keep;
-        }
-    wave_lds_handoff();  // zw is rewritten by the wave's next tasks
-}
-
-constexpr int kGatherTasksPerWave = 2;
-
-// Mark, for labelling user `user`, the components of the current labelling
-// that meet the seed mask sm (= N(seeds) & b): bit 1+user of the root's flag
-// byte.  Runs after the flag pass, so every block's root is two loads away.
-// Called by every lane of a wave (block (by, bx), or valid = false).
-__device__ __forceinline__ void ccl_reseed_lane(const Geo &g, const MRef &sm, const int32_t *__restrict__ glab_,
-                                                uint8_t *gflag_, int user, bool valid, int by, int bx) {
-    const VLG_GLOBAL int32_t *glab = glb(glab_);
-    VLG_GLOBAL uint8_t *gflag = glb(gflag_);
-    const int lane = lane_id();
-    int r = -1;
-    if (valid && block_bits_g(g, sm, by, bx)) r = glab[glab[(int64_t)by * g.BW + bx]];
-    // neighbouring blocks mostly share a root: one atomic per distinct root
-    // per wave (a giant component would otherwise serialise on one address)
-    const uint32_t bit = 1u << (1 + user);
-    uint64_t pending = __ballot(r >= 0);
-    while (pending) {
-        const int leader = __builtin_ctzll(pending);  // wave-uniform
-        const int r0 = __builtin_amdgcn_readlane(r, leader);
-        pending &= ~__ballot(r == r0);
-        if (lane == leader && !(gflag[r0] & bit))
-            __hip_atomic_fetch_or((VLG_GLOBAL unsigned int *)(gflag + (r0 & ~3)), bit << (8 * (r0 & 3)),
-                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-}
-
 // ------------------------------------------------------------------ single-image kernels
 
 template <bool NT>
@@ -1166,157 +298,6 @@ __global__ __launch_bounds__(kThreads) void k_atoms(Geo g, const T *__restrict__
         atoms_task<T, NT>(g, img, a.n, a.cmp, sthr, outf, t);
 }
 
-template <int TBH>
-__global__ __launch_bounds__(ccl_local_threads<TBH>()) void k_ccl_local(Geo g, MRef b, MRef y, MRef z, int ntx,
-                                                        int32_t *__restrict__ glab,
-                                                        uint8_t *__restrict__ gflag, LoopGuard gd) {
-    const int tile = xcd_contiguous((int)blockIdx.x, (int)gridDim.x);
-    ccl_local_tile<TBH>(g, b, y, z, tile % ntx, tile / ntx, glab, gflag, gd);
-}
-
-template <int TBH>
-__global__ __launch_bounds__(kThreads) void k_ccl_merge(Geo g, MRef b, int ntx, int ntiles, int32_t *glab,
-                                                        unsigned long long *counters, LoopGuard gd) {
-    __shared__ uint64_t win[kThreads / 64][merge_window_words<TBH>()];
-    const int wv = threadIdx.x >> 6;
-    const int w = xcd_contiguous((int)blockIdx.x, (int)gridDim.x) * (kThreads / 64) + wv, tile = w >> 1;
-    int unions = 0, tries = 0;
-    if (tile < ntiles) ccl_merge_tile<TBH>(g, b, ntx, tile, w & 1, glab, win[wv], unions, tries, gd);
-    if (counters && (unions | tries)) {
-        atomicAdd(&counters[0], (unsigned long long)unions);
-        atomicAdd(&counters[1], (unsigned long long)(tries - unions));
-    }
-}
-
-// per: blocks per thread, 4 on small images (more threads walk at once) or 16
-__global__ __launch_bounds__(kThreads) void k_ccl_flag(int64_t nblocks, int32_t *glab, uint8_t *gflag, LoopGuard gd,
-                                                       int per) {
-    const int64_t stride = (int64_t)gridDim.x * kThreads * per;
-    bool ok = true;
-    for (int64_t i0 = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * per; i0 < nblocks; i0 += stride) {
-        if (per == 4)
-            ccl_flag_n<4>(glab, gflag, nblocks, i0, gd.cap, ok);
-        else
-            ccl_flag_n<16>(glab, gflag, nblocks, i0, gd.cap, ok);
-    }
-    guard_report(gd, ok);
-}
-
-__global__ __launch_bounds__(kThreads) void k_ccl_gather(Geo g, MRef b, MRef y, MRef z,
-                                                         const int32_t *__restrict__ glab,
-                                                         const uint8_t *__restrict__ gflag, int user,
-                                                         uint64_t *__restrict__ out) {
-    constexpr int NT = kGatherTasksPerWave;
-    __shared__ uint64_t zw[kThreads / 64][8 * NT];
-    const int wv = threadIdx.x >> 6;
-    const int64_t ntasks = (int64_t)g.BH * ((g.wpr + 7) / 8);
-    const int64_t nwaves = (int64_t)gridDim.x * (kThreads / 64);
-    for (int64_t t = ((int64_t)blockIdx.x * (kThreads / 64) + wv) * NT; t < ntasks; t += nwaves * NT)
-        ccl_gather_tasks<NT>(g, b, y, z, glab, gflag, user, out, t, ntasks, zw[wv]);
-}
-
-__global__ __launch_bounds__(kThreads) void k_ccl_reseed(Geo g, MRef sm, const int32_t *__restrict__ glab,
-                                                         uint8_t *gflag, int user) {
-    const int bx = blockIdx.x * kThreads + threadIdx.x, by = blockIdx.y;
-    ccl_reseed_lane(g, sm, glab, gflag, user, bx < g.BW, by, bx);
-}
-
-// ---- several labellings per launch (blockIdx.y selects the labelling)
-template <int TBH>
-__global__ __launch_bounds__(ccl_local_threads<TBH>()) void k_ccl_local_multi(Geo g, CclMulti m, int ntx,
-                                                                              LoopGuard gd) {
-    const int l = (int)blockIdx.y, tile = xcd_contiguous((int)blockIdx.x, (int)gridDim.x);
-    ccl_local_tile<TBH>(g, m.b[l], m.y[l], m.z[l], tile % ntx, tile / ntx, m.glab[l], m.gflag[l], gd);
-}
-
-template <int TBH>
-__global__ __launch_bounds__(kThreads) void k_ccl_merge_multi(Geo g, CclMulti m, int ntx, int ntiles,
-                                                              unsigned long long *counters, LoopGuard gd) {
-    __shared__ uint64_t win[kThreads / 64][merge_window_words<TBH>()];
-    const int l = (int)blockIdx.y;
-    const int wv = threadIdx.x >> 6;
-    const int w = xcd_contiguous((int)blockIdx.x, (int)gridDim.x) * (kThreads / 64) + wv, tile = w >> 1;
-    int unions = 0, tries = 0;
-    if (tile < ntiles) ccl_merge_tile<TBH>(g, m.b[l], ntx, tile, w & 1, m.glab[l], win[wv], unions, tries, gd);
-    if (counters && (unions | tries)) {
-        atomicAdd(&counters[0], (unsigned long long)unions);
-        atomicAdd(&counters[1], (unsigned long long)(tries - unions));
-    }
-}
-
-__global__ __launch_bounds__(kThreads) void k_ccl_flag_multi(int64_t nblocks, CclMulti m, LoopGuard gd) {
-    const int l = (int)blockIdx.y;
-    const int64_t stride = (int64_t)gridDim.x * kThreads * 16;
-    bool ok = true;
-    for (int64_t i0 = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * 16; i0 < nblocks; i0 += stride)
-        ccl_flag_n<16>(m.glab[l], m.gflag[l], nblocks, i0, gd.cap, ok);
-    guard_report(gd, ok);
-}
-
-__global__ __launch_bounds__(kThreads) void k_ccl_gather_multi(Geo g, CclMulti m) {
-    constexpr int NT = kGatherTasksPerWave;
-    __shared__ uint64_t zw[kThreads / 64][8 * NT];
-    const int l = (int)blockIdx.y;
-    const int wv = threadIdx.x >> 6;
-    const int64_t ntasks = (int64_t)g.BH * ((g.wpr + 7) / 8);
-    const int64_t nwaves = (int64_t)gridDim.x * (kThreads / 64);
-    for (int64_t t = ((int64_t)blockIdx.x * (kThreads / 64) + wv) * NT; t < ntasks; t += nwaves * NT)
-        ccl_gather_tasks<NT>(g, m.b[l], m.y[l], m.z[l], m.glab[l], m.gflag[l], m.user[l], m.out[l], t, ntasks,
-                             zw[wv]);
-}
-
-// Smallest row-major pixel index of each component, gathered at its root.
-__global__ __launch_bounds__(kThreads) void k_ccl_canon(Geo g, MRef b, const int32_t *__restrict__ glab,
-                                                        int32_t *canon) {
-    const int bx = blockIdx.x * kThreads + threadIdx.x, by = blockIdx.y, lane = lane_id();
-    int r = -1, p = 0x7fffffff;
-    if (bx < g.BW) {
-        const uint32_t bits = block_bits_g(g, b, by, bx);
-        if (bits) {
-            const int k = __builtin_ctz(bits);  // top-left, top-right, bottom-left, bottom-right
-            p = (2 * by + (k >> 1)) * g.W + 2 * bx + (k & 1);
-            r = glab[glab[(int64_t)by * g.BW + bx]];
-        }
-    }
-    // one atomicMin per distinct root per wave, with the group's minimum
-    uint64_t pending = __ballot(r >= 0);
-    while (pending) {
-        const int leader = __builtin_ctzll(pending);  // wave-uniform
-        const int r0 = __builtin_amdgcn_readlane(r, leader);
-        const bool mine = r == r0;
-        pending &= ~__ballot(mine);
-        int m = mine ? p : 0x7fffffff;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) m = min(m, __shfl_xor(m, off));
-        // a giant component would serialise every wave on one address: skip
-        // the atomic when the root already holds a smaller index
-        if (lane == leader && m < __hip_atomic_load(&canon[r0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-            atomicMin(&canon[r0], m);
-    }
-}
-
-__global__ void k_fill_i32(int32_t *p, int64_t n, int32_t v) {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = v;
-}
-
-// Canonical labels: smallest row-major pixel index of each component.
-__global__ __launch_bounds__(kThreads) void k_ccl_labels(Geo g, MRef b, const int32_t *__restrict__ glab,
-                                                         const int32_t *__restrict__ canon,
-                                                         int32_t *__restrict__ labels) {
-    const int x = blockIdx.x * kThreads + threadIdx.x, yy = blockIdx.y;
-    if (x >= g.W) return;
-    const int w = x >> 6;
-    uint64_t word = ldm(b, (int64_t)yy * g.wpr + w);
-    if (w == g.wpr - 1) word &= g.tail;
-    int32_t lab = -1;
-    if ((word >> (x & 63)) & 1) {
-        const int lr = glab[(int64_t)(yy >> 1) * g.BW + (x >> 1)];
-        lab = canon[glab[lr]];
-    }
-    labels[(int64_t)yy * g.W + x] = lab;
-}
-
 __global__ __launch_bounds__(kThreads) void k_unpack(Geo g, const uint64_t *__restrict__ mask,
                                                      uint8_t *__restrict__ out) {
     const int x = blockIdx.x * kThreads + threadIdx.x, yy = blockIdx.y;
@@ -1334,36 +315,9 @@ __global__ void k_fill_i64(unsigned long long *p, int n, unsigned long long v) {
 //   BK_WORDS  256 mask words (atoms: four 64-word wave tasks)
 //   BK_LOGIC  1024 mask words (Boolean steps)
 //   BK_NEAR   four near bands (64 words wide, kBatchNearRows rows high)
-//   BK_TILES  one labelling tile          BK_MERGE  four tiles (one per wave)
-//   BK_BLOCKS 256 blocks                  BK_GATHER eight 256-block tasks (two per wave)
-//   BK_FLAG   4096 blocks (16 per thread)
+//   BK_TILES  one group of labelling tiles (64 block rows of tiles side by side)
+//   BK_MERGE  two tiles (two waves each)  BK_FLAG   four tiles (one per wave)
 //   BK_PCTH   kPctUnit channel elements   BK_ONE    one per image
-
-// The descriptor of image ii (wave-uniform) through scalar loads: the table
-// is written before the launch and only read while it runs.
-__device__ __forceinline__ BImg load_bimg(const BImg *imgs, int ii) {
-    static_assert(sizeof(BImg) % 4 == 0, "descriptor copied as 32-bit words");
-    const VLG_CONST uint32_t *p = (const VLG_CONST uint32_t *)(imgs + __builtin_amdgcn_readfirstlane(ii));
-    BImg r;
-    uint32_t *q = (uint32_t *)&r;
-#pragma unroll
-    for (int k = 0; k < (int)(sizeof(BImg) / 4); k++) q[k] = p[k];
-    return r;
-}
-
-// d: the descriptor of unit u_'s image, reloaded only when the image changes
-#define VLG_BATCH_LOOP(A)                          \
-    UnitRange ur_((A).prefix, (A).n);                  \
-    int cur_ = -1;                                     \
-    BImg dcur_;                                        \
-    for (int64_t u_ = ur_.begin; u_ < ur_.end; u_++)
-#define VLG_BATCH_IMG(A)                           \
-    const int ii = ur_.img(u_);                        \
-    if (ii != cur_) {                                  \
-        dcur_ = load_bimg((A).imgs, ii);                \
-        cur_ = ii;                                     \
-    }                                                  \
-    const BImg &d = dcur_;
 
 __global__ __launch_bounds__(kThreads) void kb_logic(BatchArgs a, BLogic ops) {
     const BLogicOp &o = ops.ops[blockIdx.y];
@@ -1405,76 +359,6 @@ __global__ __launch_bounds__(kThreads) void kb_atoms(BatchArgs a, BAtoms op) {
     }
 }
 
-// (at most 64 VGPRs, eight waves per SIMD: a few registers spill, and the
-// 512-image batch's tile-local pass still takes 4% less time than at six)
-template <int TBH>
-__global__ __launch_bounds__(ccl_local_threads<TBH>()) __attribute__((amdgpu_waves_per_eu(8))) void kb_ccl_local(
-    BatchArgs a, BRef b, BRef y, BRef z) {
-    VLG_BATCH_LOOP(a) {
-        VLG_BATCH_IMG(a)
-        const int ntx = (d.g.BW + kTileBW - 1) / kTileBW;
-        const int tile = (int)(u_ - a.prefix[ii]);
-        ccl_local_tile<TBH>(d.g, bref(d, b), bref(d, y), bref(d, z), tile % ntx, tile / ntx,
-                            (int32_t *)(d.ws + d.off_glab), (uint8_t *)(d.ws + d.off_gflag), a.guard);
-    }
-}
-
-template <int TBH>
-// (eight waves per SIMD: the descriptor's scalar registers otherwise hold
-// it at seven; 1.76 -> 1.58 ms per 512-image batch)
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) void kb_ccl_merge(BatchArgs a, BRef b) {
-    __shared__ uint64_t win[kThreads / 64][merge_window_words<TBH>()];
-    const int wv = threadIdx.x >> 6;
-    int unions = 0, tries = 0;
-    VLG_BATCH_LOOP(a) {
-        VLG_BATCH_IMG(a)
-        const int ntx = (d.g.BW + kTileBW - 1) / kTileBW, nty = (d.g.BH + TBH - 1) / TBH;
-        const int w = (int)(u_ - a.prefix[ii]) * (kThreads / 64) + wv, tile = w >> 1;
-        if (tile < ntx * nty)
-            ccl_merge_tile<TBH>(d.g, bref(d, b), ntx, tile, w & 1, (int32_t *)(d.ws + d.off_glab), win[wv], unions,
-                                tries, a.guard);
-    }
-}
-
-__global__ __launch_bounds__(kThreads) void kb_ccl_flag(BatchArgs a) {
-    bool ok = true;
-    VLG_BATCH_LOOP(a) {
-        VLG_BATCH_IMG(a)
-        const int64_t i0 = ((u_ - a.prefix[ii]) * kThreads + threadIdx.x) * 16, nb = (int64_t)d.g.BH * d.g.BW;
-        if (i0 < nb) ccl_flag_n<16>((int32_t *)(d.ws + d.off_glab), (uint8_t *)(d.ws + d.off_gflag), nb, i0, a.guard.cap, ok);
-    }
-    guard_report(a.guard, ok);
-}
-
-// (eight waves per SIMD, as kb_ccl_merge: 3.97 -> 3.54 ms per 512-image batch)
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) void kb_ccl_gather(BatchArgs a, BRef b,
-                                                                                                  BRef y, BRef z,
-                                                                                                  int user,
-                                                                                                  int32_t out) {
-    constexpr int NT = kGatherTasksPerWave;
-    __shared__ uint64_t zw[kThreads / 64][8 * NT];
-    const int wv = threadIdx.x >> 6;
-    VLG_BATCH_LOOP(a) {
-        VLG_BATCH_IMG(a)
-        const int64_t t = ((u_ - a.prefix[ii]) * (kThreads / 64) + wv) * NT;
-        const int64_t ntasks = (int64_t)d.g.BH * ((d.g.wpr + 7) / 8);
-        if (t < ntasks)
-            ccl_gather_tasks<NT>(d.g, bref(d, b), bref(d, y), bref(d, z), (const int32_t *)(d.ws + d.off_glab),
-                                 (const uint8_t *)(d.ws + d.off_gflag), user, bptr(d, out), t, ntasks, zw[wv]);
-    }
-}
-
-__global__ __launch_bounds__(kThreads) void kb_ccl_reseed(BatchArgs a, BRef sm, int user) {
-    VLG_BATCH_LOOP(a) {
-        VLG_BATCH_IMG(a)
-        const int64_t i = (u_ - a.prefix[ii]) * kThreads + threadIdx.x;
-        const bool valid = i < (int64_t)d.g.BH * d.g.BW;
-        const int by = valid ? (int)(i / d.g.BW) : 0, bx = valid ? (int)(i - (int64_t)by * d.g.BW) : 0;
-        ccl_reseed_lane(d.g, bref(d, sm), (const int32_t *)(d.ws + d.off_glab), (uint8_t *)(d.ws + d.off_gflag),
-                        user, valid, by, bx);
-    }
-}
-
 #undef VLG_BATCH_LOOP
 #undef VLG_BATCH_IMG
 
@@ -1492,13 +376,6 @@ __global__ __launch_bounds__(kThreads) void kb_ccl_reseed(BatchArgs a, BRef sm, 
 //   NEAR_*  dst = (N(a ^ ia) ^ io) OP (b ^ ib), N over the image's pixels only
 //           (operand words outside the image and padding bits are background)
 //   STORE   ptr[dst] = a ^ ia over the tile's centre (padding bits cleared)
-__device__ __forceinline__ uint64_t lane_prev64(uint64_t v) {
-    return (uint64_t)(uint32_t)lane_prev((int)(uint32_t)v) | ((uint64_t)(uint32_t)lane_prev((int)(v >> 32)) << 32);
-}
-__device__ __forceinline__ uint64_t lane_next64(uint64_t v) {
-    return (uint64_t)(uint32_t)lane_next((int)(uint32_t)v) | ((uint64_t)(uint32_t)lane_next((int)(v >> 32)) << 32);
-}
-
 __global__ __launch_bounds__(64) void k_segment_lane(Geo g, SegProg p, int nty) {
     extern __shared__ uint64_t lreg[];  // [register][word l, c, r][lane]
     // each XCD takes a contiguous range of tiles, so the neighbour words and
@@ -1662,8 +539,6 @@ __global__ __launch_bounds__(kSegWideThreads) void k_segment_wide(Geo g, SegProg
     }
 }
 
-int ntiles_x(const Geo &g) { return (g.BW + kTileBW - 1) / kTileBW; }
-int ntiles_y(const Geo &g, int tbh) { return (g.BH + tbh - 1) / tbh; }
 
 }  // namespace
 
@@ -1722,102 +597,6 @@ hipError_t launch_atoms(hipStream_t s, const Geo &g, const void *chan, int dtype
     return atoms_t(s, g, (const float *)chan, a);
 }
 
-hipError_t launch_ccl_local(hipStream_t s, const Geo &g, MRef b, MRef y, MRef z, const CclWork &w) {
-    if (g.nwords == 0) return hipSuccess;
-    if (!valid_tile_bh(w.tbh)) return hipErrorInvalidValue;
-    const int ntx = ntiles_x(g), nty = ntiles_y(g, w.tbh);
-    switch (w.tbh) {
-    case 8: k_ccl_local<8><<<ntx * nty, ccl_local_threads<8>(), 0, s>>>(g, b, y, z, ntx, w.glab, w.gflag, w.guard); break;
-    case 16: k_ccl_local<16><<<ntx * nty, ccl_local_threads<16>(), 0, s>>>(g, b, y, z, ntx, w.glab, w.gflag, w.guard); break;
-    default: k_ccl_local<32><<<ntx * nty, ccl_local_threads<32>(), 0, s>>>(g, b, y, z, ntx, w.glab, w.gflag, w.guard); break;
-    }
-    return hipGetLastError();
-}
-
-hipError_t launch_ccl_merge(hipStream_t s, const Geo &g, MRef b, const CclWork &w) {
-    if (g.nwords == 0) return hipSuccess;
-    if (!valid_tile_bh(w.tbh)) return hipErrorInvalidValue;
-    const int ntx = ntiles_x(g), nty = ntiles_y(g, w.tbh), ntiles = ntx * nty;
-    const int grid = (2 * ntiles + kThreads / 64 - 1) / (kThreads / 64);  // two waves per tile
-    switch (w.tbh) {
-    case 8: k_ccl_merge<8><<<grid, kThreads, 0, s>>>(g, b, ntx, ntiles, w.glab, w.counters, w.guard); break;
-    case 16: k_ccl_merge<16><<<grid, kThreads, 0, s>>>(g, b, ntx, ntiles, w.glab, w.counters, w.guard); break;
-    default: k_ccl_merge<32><<<grid, kThreads, 0, s>>>(g, b, ntx, ntiles, w.glab, w.counters, w.guard); break;
-    }
-    return hipGetLastError();
-}
-
-hipError_t launch_ccl_flag(hipStream_t s, const Geo &g, const CclWork &w) {
-    if (g.nwords == 0) return hipSuccess;
-    const int64_t nb = (int64_t)g.BH * g.BW;
-    // four blocks per thread unless sixteen still give 1024 workgroups
-    const int per = nb >= (int64_t)16 * kThreads * 1024 ? 16 : 4;
-    k_ccl_flag<<<grid_for((nb + per - 1) / per, kThreads, 65536), kThreads, 0, s>>>(nb, w.glab, w.gflag, w.guard,
-                                                                                    per);
-    return hipGetLastError();
-}
-
-hipError_t launch_ccl_gather(hipStream_t s, const Geo &g, MRef b, MRef y, MRef z, const CclWork &w,
-                             int user, uint64_t *out) {
-    if (g.nwords == 0) return hipSuccess;
-    const int64_t tasks = (int64_t)g.BH * ((g.wpr + 7) / 8);
-    const int grid = grid_for((tasks + kGatherTasksPerWave - 1) / kGatherTasksPerWave, kThreads / 64, 8192);
-    k_ccl_gather<<<grid, kThreads, 0, s>>>(g, b, y, z, w.glab, w.gflag, user, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_ccl_reseed(hipStream_t s, const Geo &g, MRef sm, const CclWork &w, int user) {
-    if (g.nwords == 0) return hipSuccess;
-    dim3 grid((g.BW + kThreads - 1) / kThreads, g.BH);
-    k_ccl_reseed<<<grid, kThreads, 0, s>>>(g, sm, w.glab, w.gflag, user);
-    return hipGetLastError();
-}
-
-hipError_t launch_ccl_local_multi(hipStream_t s, const Geo &g, const CclMulti &m, const CclWork &w) {
-    if (g.nwords == 0 || m.n == 0) return hipSuccess;
-    if (m.n < 0 || m.n > kMaxMulti || !valid_tile_bh(w.tbh)) return hipErrorInvalidValue;
-    const int ntx = ntiles_x(g), nty = ntiles_y(g, w.tbh);
-    const dim3 grid((unsigned)(ntx * nty), (unsigned)m.n);
-    switch (w.tbh) {
-    case 8: k_ccl_local_multi<8><<<grid, ccl_local_threads<8>(), 0, s>>>(g, m, ntx, w.guard); break;
-    case 16: k_ccl_local_multi<16><<<grid, ccl_local_threads<16>(), 0, s>>>(g, m, ntx, w.guard); break;
-    default: k_ccl_local_multi<32><<<grid, ccl_local_threads<32>(), 0, s>>>(g, m, ntx, w.guard); break;
-    }
-    return hipGetLastError();
-}
-
-hipError_t launch_ccl_merge_multi(hipStream_t s, const Geo &g, const CclMulti &m, const CclWork &w) {
-    if (g.nwords == 0 || m.n == 0) return hipSuccess;
-    if (m.n < 0 || m.n > kMaxMulti || !valid_tile_bh(w.tbh)) return hipErrorInvalidValue;
-    const int ntx = ntiles_x(g), nty = ntiles_y(g, w.tbh), ntiles = ntx * nty;
-    const dim3 grid((unsigned)((2 * ntiles + kThreads / 64 - 1) / (kThreads / 64)), (unsigned)m.n);
-    switch (w.tbh) {
-    case 8: k_ccl_merge_multi<8><<<grid, kThreads, 0, s>>>(g, m, ntx, ntiles, w.counters, w.guard); break;
-    case 16: k_ccl_merge_multi<16><<<grid, kThreads, 0, s>>>(g, m, ntx, ntiles, w.counters, w.guard); break;
-    default: k_ccl_merge_multi<32><<<grid, kThreads, 0, s>>>(g, m, ntx, ntiles, w.counters, w.guard); break;
-    }
-    return hipGetLastError();
-}
-
-hipError_t launch_ccl_flag_multi(hipStream_t s, const Geo &g, const CclMulti &m, const CclWork &w) {
-    if (g.nwords == 0 || m.n == 0) return hipSuccess;
-    if (m.n < 0 || m.n > kMaxMulti) return hipErrorInvalidValue;
-    const int64_t nb = (int64_t)g.BH * g.BW;
-    const dim3 grid((unsigned)grid_for((nb + 15) / 16, kThreads, 65536), (unsigned)m.n);
-    k_ccl_flag_multi<<<grid, kThreads, 0, s>>>(nb, m, w.guard);
-    return hipGetLastError();
-}
-
-hipError_t launch_ccl_gather_multi(hipStream_t s, const Geo &g, const CclMulti &m) {
-    if (g.nwords == 0 || m.n == 0) return hipSuccess;
-    if (m.n < 0 || m.n > kMaxMulti) return hipErrorInvalidValue;
-    const int64_t tasks = (int64_t)g.BH * ((g.wpr + 7) / 8);
-    const dim3 grid((unsigned)grid_for((tasks + kGatherTasksPerWave - 1) / kGatherTasksPerWave, kThreads / 64, 8192),
-                    (unsigned)m.n);
-    k_ccl_gather_multi<<<grid, kThreads, 0, s>>>(g, m);
-    return hipGetLastError();
-}
-
 hipError_t launch_logic_batch(hipStream_t s, const Geo &g, const LogicBatch &b) {
     if (g.nwords == 0 || b.n == 0) return hipSuccess;
     dim3 grid(grid_for(g.nwords, kThreads, 4096), b.n);
@@ -1832,18 +611,6 @@ hipError_t launch_near_batch(hipStream_t s, const Geo &g, const NearBatch &b, in
     if (!valid_near_rows(rows)) return hipErrorInvalidValue;
     dim3 grid(grid_for(near_tasks(g, rows), kThreads / 64, 8192), b.n);
     k_near_batch<<<grid, kThreads, 0, s>>>(g, b, rows);
-    return hipGetLastError();
-}
-
-hipError_t launch_ccl_labels(hipStream_t s, const Geo &g, MRef b, const CclWork &w, int32_t *canon,
-                             int32_t *labels) {
-    if (g.nwords == 0) return hipSuccess;
-    const int64_t nb = (int64_t)g.BH * g.BW;
-    k_fill_i32<<<grid_for(nb, kThreads, 8192), kThreads, 0, s>>>(canon, nb, 0x7fffffff);
-    dim3 bgrid((g.BW + kThreads - 1) / kThreads, g.BH);
-    k_ccl_canon<<<bgrid, kThreads, 0, s>>>(g, b, w.glab, canon);
-    dim3 grid((g.W + kThreads - 1) / kThreads, g.H);
-    k_ccl_labels<<<grid, kThreads, 0, s>>>(g, b, w.glab, canon, labels);
     return hipGetLastError();
 }
 
@@ -1946,20 +713,15 @@ hipError_t launch_fill_i64(hipStream_t s, unsigned long long *p, int n, unsigned
 
 int64_t batch_units(const Geo &g, int kind, int tbh) {
     if (g.nwords == 0) return 0;
-    const int64_t nb = (int64_t)g.BH * g.BW;
-    const int64_t ntiles = (int64_t)ntiles_x(g) * ntiles_y(g, tbh);
+    const CclGeo q = ccl_geo(g, tbh);
+    const int64_t ntiles = (int64_t)q.ntx * q.nty;
     switch (kind) {
     case BK_WORDS: return (g.nwords + kThreads - 1) / kThreads;
     case BK_LOGIC: return (g.nwords + kThreads * kLogicUnroll - 1) / (kThreads * kLogicUnroll);
     case BK_NEAR: return (near_tasks(g, kBatchNearRows) + kThreads / 64 - 1) / (kThreads / 64);
-    case BK_TILES: return ntiles;
-    case BK_MERGE: return (2 * ntiles + kThreads / 64 - 1) / (kThreads / 64);  // two waves per tile
-    case BK_BLOCKS: return (nb + kThreads - 1) / kThreads;
-    case BK_FLAG: return (nb + 16 * kThreads - 1) / (16 * kThreads);
-    case BK_GATHER: {
-        const int64_t per = (int64_t)kGatherTasksPerWave * (kThreads / 64);  // tasks per unit
-        return ((int64_t)g.BH * ((g.wpr + 7) / 8) + per - 1) / per;
-    }
+    case BK_TILES: return (int64_t)ccl_groups_x(q) * q.nty;
+    case BK_MERGE: return (2 * ntiles + kThreads / 64 - 1) / (kThreads / 64);
+    case BK_FLAG: return (ntiles + kThreads / 64 - 1) / (kThreads / 64);
     case BK_PCTH: return ((int64_t)g.H * g.wpr * 64 + kPctUnit - 1) / kPctUnit;
     case BK_ONE: return 1;
     }
@@ -2000,49 +762,6 @@ hipError_t launch_b_near(hipStream_t s, const BatchArgs &a, int64_t total, const
     if (total == 0 || op.n == 0) return hipSuccess;
     dim3 grid(persistent_grid(a, total), op.n);
     kb_near<<<grid, kThreads, 0, s>>>(a, op);
-    return hipGetLastError();
-}
-
-hipError_t launch_b_ccl_local(hipStream_t s, const BatchArgs &a, int64_t total, int tbh, BRef b, BRef y, BRef z) {
-    if (total == 0) return hipSuccess;
-    const int grid = persistent_grid(a, total);
-    switch (tbh) {
-    case 8: kb_ccl_local<8><<<grid, ccl_local_threads<8>(), 0, s>>>(a, b, y, z); break;
-    case 16: kb_ccl_local<16><<<grid, ccl_local_threads<16>(), 0, s>>>(a, b, y, z); break;
-    case 32: kb_ccl_local<32><<<grid, ccl_local_threads<32>(), 0, s>>>(a, b, y, z); break;
-    default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
-}
-
-hipError_t launch_b_ccl_merge(hipStream_t s, const BatchArgs &a, int64_t total, int tbh, BRef b) {
-    if (total == 0) return hipSuccess;
-    const int grid = persistent_grid(a, total);
-    switch (tbh) {
-    case 8: kb_ccl_merge<8><<<grid, kThreads, 0, s>>>(a, b); break;
-    case 16: kb_ccl_merge<16><<<grid, kThreads, 0, s>>>(a, b); break;
-    case 32: kb_ccl_merge<32><<<grid, kThreads, 0, s>>>(a, b); break;
-    default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
-}
-
-hipError_t launch_b_ccl_flag(hipStream_t s, const BatchArgs &a, int64_t total) {
-    if (total == 0) return hipSuccess;
-    kb_ccl_flag<<<persistent_grid(a, total), kThreads, 0, s>>>(a);
-    return hipGetLastError();
-}
-
-hipError_t launch_b_ccl_gather(hipStream_t s, const BatchArgs &a, int64_t total, BRef b, BRef y, BRef z, int user,
-                               int32_t out) {
-    if (total == 0) return hipSuccess;
-    kb_ccl_gather<<<persistent_grid(a, total), kThreads, 0, s>>>(a, b, y, z, user, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_b_ccl_reseed(hipStream_t s, const BatchArgs &a, int64_t total, BRef sm, int user) {
-    if (total == 0) return hipSuccess;
-    kb_ccl_reseed<<<persistent_grid(a, total), kThreads, 0, s>>>(a, sm, user);
     return hipGetLastError();
 }
 
