@@ -998,7 +998,8 @@ int run_batch(vlg_ctx *c, vlg_formula *f, const vlg_image *const *imgs, const st
     const size_t npct = (size_t)P.npct;
     const size_t d_imgs = total;
     const size_t d_outs = d_imgs + align256((size_t)n * sizeof(BImg));
-    const size_t d_ranks = d_outs + align256((size_t)n * nout * sizeof(uint64_t *));
+    const size_t d_bytes = d_outs + align256((size_t)n * nout * sizeof(uint64_t *));  // byte-mask destinations
+    const size_t d_ranks = d_bytes + align256((size_t)n * nout * sizeof(uint8_t *));
     const size_t d_prefix = d_ranks + align256((size_t)n * std::max<size_t>(npct, 1) * 4);
     const size_t d_end = d_prefix + align256((size_t)BK_COUNT * (n + 1) * 8);
     int rc = ensure_ws(c, d_end);
@@ -1020,6 +1021,7 @@ int run_batch(vlg_ctx *c, vlg_formula *f, const vlg_image *const *imgs, const st
     std::memset(h, 0, dbytes);
     BImg *hi = (BImg *)h;
     uint64_t **ho = (uint64_t **)(h + (d_outs - d_imgs));
+    uint8_t **hb = (uint8_t **)(h + (d_bytes - d_imgs));
     uint32_t *hr = (uint32_t *)(h + (d_ranks - d_imgs));
     int64_t *hp = (int64_t *)(h + (d_prefix - d_imgs));
     std::vector<double> pct_q(npct, 0.0);
@@ -1050,6 +1052,10 @@ int run_batch(vlg_ctx *c, vlg_formula *f, const vlg_image *const *imgs, const st
             uint64_t *e = direct && user ? (uint64_t *)user : (uint64_t *)(wb + L.off_stage + o * L.mask_bytes);
             ext[(size_t)k * nout + o] = e;
             ho[(size_t)k * nout + o] = e;
+            if (fmt == VLG_U8MASK && user)
+                hb[(size_t)k * nout + o] = where == VLG_DEVICE
+                                               ? (uint8_t *)user
+                                               : (uint8_t *)(wb + L.off_u8 + o * align256((size_t)geo[k].H * geo[k].W));
         }
         for (int kind = 0; kind < BK_COUNT; kind++)
             hp[(size_t)kind * (n + 1) + k + 1] = hp[(size_t)kind * (n + 1) + k] + batch_units(geo[k], kind, tbh);
@@ -1206,17 +1212,9 @@ int run_batch(vlg_ctx *c, vlg_formula *f, const vlg_image *const *imgs, const st
             if (hook) hook(hook_ctx, si, false);
         }
         if (fmt == VLG_U8MASK) {
-            for (int k = 0; k < n; k++)
-                for (size_t o = 0; o < nout; o++) {
-                    void *user = outs[(size_t)idx[k] * nout + o];
-                    if (!user) continue;
-                    uint8_t *dst = where == VLG_DEVICE
-                                       ? (uint8_t *)user
-                                       : (uint8_t *)(base + off[k] + lay[k].off_u8 +
-                                                     o * align256((size_t)geo[k].H * geo[k].W));
-                    hipError_t e = launch_unpack(c->stream, geo[k], ext[(size_t)k * nout + o], dst);
-                    if (e != hipSuccess) return fail(VLG_EHIP, hipGetErrorString(e));
-                }
+            const hipError_t e = launch_b_unpack(c->stream, args(BK_UNPACK), units(BK_UNPACK),
+                                                 (uint8_t *const *)(base + d_bytes), (int)nout);
+            if (e != hipSuccess) return fail(VLG_EHIP, hipGetErrorString(e));
         }
         return VLG_OK;
     };

@@ -386,7 +386,7 @@ struct BRef {
     uint32_t inv;
 };
 
-enum BatchKind { BK_WORDS = 0, BK_LOGIC, BK_NEAR, BK_TILES, BK_MERGE, BK_FLAG, BK_PCTH, BK_ONE, BK_COUNT };
+enum BatchKind { BK_WORDS = 0, BK_LOGIC, BK_NEAR, BK_TILES, BK_MERGE, BK_FLAG, BK_UNPACK, BK_PCTH, BK_ONE, BK_COUNT };
 
 struct BatchArgs {
     int n;
@@ -425,6 +425,8 @@ struct BNear {
 int64_t batch_units(const Geo &g, int kind, int tbh);
 
 hipError_t launch_b_atoms(hipStream_t s, const BatchArgs &a, int64_t total, const BAtoms &op);
+// dst[image * nout + k]: byte mask of output k of each image (null: skipped)
+hipError_t launch_b_unpack(hipStream_t s, const BatchArgs &a, int64_t total, uint8_t *const *dst, int nout);
 hipError_t launch_b_logic(hipStream_t s, const BatchArgs &a, int64_t total, const BLogic &op);
 hipError_t launch_b_near(hipStream_t s, const BatchArgs &a, int64_t total, const BNear &op);
 // a labelling step of a batch (the fields as in CclOp)
