@@ -248,15 +248,43 @@ struct Layout {
     size_t lane_bytes = 0;  // labelling workspace of lane l at off_ccl + l * lane_bytes
     bool pj = false;        // pointer-jumping labelling: its arrays (pj_work) start at off_ccl
     bool vol = false;       // volume labelling: voxel parents (4 B) then flag bytes at off_ccl
+    size_t off_cand = 0;    // percentile candidates, cand_cap per rank of a step (0: radix select)
+    uint32_t cand_cap = 0;
 };
 
 // the block parents of a volume labelling (vl_nblocks <= g.BH * g.BW)
 size_t vol_label_bytes(const Geo &g) { return align256((size_t)g.BH * g.BW * 4); }
 
+// Percentile candidates may use the labelling workspace when no percentile
+// step runs between the first and the last step of a labelling.
+bool pct_may_share(const Plan &P) {
+    std::vector<size_t> first((size_t)kMaxCclLanes, SIZE_MAX), last((size_t)kMaxCclLanes, 0);
+    std::vector<std::pair<size_t, size_t>> spans;
+    for (size_t si = 0; si < P.steps.size(); si++) {
+        const Step &s = P.steps[si];
+        if (s.kind != SK::CclLocal && s.kind != SK::CclMerge && s.kind != SK::CclFlag && s.kind != SK::CclGather &&
+            s.kind != SK::CclReseed)
+            continue;
+        const size_t w = (size_t)std::max(s.lane, 0);
+        if (s.kind == SK::CclLocal) {
+            if (first[w] != SIZE_MAX) spans.emplace_back(first[w], last[w]);
+            first[w] = si;
+        }
+        last[w] = si;
+    }
+    for (size_t w = 0; w < first.size(); w++)
+        if (first[w] != SIZE_MAX) spans.emplace_back(first[w], last[w]);
+    for (size_t si = 0; si < P.steps.size(); si++)
+        if (P.steps[si].kind == SK::Pct)
+            for (const auto &sp : spans)
+                if (si > sp.first && si < sp.second) return false;
+    return true;
+}
+
 // batch_tbh: the labelling tile height of a batch (one for all its images, so
 // it may need more than ccl_workspace on some); 0 for a single image
 Layout layout_for(const Plan &P, const Geo &g, bool stage_packed, bool stage_u8, bool pj = false,
-                  bool vol = false, int batch_tbh = 0) {
+                  bool vol = false, int batch_tbh = 0, bool cand = false) {
     Layout L;
     L.mask_bytes = align256((size_t)g.nwords * 8);
     size_t off = 0;
@@ -280,6 +308,20 @@ Layout layout_for(const Plan &P, const Geo &g, bool stage_packed, bool stage_u8,
     off += align256((size_t)P.npct * 4);
     L.off_pctst = off;
     off += (size_t)P.npct * kPctStateBytes;
+    // percentile candidates (cand: wanted): in the labelling workspace, or in
+    // room of their own when the plan labels nothing
+    const int64_t npix = (int64_t)g.H * g.W;
+    if (cand && P.npct > 0 && npix > 0) {
+        const uint32_t cap = pct_candidates(npix) + 64;
+        if (P.ccl_count == 0) {
+            L.off_cand = off;
+            L.cand_cap = cap;
+            off += align256((size_t)cap * kMaxPctSel * 4);
+        } else if (pct_may_share(P)) {
+            L.off_cand = L.off_ccl;
+            L.cand_cap = (uint32_t)std::min<size_t>(cap, (size_t)std::max(P.ccl_lanes, 1) * L.lane_bytes / (kMaxPctSel * 4));
+        }
+    }
     L.total = off + 256;
     return L;
 }
@@ -754,7 +796,8 @@ int enqueue_plan(vlg_ctx *c, const Plan &P, const vlg_image *img, const Layout &
                 sel.slot[j] = s.pct_out[j];
                 sel.k[j] = pct_rank(s.q[j], npix);
             }
-            e = launch_percentile(stream, g, img->chan(s.chan), img->dtype, sel, base + L.off_pctst, pct);
+            e = launch_percentile(stream, g, img->chan(s.chan), img->dtype, sel, base + L.off_pctst, pct,
+                                  (uint32_t *)(base + L.off_cand), L.cand_cap);
         }
             break;
         case SK::Atoms: {
@@ -876,7 +919,9 @@ int run(vlg_ctx *c, vlg_formula *f, const vlg_image *img, const std::vector<int>
     const bool pj = !vol && P.ccl_count > 0 && ccl_algo(c, img->H, img->W) == VLG_CCL_POINTER_JUMPING;
     if (pj && !pj_shape_ok(img->H, img->W))
         return fail(VLG_ESHAPE, "pointer-jumping labelling: rows and columns must stay below 65535");
-    Layout L = layout_for(P, g, !direct, stage_u8, pj, vol);
+    // (a lent workspace has no room for candidates beyond the labelling's)
+    const bool cand = img->dtype != VLG_U8 && (!c->ws_external || P.ccl_count > 0);
+    Layout L = layout_for(P, g, !direct, stage_u8, pj, vol, 0, cand);
     int rc = ensure_ws(c, L.total);
     if (rc != VLG_OK) return rc;
     char *base = (char *)c->ws;
@@ -991,7 +1036,7 @@ int run_batch(vlg_ctx *c, vlg_formula *f, const vlg_image *const *imgs, const st
     size_t total = 0;
     for (int k = 0; k < n; k++) {
         geo[k] = make_geo(imgs[idx[k]]->H, imgs[idx[k]]->W);
-        lay[k] = layout_for(P, geo[k], true, stage_u8, false, false, tbh);
+        lay[k] = layout_for(P, geo[k], true, stage_u8, false, false, tbh, dtype != VLG_U8);
         off[k] = total;
         total += align256(lay[k].total);
     }
@@ -1040,6 +1085,8 @@ int run_batch(vlg_ctx *c, vlg_formula *f, const vlg_image *const *imgs, const st
         d.ws = wb + L.off_slots;
         d.mask_bytes = L.mask_bytes;
         d.off_ccl = L.off_ccl - L.off_slots;
+        d.off_cand = L.off_cand - L.off_slots;
+        d.cand_cap = L.cand_cap;
         d.off_pct = L.off_pct - L.off_slots;
         d.off_pctst = L.off_pctst - L.off_slots;
         d.outs = (uint64_t *const *)(base + d_outs) + (size_t)k * nout;
@@ -1100,6 +1147,8 @@ int run_batch(vlg_ctx *c, vlg_formula *f, const vlg_image *const *imgs, const st
         for (size_t si = 0; si < P.steps.size(); si++)
             for (int k = 0; k < n; k++) (*bytes)[si] += algorithmic_bytes(P, P.steps[si], geo[k], dtype, tbh);
     }
+    bool sampled = true;  // every image of the batch has room for percentile candidates
+    for (int k = 0; k < n; k++) sampled &= lay[k].cand_cap > 0 || geo[k].nwords == 0;
     const CclPlan cp = ccl_plan(P);
     auto enqueue_steps = [&]() -> int {
         for (size_t si = 0; si < P.steps.size(); si++) {
@@ -1152,7 +1201,7 @@ int run_batch(vlg_ctx *c, vlg_formula *f, const vlg_image *const *imgs, const st
                 sel.n = s.npq;
                 for (int j = 0; j < s.npq; j++) sel.slot[j] = s.pct_out[j];
                 e = launch_b_percentile(c->stream, args(BK_ONE), units(BK_ONE), args(BK_PCTH), units(BK_PCTH), s.chan,
-                                        sel);
+                                        sel, sampled);
             }
                 break;
             case SK::Atoms: {
@@ -1874,7 +1923,7 @@ int vlg_profile(vlg_ctx *c, const vlg_formula *cf, const vlg_image *img, int ite
     const bool pj = !vol && P.ccl_count > 0 && ccl_algo(c, img->H, img->W) == VLG_CCL_POINTER_JUMPING;
     if (pj && !pj_shape_ok(img->H, img->W))
         return fail(VLG_ESHAPE, "pointer-jumping labelling: rows and columns must stay below 65535");
-    Layout L = layout_for(P, g, true, false, pj, vol);
+    Layout L = layout_for(P, g, true, false, pj, vol, 0, img->dtype != VLG_U8);
     int rc = ensure_ws(c, L.total);
     if (rc != VLG_OK) return rc;
     std::vector<uint64_t *> ext(which.size());
@@ -2061,7 +2110,7 @@ int vlg_profile_step(vlg_ctx *c, const vlg_formula *cf, const vlg_image *img, co
     if (at == SIZE_MAX) return fail(VLG_EINVAL, "the fused schedule has no single (ungrouped) step of kind " + k);
     const bool pj = !vol && P.ccl_count > 0 && ccl_algo(c, img->H, img->W) == VLG_CCL_POINTER_JUMPING;
     if (pj) return fail(VLG_EINVAL, "not with the pointer-jumping labelling (its rounds wait on the host)");
-    const Layout L = layout_for(P, g, true, false, false, vol);
+    const Layout L = layout_for(P, g, true, false, false, vol, 0, img->dtype != VLG_U8);
     int rc = ensure_ws(c, L.total);
     if (rc != VLG_OK) return rc;
     std::vector<uint64_t *> ext(which.size());
@@ -2181,7 +2230,7 @@ int vlg_autotune(vlg_ctx *c, const vlg_formula *cf, const vlg_image *img, int it
         for (int pj = 0; pj <= (int)try_pj; pj++)
             for (int ln : lane_cands)
                 if (ln == 1 || try_lanes)
-                    need = std::max(need, layout_for(f->plan(which, Mode::Fused, ln, fz), g, true, false, pj).total);
+                    need = std::max(need, layout_for(f->plan(which, Mode::Fused, ln, fz), g, true, false, pj, false, 0, img->dtype != VLG_U8).total);
     std::vector<std::pair<int, std::vector<int>>> space;
     // the labelling schedule first (union-find, then the paper's pointer
     // jumping), then its tile height, then how many labellings run together
@@ -2198,7 +2247,7 @@ int vlg_autotune(vlg_ctx *c, const vlg_formula *cf, const vlg_image *img, int it
         const Plan &P = f->plan(which, Mode::Fused, tuned_value(c, VLG_TUNE_CCL_LANES, img->H, img->W),
                                 tuned_value(c, VLG_TUNE_FUSE_HALO, img->H, img->W));
         const bool pj = P.ccl_count > 0 && ccl_algo(c, img->H, img->W) == VLG_CCL_POINTER_JUMPING;
-        const Layout L = layout_for(P, g, true, false, pj);
+        const Layout L = layout_for(P, g, true, false, pj, false, 0, img->dtype != VLG_U8);
         std::vector<uint64_t *> ext(which.size());
         for (size_t k = 0; k < which.size(); k++) ext[k] = (uint64_t *)((char *)c->ws + L.off_stage + k * L.mask_bytes);
         return enqueue_plan(c, P, img, L, ext);

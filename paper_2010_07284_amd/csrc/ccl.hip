@@ -1057,10 +1057,6 @@ dim3 tile_grid(const Geo &g, const CclMulti &m, int per) {
     const CclGeo q = ccl_geo(g, m.tbh);
     return dim3((unsigned)(((int64_t)per * q.ntx * q.nty + kThreads / 64 - 1) / (kThreads / 64)), (unsigned)m.n);
 }
-int batch_grid(const BatchArgs &a, int64_t total) {
-    return grid_for(total, 1, valid_batch_grid(a.grid_cap) ? a.grid_cap : kBatchGridDefault);
-}
-
 }  // namespace
 
 hipError_t launch_ccl_local(hipStream_t s, const Geo &g, const CclMulti &m) {
@@ -1133,7 +1129,7 @@ hipError_t launch_ccl_labels(hipStream_t s, const Geo &g, const CclMulti &m, int
 
 hipError_t launch_b_ccl_local(hipStream_t s, const BatchArgs &a, int64_t total, const BCcl &o) {
     if (total == 0) return hipSuccess;
-#define K(T) kb_ccl_local<T><<<batch_grid(a, total), kThreads, 0, s>>>(a, o)
+#define K(T) kb_ccl_local<T><<<persistent_grid(a, total), kThreads, 0, s>>>(a, o)
     VLG_BY_TBH(o.tbh, K)
 #undef K
     return hipGetLastError();
@@ -1142,20 +1138,20 @@ hipError_t launch_b_ccl_local(hipStream_t s, const BatchArgs &a, int64_t total, 
 hipError_t launch_b_ccl_merge(hipStream_t s, const BatchArgs &a, int64_t total, const BCcl &o) {
     if (total == 0) return hipSuccess;
     if (!valid_tile_bh(o.tbh)) return hipErrorInvalidValue;
-    kb_ccl_merge<<<batch_grid(a, total), kThreads, 0, s>>>(a, o);
+    kb_ccl_merge<<<persistent_grid(a, total), kThreads, 0, s>>>(a, o);
     return hipGetLastError();
 }
 
 hipError_t launch_b_ccl_flag(hipStream_t s, const BatchArgs &a, int64_t total, const BCcl &o) {
     if (total == 0 || !o.multi) return hipSuccess;
     if (!valid_tile_bh(o.tbh)) return hipErrorInvalidValue;
-    kb_ccl_flag<<<batch_grid(a, total), kThreads, 0, s>>>(a, o);
+    kb_ccl_flag<<<persistent_grid(a, total), kThreads, 0, s>>>(a, o);
     return hipGetLastError();
 }
 
 hipError_t launch_b_ccl_reseed(hipStream_t s, const BatchArgs &a, int64_t total, const BCcl &o) {
     if (total == 0) return hipSuccess;
-#define K(T) kb_ccl_reseed<T><<<batch_grid(a, total), kThreads, 0, s>>>(a, o)
+#define K(T) kb_ccl_reseed<T><<<persistent_grid(a, total), kThreads, 0, s>>>(a, o)
     VLG_BY_TBH(o.tbh, K)
 #undef K
     return hipGetLastError();
@@ -1163,7 +1159,7 @@ hipError_t launch_b_ccl_reseed(hipStream_t s, const BatchArgs &a, int64_t total,
 
 hipError_t launch_b_ccl_gather(hipStream_t s, const BatchArgs &a, int64_t total, const BCcl &o) {
     if (total == 0) return hipSuccess;
-#define K(T) kb_ccl_gather<T><<<batch_grid(a, total), kThreads, 0, s>>>(a, o)
+#define K(T) kb_ccl_gather<T><<<persistent_grid(a, total), kThreads, 0, s>>>(a, o)
     VLG_BY_TBH(o.tbh, K)
 #undef K
     return hipGetLastError();

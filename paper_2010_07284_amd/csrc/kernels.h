@@ -38,6 +38,8 @@ __host__ __device__ inline int near_band_rows(const Geo &g) {
 }
 constexpr int kBatchNearRows = 8;
 inline bool valid_near_rows(int r) { return r == 4 || r == 8 || r == 16 || r == 32; }
+// channel elements per batched unit of a percentile pass
+constexpr int64_t kPctUnit = 65536;
 constexpr int kBatchGridDefault = 8192;
 inline bool valid_batch_grid(int n) { return n == 1024 || n == 2048 || n == 4096 || n == 8192; }
 __host__ __device__ inline int64_t near_tasks(const Geo &g, int R) {
@@ -375,6 +377,8 @@ struct BImg {
     char *ws;               // this image's workspace: mask slots, labelling, percentiles
     uint64_t mask_bytes;    // slot stride
     uint64_t off_ccl, off_pct, off_pctst;
+    uint64_t off_cand;      // percentile candidates: cand_cap per rank of a step
+    uint32_t cand_cap, pad;
     uint64_t *const *outs;  // packed output buffer per external slot
     const uint32_t *ranks;  // percentile rank per percentile slot
 };
@@ -448,15 +452,17 @@ struct PctSel {
     uint32_t k[kMaxPctSel];
 };
 hipError_t launch_b_percentile(hipStream_t s, const BatchArgs &one, int64_t total_one, const BatchArgs &hist,
-                               int64_t total_hist, int chan, const PctSel &sel);
+                               int64_t total_hist, int chan, const PctSel &sel, bool sampled);
 }  // namespace vlg
 
 namespace vlg {
-// Percentiles (k-th smallest value of a channel, nearest rank) by radix
-// select over order-preserving uint32 keys, several ranks of one channel per
-// pass over it.  Slot p has kPctStateBytes of device state at
-// states + p * kPctStateBytes; its value is written to results[p].
+// Percentiles (k-th smallest value of a channel, nearest rank), several ranks
+// of one channel per pass over it.  Slot p has kPctStateBytes of device state
+// at states + p * kPctStateBytes; its value is written to results[p].  cand:
+// room for cap candidate keys per rank (pct_candidates(pixels) of them for the
+// sampled select; cap = 0 selects by radix passes).
+inline uint32_t pct_candidates(int64_t pixels) { return (uint32_t)(pixels / 16); }
 constexpr size_t kPctStateBytes = 41216;
 hipError_t launch_percentile(hipStream_t s, const Geo &g, const void *chan, int dtype, const PctSel &sel,
-                             void *states, float *results);
+                             void *states, float *results, uint32_t *cand, uint32_t cap);
 }  // namespace vlg

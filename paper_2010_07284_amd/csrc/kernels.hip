@@ -2,8 +2,8 @@
 //
 // Operators (paper "A spatial model checker in GPU", Sect. 2): threshold
 // atoms, pixel-wise Boolean connectives, N (Moore-neighbourhood dilation),
-// fused segments of the last two, and the radix-select
-// percentiles.  The reachability labelling is in ccl.hip.
+// and fused segments of the last two.  The reachability labelling is in
+// ccl.hip, percentiles are in pct.hip.
 //
 // Every operator is written once as a per-unit device function; single-image
 // kernels walk one image's units, batch kernels walk the units of many
@@ -15,29 +15,12 @@
 namespace vlg {
 namespace {
 
-// channel elements per batched histogram unit: large enough that flushing a
-// workgroup's LDS histograms (up to 8192 bins, global atomics that all units
-// of an image aim at the same addresses) stays small next to the reads
-constexpr int64_t kPctUnit = 262144;
-
 // ------------------------------------------------------------------ Boolean
 // out = ((x ^ x.inv) OP (y ^ y.inv)) ^ inv_out, OP = and (op 0) / or (op 1).
 // A null operand is a constant (its inv); the loops below are specialised on
 // that once per launch so that every load is unconditional and a thread keeps
 // kLogicUnroll words in flight.
 constexpr int kLogicUnroll = 4;
-
-// A launch whose operands add up to more than the last-level cache (256 MB
-// Infinity Cache) cannot leave them cached for the next launch, so it reads
-// them with the non-temporal hint (a connective over 265 MB masks went from
-// 59% to over 80% of HBM peak with it); smaller launches read normally, since
-// the next step of a schedule usually reads their operands again.
-constexpr int64_t kStreamBytes = 256ll << 20;
-template <bool NT, typename T>
-__device__ __forceinline__ T ld_hint(const VLG_GLOBAL T *p) {
-    if constexpr (NT) return __builtin_nontemporal_load(p);
-    else return *p;
-}
 
 template <bool HX, bool HY, bool NT>
 __device__ __forceinline__ void logic_span(const Geo &g, const uint64_t *__restrict__ xg, uint64_t xinv,
@@ -790,10 +773,6 @@ int64_t batch_units(const Geo &g, int kind, int tbh) {
     return 0;
 }
 
-static int persistent_grid(const BatchArgs &a, int64_t total) {
-    return grid_for(total, 1, valid_batch_grid(a.grid_cap) ? a.grid_cap : kBatchGridDefault);
-}
-
 hipError_t launch_b_atoms(hipStream_t s, const BatchArgs &a, int64_t total, const BAtoms &op) {
     if (total == 0) return hipSuccess;
     if (op.n < 1 || op.n > kMaxAtomsPerLaunch) return hipErrorInvalidValue;
@@ -830,357 +809,6 @@ hipError_t launch_b_near(hipStream_t s, const BatchArgs &a, int64_t total, const
     if (total == 0 || op.n == 0) return hipSuccess;
     dim3 grid(persistent_grid(a, total), op.n);
     kb_near<<<grid, kThreads, 0, s>>>(a, op);
-    return hipGetLastError();
-}
-
-}  // namespace vlg
-
-// ------------------------------------------------------------------ percentile
-// Radix select: keys are the float32 bit patterns made order-preserving
-// (negatives complemented, positives with the sign bit set) or the uint8
-// values.  Each pass histograms one digit of the keys that agree with the
-// digits chosen so far, then a single workgroup finds the bucket holding rank
-// k.  float32 uses digits of 13, 10 and 9 bits in batches (the first pass
-// has a single group, so its histogram takes the LDS of all four) and 11, 11
-// and 10 bits on single images (whose workgroups read fewer elements, so a
-// wider histogram to clear and add costs more than its fewer LDS conflicts
-// save); uint8 one digit of 8 bits, uint16 two.
-namespace vlg {
-namespace {
-
-// Selections of a pass whose digits chosen so far agree share one
-// histogram: that of the first of them in the step, whose slot is `src`.
-// Passes 0 and 2 count into `a`, pass 1 into `b`, so the selection of pass 1
-// can clear `a` while others still read `b`.
-struct PctState {
-    uint32_t prefix, mask, k, src;
-    uint32_t a[8192];
-    uint32_t b[2048];
-};
-static_assert(sizeof(PctState) <= kPctStateBytes, "percentile state");
-
-__device__ __forceinline__ uint32_t f32_key(float f) {
-    const uint32_t u = __float_as_uint(f);
-    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
-
-__device__ __forceinline__ float key_f32(uint32_t k) {
-    const uint32_t u = (k & 0x80000000u) ? (k & 0x7fffffffu) : ~k;
-    return __uint_as_float(u);
-}
-
-__device__ void pct_init_wg(PctState *st_, uint32_t k, int slot) {
-    VLG_GLOBAL PctState *st = glb(st_);
-    for (int i = threadIdx.x; i < 8192; i += blockDim.x) st->a[i] = 0;
-    for (int i = threadIdx.x; i < 2048; i += blockDim.x) st->b[i] = 0;
-    if (threadIdx.x == 0) {
-        st->prefix = 0;
-        st->mask = 0;
-        st->k = k;
-        st->src = (uint32_t)slot;
-    }
-}
-
-
-template <typename T> struct Vec4;
-template <> struct Vec4<float> { typedef float type __attribute__((ext_vector_type(4))); };
-template <> struct Vec4<uint8_t> { typedef uint8_t type __attribute__((ext_vector_type(4))); };
-template <> struct Vec4<uint16_t> { typedef uint16_t type __attribute__((ext_vector_type(4))); };
-
-// Histogram the channel elements of the chunks [c, c + 1024) for c = i0,
-// i0 + stride, ... below i1 (a channel is stored with pitch wpr*64; i0,
-// stride and i1 are multiples of 1024 or of the pitch, so four consecutive
-// elements share a row), for the n selections st[0..n): selections whose
-// digits chosen so far agree share one LDS histogram (in the first pass all
-// of them do), which is then added into the state of the group's first
-// selection.
-// The streaming part of a histogram pass over elements [i0, i1): MG is the
-// number of groups the group test has to try (one in every first pass).
-template <typename T, int MG, bool NT>
-__device__ __forceinline__ void pct_hist_stream(const Geo &g, const T *__restrict__ img, int m, const uint32_t *pre,
-                                                const uint32_t *msk, int shift, int bins, int64_t i0, int64_t i1,
-                                                int64_t stride, uint32_t (*h)[2048]) {
-    const int64_t pitch = (int64_t)g.wpr * 64;
-    const uint32_t dmask = (uint32_t)(bins - 1);
-    using V = typename Vec4<T>::type;
-    constexpr int U = 8;  // chunks per iteration: U vector loads in flight per thread
-    for (int64_t c = i0; c < i1; c += U * stride) {
-        V v[U];
-        int64_t idx[U];
-#pragma unroll
-        for (int u = 0; u < U; u++) {
-            idx[u] = c + u * stride + threadIdx.x * 4;
-            v[u] = ld_hint<NT>((const VLG_GLOBAL V *)(glb(img) + (idx[u] < i1 ? idx[u] : i0)));
-        }
-#pragma unroll
-        for (int u = 0; u < U; u++) {
-            const int64_t i = idx[u];
-            const bool in = i < i1;
-            const uint32_t row = fdiv((uint32_t)(i >> 6), g.wpr_mul, g.wpr_shift);
-            const int64_t col = i - (int64_t)row * pitch;
-            const float f[4] = {(float)v[u].x, (float)v[u].y, (float)v[u].z, (float)v[u].w};
-            uint32_t key[4];
-#pragma unroll
-            for (int e = 0; e < 4; e++) key[e] = sizeof(T) < 4 ? (uint32_t)f[e] : f32_key(f[e]);
-            // the groups of a pass share the digit mask and differ in prefix,
-            // so an element belongs to at most one of them
-            uint32_t bin[4];
-            bool act[4];
-#pragma unroll
-            for (int e = 0; e < 4; e++) {
-                int grp = -1;
-#pragma unroll
-                for (int q = MG - 1; q >= 0; q--)
-                    if (q < m && (key[e] & msk[q]) == pre[q]) grp = q;
-                act[e] = in && col + e < g.W && grp >= 0;
-                bin[e] = (uint32_t)max(grp, 0) * 2048u + ((key[e] >> shift) & dmask);
-            }
-            // four neighbouring elements in one bin (channel values cluster)
-            // take one atomic; otherwise each active element adds its own
-            uint32_t *hh = &h[0][0];
-            if (act[0] && act[1] && act[2] && act[3] && bin[0] == bin[1] && bin[1] == bin[2] && bin[2] == bin[3]) {
-                atomicAdd(&hh[bin[0]], 4u);
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; e++)
-                    if (act[e]) atomicAdd(&hh[bin[e]], 1u);
-            }
-        }
-    }
-}
-
-template <typename T, bool NT>
-__device__ void pct_hist_range(const Geo &g, const T *__restrict__ img, PctState *const *st, const int32_t *slot,
-                               int n, int pass, int shift, int bins, int64_t i0, int64_t i1, int64_t stride,
-                               uint32_t (*h)[2048]) {
-    __shared__ uint32_t gpre[kMaxPctSel], gmask[kMaxPctSel];
-    __shared__ int rep[kMaxPctSel], first[kMaxPctSel], ngroups;
-    if (threadIdx.x == 0) {
-        int m = 0;
-        for (int j = 0; j < n; j++) {
-            const uint32_t p = glb(st[j])->prefix, mk = glb(st[j])->mask;
-            int r = -1;
-            for (int q = 0; q < m; q++)
-                if (gpre[q] == p && gmask[q] == mk) r = q;
-            if (r < 0) {
-                gpre[m] = p;
-                gmask[m] = mk;
-                first[m] = j;
-                r = m++;
-            }
-            rep[j] = r;
-        }
-        ngroups = m;
-        // (every workgroup writes the same values)
-        for (int j = 0; j < n; j++) glb(st[j])->src = (uint32_t)slot[first[rep[j]]];
-    }
-    __syncthreads();
-    // the group table in registers: the histogram atomics below write LDS, so
-    // values left in LDS would be reloaded after every one of them
-    const int m = ngroups;
-    uint32_t pre[kMaxPctSel], msk[kMaxPctSel];
-#pragma unroll
-    for (int q = 0; q < kMaxPctSel; q++) {
-        pre[q] = q < m ? gpre[q] : 0u;
-        msk[q] = q < m ? gmask[q] : 0u;
-    }
-    // group q's bins at q * 2048 (a single group may take all 8192)
-    uint32_t *hh = &h[0][0];
-    for (int i = threadIdx.x; i < (m - 1) * 2048 + bins; i += kThreads) hh[i] = 0;
-    __syncthreads();
-    if (m == 1)
-        pct_hist_stream<T, 1, NT>(g, img, m, pre, msk, shift, bins, i0, i1, stride, h);
-    else
-        pct_hist_stream<T, kMaxPctSel, NT>(g, img, m, pre, msk, shift, bins, i0, i1, stride, h);
-    __syncthreads();
-    // each group's histogram into its first selection's state
-    for (int q = 0; q < m; q++) {
-        VLG_GLOBAL uint32_t *gh = pass == 1 ? glb(st[first[q]])->b : glb(st[first[q]])->a;
-        for (int i = threadIdx.x; i < bins; i += kThreads) {
-            const uint32_t cnt = hh[q * 2048 + i];
-            if (cnt) __hip_atomic_fetch_add(&gh[i], cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-    }
-    __syncthreads();
-}
-
-// one workgroup of 256 threads: find the bucket holding rank k
-// (src: the state whose histogram the selection shares in this pass)
-__device__ void pct_select_wg(PctState *st_, const PctState *src, int pass, int shift, int bins, int last,
-                              int is_int, float *result_, uint32_t *part) {
-    VLG_GLOBAL PctState *st = glb(st_);
-    VLG_GLOBAL float *result = glb(result_);
-    const VLG_GLOBAL uint32_t *hist = pass == 1 ? glb(src)->b : glb(src)->a;
-    const int per = bins / kThreads;
-    uint32_t local = 0;
-    for (int j = 0; j < per; j++) local += hist[threadIdx.x * per + j];
-    part[threadIdx.x] = local;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t acc = 0, k = st->k;
-        int t = 0;
-        while (t < kThreads - 1 && acc + part[t] <= k) acc += part[t++];
-        int b = t * per;
-        while (b < t * per + per - 1 && acc + hist[b] <= k) acc += hist[b++];
-        st->k = k - acc;
-        st->prefix |= (uint32_t)b << shift;
-        st->mask |= (uint32_t)(bins - 1) << shift;
-        if (last) *result = is_int ? (float)st->prefix : key_f32(st->prefix);
-    }
-    // `a` is read only by the selections of passes 0 and 2: after pass 1 it
-    // is cleared for pass 2
-    if (pass == 1)
-        for (int i = threadIdx.x; i < 8192; i += kThreads) st->a[i] = 0;
-    __syncthreads();
-}
-
-__device__ __forceinline__ PctState *sstate(void *states, int slot) {
-    return (PctState *)((char *)states + (size_t)slot * kPctStateBytes);
-}
-
-__global__ void k_pct_init(PctSel sel, void *states) {
-    pct_init_wg(sstate(states, sel.slot[blockIdx.x]), sel.k[blockIdx.x], sel.slot[blockIdx.x]);
-}
-
-template <typename T, bool NT>
-__global__ __launch_bounds__(kThreads) void k_pct_hist(Geo g, const T *__restrict__ img, PctSel sel, void *states,
-                                                       int pass, int shift, int bins) {
-    __shared__ uint32_t h[kMaxPctSel][2048];
-    PctState *st[kMaxPctSel];
-    for (int j = 0; j < sel.n; j++) st[j] = sstate(states, sel.slot[j]);
-    // one contiguous range of whole chunks per workgroup: neighbouring
-    // pixels share bins, so the histogram a workgroup adds into the state has
-    // fewer nonzero bins than that of a strided range
-    const int64_t n = (int64_t)g.H * g.wpr * 64, chunks = (n + kThreads * 4 - 1) / (kThreads * 4);
-    const int64_t per = (chunks + gridDim.x - 1) / gridDim.x * (kThreads * 4);
-    const int64_t i0 = (int64_t)blockIdx.x * per, i1 = i0 + per < n ? i0 + per : n;
-    pct_hist_range<T, NT>(g, img, st, sel.slot, sel.n, pass, shift, bins, i0, i1, kThreads * 4, h);
-}
-
-__global__ __launch_bounds__(kThreads) void k_pct_select(PctSel sel, void *states, int pass, int shift, int bins,
-                                                         int last, int is_int, float *results) {
-    __shared__ uint32_t part[kThreads];
-    const int slot = sel.slot[blockIdx.x];
-    PctState *st = sstate(states, slot);
-    pct_select_wg(st, sstate(states, (int)glb(st)->src), pass, shift, bins, last, is_int, results + slot, part);
-}
-
-// batch variants: state and result of percentile slot p live in each image's workspace
-__device__ __forceinline__ PctState *bstate(const BImg &d, int p) {
-    return (PctState *)(d.ws + d.off_pctst + (uint64_t)p * kPctStateBytes);
-}
-
-__global__ void kb_pct_init(BatchArgs a, PctSel sel) {
-    UnitRange ur(a.prefix, a.n);
-    for (int64_t u = ur.begin; u < ur.end; u++) {
-        const int ii = ur.img(u);
-        for (int j = 0; j < sel.n; j++) {
-            pct_init_wg(bstate(a.imgs[ii], sel.slot[j]), a.imgs[ii].ranks[sel.slot[j]], sel.slot[j]);
-            __syncthreads();
-        }
-    }
-}
-
-template <typename T, bool NT>
-__global__ __launch_bounds__(kThreads) void kb_pct_hist(BatchArgs a, int chan, PctSel sel, int pass, int shift,
-                                                        int bins) {
-    __shared__ uint32_t h[kMaxPctSel][2048];
-    UnitRange ur(a.prefix, a.n);
-    for (int64_t u = ur.begin; u < ur.end; u++) {
-        const int ii = ur.img(u);
-        const BImg d = a.imgs[ii];  // by value (see UnitRange)
-        PctState *st[kMaxPctSel];
-        for (int j = 0; j < sel.n; j++) st[j] = bstate(d, sel.slot[j]);
-        const int64_t i0 = (u - a.prefix[ii]) * kPctUnit;
-        const int64_t n = (int64_t)d.g.H * d.g.wpr * 64;
-        const int64_t i1 = i0 + kPctUnit < n ? i0 + kPctUnit : n;
-        pct_hist_range<T, NT>(d.g, (const T *)(d.img + (int64_t)chan * d.chan_bytes), st, sel.slot, sel.n, pass, shift,
-                              bins, i0, i1,
-                       kThreads * 4, h);
-    }
-}
-
-__global__ __launch_bounds__(kThreads) void kb_pct_select(BatchArgs a, PctSel sel, int pass, int shift, int bins,
-                                                          int last, int is_int) {
-    __shared__ uint32_t part[kThreads];
-    const int slot = sel.slot[blockIdx.y];
-    UnitRange ur(a.prefix, a.n);
-    for (int64_t u = ur.begin; u < ur.end; u++) {
-        const int ii = ur.img(u);
-        const BImg d = a.imgs[ii];  // by value (see UnitRange)
-        PctState *st = bstate(d, slot);
-        pct_select_wg(st, bstate(d, (int)glb(st)->src), pass, shift, bins, last, is_int,
-                      (float *)(d.ws + d.off_pct) + slot, part);
-    }
-}
-
-}  // namespace
-
-hipError_t launch_percentile(hipStream_t s, const Geo &g, const void *chan, int dtype, const PctSel &sel,
-                             void *states, float *results) {
-    if (sel.n < 1 || sel.n > kMaxPctSel) return hipErrorInvalidValue;
-    k_pct_init<<<sel.n, kThreads, 0, s>>>(sel, states);
-    const int64_t n = (int64_t)g.H * g.wpr * 64;
-    if (n == 0) return hipGetLastError();
-    // at least 32 chunks of 1024 elements per workgroup, so that clearing and
-    // adding its histogram (up to 8192 bins) stays small next to its reads
-    const int grid = grid_for(n, kThreads * 4 * 32, 2048);
-    if (dtype == 1) {
-        if (n > kStreamBytes) k_pct_hist<uint8_t, true><<<grid, kThreads, 0, s>>>(g, (const uint8_t *)chan, sel, states, 0, 0, 256);
-        else k_pct_hist<uint8_t, false><<<grid, kThreads, 0, s>>>(g, (const uint8_t *)chan, sel, states, 0, 0, 256);
-        k_pct_select<<<sel.n, kThreads, 0, s>>>(sel, states, 0, 0, 256, 1, 1, results);
-        return hipGetLastError();
-    }
-    if (dtype == 2) {  // uint16: two 8-bit digits
-        for (int p = 0; p < 2; p++) {
-            if (2 * n > kStreamBytes)
-                k_pct_hist<uint16_t, true><<<grid, kThreads, 0, s>>>(g, (const uint16_t *)chan, sel, states, p, 8 - 8 * p, 256);
-            else
-                k_pct_hist<uint16_t, false><<<grid, kThreads, 0, s>>>(g, (const uint16_t *)chan, sel, states, p, 8 - 8 * p, 256);
-            k_pct_select<<<sel.n, kThreads, 0, s>>>(sel, states, p, 8 - 8 * p, 256, p == 1, 1, results);
-        }
-        return hipGetLastError();
-    }
-    const int shifts[3] = {21, 10, 0}, bins[3] = {2048, 2048, 1024};
-    for (int p = 0; p < 3; p++) {
-        if (4 * n > kStreamBytes)
-            k_pct_hist<float, true><<<grid, kThreads, 0, s>>>(g, (const float *)chan, sel, states, p, shifts[p], bins[p]);
-        else
-            k_pct_hist<float, false><<<grid, kThreads, 0, s>>>(g, (const float *)chan, sel, states, p, shifts[p], bins[p]);
-        k_pct_select<<<sel.n, kThreads, 0, s>>>(sel, states, p, shifts[p], bins[p], p == 2, 0, results);
-    }
-    return hipGetLastError();
-}
-
-hipError_t launch_b_percentile(hipStream_t s, const BatchArgs &one, int64_t total_one, const BatchArgs &hist,
-                               int64_t total_hist, int chan, const PctSel &sel) {
-    if (total_one == 0) return hipSuccess;
-    if (sel.n < 1 || sel.n > kMaxPctSel) return hipErrorInvalidValue;
-    const int g1 = persistent_grid(one, total_one), gh = persistent_grid(hist, total_hist);
-    kb_pct_init<<<g1, kThreads, 0, s>>>(one, sel);
-    dim3 gs(g1, sel.n);
-    // a histogram unit is kPctUnit channel elements
-    const bool nt = total_hist * kPctUnit * (hist.dtype == 1 ? 1 : hist.dtype == 2 ? 2 : 4) > kStreamBytes;
-    if (hist.dtype == 1) {
-        if (nt) kb_pct_hist<uint8_t, true><<<gh, kThreads, 0, s>>>(hist, chan, sel, 0, 0, 256);
-        else kb_pct_hist<uint8_t, false><<<gh, kThreads, 0, s>>>(hist, chan, sel, 0, 0, 256);
-        kb_pct_select<<<gs, kThreads, 0, s>>>(one, sel, 0, 0, 256, 1, 1);
-        return hipGetLastError();
-    }
-    if (hist.dtype == 2) {  // uint16: two 8-bit digits
-        for (int p = 0; p < 2; p++) {
-            if (nt) kb_pct_hist<uint16_t, true><<<gh, kThreads, 0, s>>>(hist, chan, sel, p, 8 - 8 * p, 256);
-            else kb_pct_hist<uint16_t, false><<<gh, kThreads, 0, s>>>(hist, chan, sel, p, 8 - 8 * p, 256);
-            kb_pct_select<<<gs, kThreads, 0, s>>>(one, sel, p, 8 - 8 * p, 256, p == 1, 1);
-        }
-        return hipGetLastError();
-    }
-    const int shifts[3] = {19, 9, 0}, bins[3] = {8192, 1024, 512};
-    for (int p = 0; p < 3; p++) {
-        if (nt) kb_pct_hist<float, true><<<gh, kThreads, 0, s>>>(hist, chan, sel, p, shifts[p], bins[p]);
-        else kb_pct_hist<float, false><<<gh, kThreads, 0, s>>>(hist, chan, sel, p, shifts[p], bins[p]);
-        kb_pct_select<<<gs, kThreads, 0, s>>>(one, sel, p, shifts[p], bins[p], p == 2, 0);
-    }
     return hipGetLastError();
 }
 
