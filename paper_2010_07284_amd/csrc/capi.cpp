@@ -740,8 +740,6 @@ int enqueue_plan(vlg_ctx *c, const Plan &P, const vlg_image *img, const Layout &
         const int lane = s.lane > 0 ? s.lane : 0;
         hipStream_t stream = c->stream;
         const PjWork pw = pj_work(base + L.off_ccl + (size_t)lane * L.lane_bytes, g);
-        int *vP = (int *)(base + L.off_ccl + (size_t)lane * L.lane_bytes);
-        uint8_t *vflag = (uint8_t *)vP + vol_label_bytes(g);
         if (hook) hook(hook_ctx, si, true);
         hipError_t e = hipSuccess;
         if (s.group >= 0) {
@@ -830,10 +828,7 @@ int enqueue_plan(vlg_ctx *c, const Plan &P, const vlg_image *img, const Layout &
             break;
         case SK::CclLocal:
             if (L.vol) {
-                // the whole voxel labelling, then the seeds
-                e = launch_vl_label(stream, g, vS, vD, mref(s.x), vP, m0.guard);
-                if (e == hipSuccess) e = launch_vl_clear_flags(stream, g, vS, vD, vflag);
-                if (e == hipSuccess) e = launch_vl_seed(stream, g, vS, vD, mref(s.x), mref(s.y), mref(s.z), vP, vflag, 0);
+                e = launch_vl_label(stream, g, vS, vD, ccl_op(si), m0.guard);  // the whole labelling and its seeds
             } else if (L.pj) {
                 // the whole labelling (host-waited rounds), then the seeds
                 const int rc = pj_label(c, stream, g, mref(s.x), pw, pj_k, pj_at);
@@ -852,8 +847,7 @@ int enqueue_plan(vlg_ctx *c, const Plan &P, const vlg_image *img, const Layout &
             break;
         case SK::CclGather:
             if (L.vol)
-                e = launch_vl_gather(stream, g, vS, vD, mref(s.x), mref(s.y), mref(s.z), vP, vflag, s.user,
-                                     slot_ptr(s.out));
+                e = launch_vl_gather(stream, g, vS, vD, ccl_op(si), m0.guard);
             else if (L.pj)
                 e = launch_pj_gather(stream, g, mref(s.x), mref(s.y), mref(s.z), pw, pj_at, s.user, slot_ptr(s.out));
             else
@@ -861,7 +855,7 @@ int enqueue_plan(vlg_ctx *c, const Plan &P, const vlg_image *img, const Layout &
             break;
         case SK::CclReseed:
             if (L.vol)
-                e = launch_vl_reseed(stream, g, vS, vD, mref(s.x), vP, vflag, s.user);
+                e = launch_vl_reseed(stream, g, vS, vD, ccl_op(si), m0.guard);
             else if (L.pj)
                 e = launch_pj_reseed(stream, g, mref(s.x), pw, pj_at, s.user);
             else
@@ -1652,13 +1646,12 @@ int vlg_ccl_labels3(vlg_ctx *c, const uint64_t *mask_dev, int depth, int height,
     const Geo g = make_geo(depth * height, width);
     if (g.nwords == 0) return VLG_OK;
     // block parents and each component's smallest voxel in the workspace
-    const size_t pb = align256((size_t)vl_nblocks(g, height, depth) * 4);
+    const size_t pb = align256(((size_t)vl_nblocks(g, height, depth) + 1) * 4);
     int rc = ensure_ws(c, 2 * pb);
     if (rc != VLG_OK) return rc;
     int *P = (int *)c->ws, *canon = (int *)((char *)c->ws + pb);
     const MRef b{mask_dev, 0ull};
-    HIP_TRY(launch_vl_label(c->stream, g, height, depth, b, P, c->guard()));
-    HIP_TRY(launch_vl_labels(c->stream, g, height, depth, b, P, canon, labels_dev));
+    HIP_TRY(launch_vl_labels(c->stream, g, height, depth, b, P, canon, labels_dev, c->guard()));
     return VLG_OK;
 }
 

@@ -265,24 +265,16 @@ hipError_t launch_arith(hipStream_t s, const Geo &g, const void *img, int64_t ch
 // N over the 26-neighbourhood: out = (N(x) ^ inv_out) OP z (zop 0 and, 1 or).
 hipError_t launch_near3(hipStream_t s, const Geo &g, int S, int D, MRef x, int inv_out, MRef z, int zop,
                         uint64_t *out);
-// 26-connected labelling of b over blocks of 2 x 2 x 2 voxels: P[k] = the
-// root block (the smallest block id) of block k's component, -1 for a block
-// without voxels of b; P has vl_nblocks entries, at most g.BH * g.BW (the
-// block count of the D*S-row mask).
+// 26-connected labelling over the runs of 2 x 2 x 2 voxel blocks (CclOp as for
+// images; workspace: 5 bytes per block, at least 5 * 256).
 int64_t vl_nblocks(const Geo &g, int S, int D);
-hipError_t launch_vl_label(hipStream_t s, const Geo &g, int S, int D, MRef b, int *P, const LoopGuard &gd);
+hipError_t launch_vl_label(hipStream_t s, const Geo &g, int S, int D, const CclOp &o, const LoopGuard &gd);
+hipError_t launch_vl_reseed(hipStream_t s, const Geo &g, int S, int D, const CclOp &o, const LoopGuard &gd);
+hipError_t launch_vl_gather(hipStream_t s, const Geo &g, int S, int D, const CclOp &o, const LoopGuard &gd);
 // labels[v] (voxel index (z*S + y)*W + x) = the smallest voxel of v's
-// component, -1 for background, from a labelling P; canon: vl_nblocks ints.
-hipError_t launch_vl_labels(hipStream_t s, const Geo &g, int S, int D, MRef b, const int *P, int *canon,
-                            int *labels);
-// flag: one byte per block
-hipError_t launch_vl_clear_flags(hipStream_t s, const Geo &g, int S, int D, uint8_t *flag);
-hipError_t launch_vl_seed(hipStream_t s, const Geo &g, int S, int D, MRef b, MRef y, MRef z, const int *P,
-                          uint8_t *flag, int user);
-hipError_t launch_vl_reseed(hipStream_t s, const Geo &g, int S, int D, MRef sm, const int *P, uint8_t *flag,
-                            int user);
-hipError_t launch_vl_gather(hipStream_t s, const Geo &g, int S, int D, MRef b, MRef y, MRef z, const int *P,
-                            const uint8_t *flag, int user, uint64_t *out);
+// component, -1 for background; par and canon: vl_nblocks + 1 ints each.
+hipError_t launch_vl_labels(hipStream_t s, const Geo &g, int S, int D, MRef b, int *par, int *canon, int *labels,
+                            const LoopGuard &gd);
 
 // The paper's labelling (Sect. 3, Alg. CCL), pj.hip.  lab[0], lab[1]: the
 // ping-pong label arrays [H][W] (keys ((row << 16) | column) + 1, 0 = null);
