@@ -276,7 +276,9 @@ int vlg_ccl_read_counters(vlg_ctx *ctx, vlg_ccl_counters *out);
  * pixel points to, the largest label around that pixel when it is larger
  * (atomic maximum over the writers), and the termination check looks for
  * two neighbouring pixels of the mask with different labels.  The host
- * waits for the check after every round, as the paper's tool does.
+ * waits for the check after every round, as the paper's tool does; up to
+ * four main iterations of the next round are enqueued before that wait and
+ * return at once when the check passed (they are not counted then).
  * labels_dev (device int32 [height][width]) receives, for each pixel of the
  * mask, the row-major index y*width+x of its component's largest pixel, -1
  * for background.  stats (optional) receives the main iterations, rounds

@@ -211,6 +211,7 @@ struct vlg_ctx {
     void *desc_host = nullptr;
     size_t desc_host_size = 0;
     hipEvent_t desc_done = nullptr;
+    hipEvent_t pj_checked = nullptr;  // a pointer-jumping round's check is on the host
 
     // an executable graph may still be running from an earlier launch: wait
     // for the stream (its parallel branches join into it) before destroying
@@ -509,27 +510,44 @@ int pj_reconnect_every(const vlg_ctx *c, int H, int W) {
 // host waiting for the check's word after every round as the paper's tool
 // does.  On return the labels are in w.lab[at].  VLG_ENOCONV when the check
 // still fails after the context's loop cap of rounds.
+constexpr int kPjAhead = 4;
 int pj_label(vlg_ctx *c, hipStream_t s, const Geo &g, MRef b, const PjWork &w, int k, int &at) {
-    HIP_TRY(launch_pj_init(s, g, b, w));
     at = 0;
+    if (g.nwords == 0) return VLG_OK;
+    if (!c->pj_checked) HIP_TRY(hipEventCreateWithFlags(&c->pj_checked, hipEventDisableTiming));
+    HIP_TRY(launch_pj_init(s, g, b, w));
     int64_t launches = 1;
+    int ahead = 0;  // main iterations of this round that are enqueued already
     for (int64_t round = 0;; round++) {
         if (round >= c->loop_cap)
             return fail(VLG_ENOCONV, "pointer-jumping labelling: the termination check still fails after " +
                                          std::to_string(round) + " rounds (the loop cap)");
-        for (int it = 0; it < k; it++) {
-            HIP_TRY(launch_pj_main(s, g, b, w, at));
+        for (int it = ahead; it < k; it++) {
+            HIP_TRY(launch_pj_main(s, g, b, w, at, nullptr));
             at ^= 1;
         }
         HIP_TRY(launch_pj_reconnect(s, g, b, w, at));
         at ^= 1;
-        HIP_TRY(launch_pj_check(s, g, b, w, at));
+        HIP_TRY(launch_pj_check(s, g, b, w, at, round, c->status_host + 1));
+        HIP_TRY(hipEventRecord(c->pj_checked, s));
         launches += k + 4;
         c->pj_iters += k;
         c->pj_rounds++;
-        HIP_TRY(hipMemcpyAsync(c->status_host + 1, w.term, sizeof(unsigned int), hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
-        if (c->status_host[1] == 0) break;
+        // While the host waits for the check the GPU goes on with the next
+        // round's first main iterations, which return at once when the check
+        // passed: the labels are final then and stay as they are.  (About
+        // 40 us of waiting per round at 2048^2; an iteration that returns at once
+        // takes about 2 us.)
+        const int final_at = at;
+        for (ahead = 0; round + 1 < c->loop_cap && ahead < std::min(k, kPjAhead); ahead++) {
+            HIP_TRY(launch_pj_main(s, g, b, w, at, w.term + (round & 1)));
+            at ^= 1;
+        }
+        HIP_TRY(hipEventSynchronize(c->pj_checked));
+        if (c->status_host[1] == 0) {
+            at = final_at;
+            break;
+        }
     }
     c->pj_launches += launches;
     c->pj_labellings++;
@@ -1521,6 +1539,7 @@ void vlg_destroy(vlg_ctx *c) {
     if (c->status_host) (void)hipHostFree(c->status_host);
     if (c->desc_host) (void)hipHostFree(c->desc_host);
     if (c->desc_done) (void)hipEventDestroy(c->desc_done);
+    if (c->pj_checked) (void)hipEventDestroy(c->pj_checked);
     if (c->own_stream) (void)hipStreamDestroy(c->stream);
     delete c;
 }

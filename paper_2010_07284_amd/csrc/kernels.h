@@ -279,9 +279,10 @@ hipError_t launch_vl_labels(hipStream_t s, const Geo &g, int S, int D, MRef b, i
 // The paper's labelling (Sect. 3, Alg. CCL), pj.hip.  lab[0], lab[1]: the
 // ping-pong label arrays [H][W] (keys ((row << 16) | column) + 1, 0 = null);
 // flag: [H][W] seed bytes indexed by a label's pixel (bit 1+u: the seeds of
-// labelling user u); term: the termination check's word (non-zero: some
-// pixel has a neighbour with another label).  `from` / `at` select the
-// label array a step reads.
+// labelling user u); term: the termination check's words of even and odd
+// rounds (non-zero: some pixel has a neighbour with another label), copied to
+// the host's word `host` after the check.  `from` / `at` select the label
+// array a step reads; `go`: the step does nothing when that word is 0.
 struct PjWork {
     uint32_t *lab[2];
     uint8_t *flag;
@@ -302,9 +303,10 @@ inline PjWork pj_work(void *base, const Geo &g) {
     return w;
 }
 hipError_t launch_pj_init(hipStream_t s, const Geo &g, MRef b, const PjWork &w);
-hipError_t launch_pj_main(hipStream_t s, const Geo &g, MRef b, const PjWork &w, int from);
+hipError_t launch_pj_main(hipStream_t s, const Geo &g, MRef b, const PjWork &w, int from, const uint32_t *go);
 hipError_t launch_pj_reconnect(hipStream_t s, const Geo &g, MRef b, const PjWork &w, int from);
-hipError_t launch_pj_check(hipStream_t s, const Geo &g, MRef b, const PjWork &w, int at);
+hipError_t launch_pj_check(hipStream_t s, const Geo &g, MRef b, const PjWork &w, int at, int64_t round,
+                           uint32_t *host);
 hipError_t launch_pj_clear_flags(hipStream_t s, const Geo &g, const PjWork &w);
 hipError_t launch_pj_seed(hipStream_t s, const Geo &g, MRef b, MRef y, MRef z, const PjWork &w, int at, int user);
 hipError_t launch_pj_reseed(hipStream_t s, const Geo &g, MRef sm, const PjWork &w, int at, int user);
