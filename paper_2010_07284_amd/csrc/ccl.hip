@@ -34,17 +34,19 @@ namespace {
 
 constexpr uint32_t kLabNode = 0x8000u, kLabSeed = 0x4000u;
 
-// The words of a group of tiles, one per thread: 2*TBH pixel rows of SW words.
-template <int TBH>
+// A group of NR block rows: NR / TBH tiles side by side, 2*TBH pixel rows of SW
+// words, NW words in all.  A wave has 64 / NR lanes per row (segments).
+template <int TBH, int NR>
 struct Grp {
-    static constexpr int SUB = 64 / TBH;      // tiles side by side
+    static constexpr int SUB = NR / TBH;      // tiles side by side
+    static constexpr int SEG = 64 / NR;
     static constexpr int SW = 2 * SUB;        // words per pixel row
     static constexpr int PR = 2 * TBH;        // pixel rows
     static constexpr int SBP = SW + 1;        // LDS row strides in words (odd: no bank conflicts
     static constexpr int SAP = SW + 3;        // between the rows of one column)
     static constexpr int NA = (PR + 2) * (SW + 2);  // with a halo of one row and one word
-    static constexpr int NAI = (NA + kThreads - 1) / kThreads;
-    static_assert(PR * SW == kThreads, "one word per thread");
+    static constexpr int NW = PR * SW;
+    static_assert(NW == 4 * NR && NR >= TBH && NW <= kThreads, "at most one word per thread");
 };
 
 // A block row: its blocks' four pixels, and its runs.
@@ -80,17 +82,17 @@ struct RowMasks {
 // united from a queue.  Then every run finds its root, roots collect whether
 // they touch a shared border and whether they meet the seeds (bit sets per
 // row in LDS), and the runs' labels, the nodes and the border tables are
-// written.  NW waves, each for 64 / NW columns of every row.  Bound by chains
+// written.  NW waves, 64 / (NW * SEG) columns of a row per lane.  Bound by chains
 // of LDS round trips (of 20 k cycles at 1024^2 smoothed noise: staging 3 k,
 // unions 4 k, roots 4 k, border tables 2 k), on large images by VALU issue.
 // CANON (vlg_ccl_labels): also the smallest pixel of every component, at its
 // node (ncanon) or its root block (icanon).
-template <int TBH, int NW, bool CANON>
+template <int TBH, int NR, int NW, bool CANON>
 __device__ __forceinline__ void ccl_local_group(const Geo &g, const CclGeo &q, const CclArrays &a, const MRef &b,
                                                 const MRef &y, const MRef &z, bool multi, int gx, int ty,
                                                 const LoopGuard &gd, int32_t *ncanon_, int32_t *icanon_) {
-    using G = Grp<TBH>;
-    constexpr int NT = 64 * NW, CW = 64 / NW;          // threads; columns per wave
+    using G = Grp<TBH, NR>;
+    constexpr int NT = 64 * NW, CW = 64 / (NW * G::SEG);  // threads; columns per lane
     constexpr int NAI = (G::NA + NT - 1) / NT;
     __shared__ uint64_t sb[G::PR * G::SBP];
     __shared__ uint64_t sa[(G::PR + 2) * G::SAP];
@@ -109,7 +111,7 @@ __device__ __forceinline__ void ccl_local_group(const Geo &g, const CclGeo &q, c
     {
         const int p = tid / G::SW, w = tid % G::SW, row = r0 + p, word = wc0 + w;
         // all loads first, from clamped addresses, so that none waits for another
-        const bool in = tid < 256 && row < g.H && word < g.wpr;
+        const bool in = tid < G::NW && row < g.H && word < g.wpr;
         uint64_t v = b.p ? glb(b.p)[in ? (int64_t)row * g.wpr + word : 0] : 0ull;
         uint64_t s[NAI], t[NAI];
         bool sin[NAI];
@@ -125,12 +127,12 @@ __device__ __forceinline__ void ccl_local_group(const Geo &g, const CclGeo &q, c
         }
         if (tid < 256) (&sbits[0][0][0])[tid] = 0;
 #pragma unroll
-        for (int k = 0; k < 4096 / NT; k++) {
+        for (int k = 0; k < NR * 64 / NT; k++) {
             const int x = tid + k * NT;
             L[fat(x)] = x;
             if (CANON) smin[fat(x)] = 0x7fffffff;
         }
-        if (tid < 256) sb[p * G::SBP + w] = in ? (v ^ b.inv) & keep_of(g, word) : 0ull;
+        if (tid < G::NW) sb[p * G::SBP + w] = in ? (v ^ b.inv) & keep_of(g, word) : 0ull;
         if (seeds) {
 #pragma unroll
             for (int k = 0; k < NAI; k++) {
@@ -143,14 +145,15 @@ __device__ __forceinline__ void ccl_local_group(const Geo &g, const CclGeo &q, c
         }
     }
     __syncthreads();
-    const int sub = lane / TBH, rr = lane % TBH;
-    if (wave < 4) {
-        const int p = 2 * rr + (wave >> 1), w = 2 * sub + (wave & 1);
+    // this lane's row and its segment of the columns
+    const int lr = lane % NR, seg = lane / NR, sub = lr / TBH, rr = lr % TBH;
+    if (tid < G::NW) {
+        const int k = tid / NR, p = 2 * rr + (k >> 1), w = 2 * sub + (k & 1);
         const uint64_t bw = sb[p * G::SBP + w];
         uint32_t e, o;
         split_even_odd(bw, e, o);
-        rm.e[wave][lane] = e;
-        rm.o[wave][lane] = o;
+        rm.e[k][lr] = e;
+        rm.o[k][lr] = o;
         if (seeds) {
             uint64_t l = 0, c = 0, r = 0;
 #pragma unroll
@@ -161,15 +164,16 @@ __device__ __forceinline__ void ccl_local_group(const Geo &g, const CclGeo &q, c
                 r |= s[2];
             }
             const uint64_t n = (c | (c << 1) | (c >> 1) | (l >> 63) | (r << 63)) & bw;
-            sseed[wave][lane] = even_bits(n | (n >> 1));
+            sseed[k][lr] = even_bits(n | (n >> 1));
         }
     }
     __syncthreads();
 
-    // this lane's row (the same in every wave) and the row above it
-    const Row m = rm.row(lane);
+    // the row (the same in every wave) and the row above it
+    const Row m = rm.row(lr);
     const int tx = gx * G::SUB + sub, by = ty * TBH + rr, tile = ty * q.ntx + tx;
-    const uint64_t mine = (below(CW)) << (CW * wave);  // this wave's columns
+    const int c0 = CW * (wave * G::SEG + seg);  // this lane's columns
+    const uint64_t mine = below(CW) << c0;
     bool ok = true;
     {
         // (lane shifts outside any branch: every lane has to take part)
@@ -188,7 +192,7 @@ __device__ __forceinline__ void ccl_local_group(const Geo &g, const CclGeo &q, c
         auto first = [&](uint64_t x, int off) {
             for (; x; x &= x - 1) {
                 const int l = __builtin_ctzll(x);
-                L[fat(lane * 64 + run_of(m.starts, l))] = lane * 64 - 64 + run_of(us, l + off);
+                L[fat(lr * 64 + run_of(m.starts, l))] = lr * 64 - 64 + run_of(us, l + off);
             }
         };
         first(um & f, 0);
@@ -218,8 +222,8 @@ __device__ __forceinline__ void ccl_local_group(const Geo &g, const CclGeo &q, c
                     x &= x - 1;
                     const int at = n + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(act >> 32),
                                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)act, 0u));
-                    pairs[wave][at] = (lane * 64 + run_of(m.starts, l)) |
-                                      (lane * 64 - 64 + run_of(us, l + off)) << 16;
+                    pairs[wave][at] = (lr * 64 + run_of(m.starts, l)) |
+                                      (lr * 64 - 64 + run_of(us, l + off)) << 16;
                 }
                 n += __popcll(act);
                 if (n >= 64) take(64);
@@ -238,8 +242,8 @@ __device__ __forceinline__ void ccl_local_group(const Geo &g, const CclGeo &q, c
     if (tx > 0) bs |= m.starts & 1ull;
     if (tx < q.ntx - 1 && (m.fg() >> 63)) bs |= 1ull << run_of(m.starts, 63);
     if (seeds) {
-        const uint64_t s = (uint64_t)(sseed[0][lane] | sseed[2][lane]) |
-                           ((uint64_t)(sseed[1][lane] | sseed[3][lane]) << 32);
+        const uint64_t s = (uint64_t)(sseed[0][lr] | sseed[2][lr]) |
+                           ((uint64_t)(sseed[1][lr] | sseed[3][lr]) << 32);
         ss = starts_of(m.conn, s);
     }
     // Two runs at a time, so that their walks overlap; path halving through
@@ -252,8 +256,8 @@ __device__ __forceinline__ void ccl_local_group(const Geo &g, const CclGeo &q, c
         const int nr = st ? 2 : 1;
         s[1] = st ? __builtin_ctzll(st) : s[0];
         st &= st - 1;
-        x[0] = lane * 64 + s[0];
-        x[1] = lane * 64 + s[1];
+        x[0] = lr * 64 + s[0];
+        x[1] = lr * 64 + s[1];
         for (int it = 0;; it++) {
             const int p0 = lds_ld(&L[fat(x[0])]), p1 = lds_ld(&L[fat(x[1])]);
             if (p0 == x[0] && p1 == x[1]) break;
@@ -270,11 +274,11 @@ __device__ __forceinline__ void ccl_local_group(const Geo &g, const CclGeo &q, c
 #pragma unroll
         for (int j = 0; j < 2; j++) {
             if (j >= nr) break;
-            const int v = lane * 64 + s[j], xr = x[j] >> 6, xc = x[j] & 63;
+            const int v = lr * 64 + s[j], xr = x[j] >> 6, xc = x[j] & 63;
             if (x[j] != v) L[fat(v)] = x[j];
             if ((bs >> s[j]) & 1) atomicOr(&sbits[0][xr][xc >> 5], 1u << (xc & 31));
             if ((ss >> s[j]) & 1) atomicOr(&sbits[1][xr][xc >> 5], 1u << (xc & 31));
-            if (CANON && xr == lane) {
+            if (CANON && xr == lr) {
                 // the run's first pixel: in its top pixel row if it has one there
                 const uint64_t run = fill_up(m.conn, 1ull << s[j]), top = (m.t0 | m.t1) & run;
                 const int l = __builtin_ctzll(top ? top : (m.b0 | m.b1) & run);
@@ -286,7 +290,7 @@ __device__ __forceinline__ void ccl_local_group(const Geo &g, const CclGeo &q, c
     __syncthreads();
 
     // ranks of the nodes: prefix sums over the rows of each tile
-    const uint64_t nodes = (uint64_t)sbits[0][lane][0] | ((uint64_t)sbits[0][lane][1] << 32);
+    const uint64_t nodes = (uint64_t)sbits[0][lr][0] | ((uint64_t)sbits[0][lr][1] << 32);
     {
         const int cnt = __popcll(nodes);
         int sum = cnt;
@@ -295,15 +299,15 @@ __device__ __forceinline__ void ccl_local_group(const Geo &g, const CclGeo &q, c
             const int t = __shfl_up(sum, d);
             if (rr >= d) sum += t;
         }
-        spre[lane] = (uint32_t)(sum - cnt);  // (all waves write the same values)
-        if (wave == 0 && rr == TBH - 1 && tx < q.ntx) glb(a.cnt)[tile] = (uint32_t)sum;
+        spre[lr] = (uint32_t)(sum - cnt);  // (all waves write the same values)
+        if (wave == 0 && seg == 0 && rr == TBH - 1 && tx < q.ntx) glb(a.cnt)[tile] = (uint32_t)sum;
     }
     wave_lds_handoff();
     VLG_GLOBAL uint16_t *lab = glb(a.lab) + (int64_t)by * g.BW + tx * 64;
     const int node0 = tile * q.np + 1;
-    int k = __popcll(m.starts & below(CW * wave));
+    int k = __popcll(m.starts & below(c0));
     for (uint64_t st = m.starts & mine; st; st &= st - 1, k++) {
-        const int s = __builtin_ctzll(st), v = lane * 64 + s;
+        const int s = __builtin_ctzll(st), v = lr * 64 + s;
         const int x = L[fat(v)], xr = x >> 6, xc = x & 63;
         const uint64_t xn = (uint64_t)sbits[0][xr][0] | ((uint64_t)sbits[0][xr][1] << 32);
         uint32_t lb;
@@ -315,8 +319,8 @@ __device__ __forceinline__ void ccl_local_group(const Geo &g, const CclGeo &q, c
         // (a run whose bit is set is a root unless a walk gave up; its node is
         // set up in either case, so that every label names a valid node)
         if ((nodes >> s) & 1) {
-            const int id = node0 + (int)spre[lane] + __popcll(nodes & below(s));
-            const bool seeded = (sbits[1][lane][s >> 5] >> (s & 31)) & 1;
+            const int id = node0 + (int)spre[lr] + __popcll(nodes & below(s));
+            const bool seeded = (sbits[1][lr][s >> 5] >> (s & 31)) & 1;
             glb(a.par)[id] = seeded && !multi ? 0 : id;
             if (multi) glb(a.flag)[id] = seeded ? 2 : 0;
         }
@@ -324,7 +328,7 @@ __device__ __forceinline__ void ccl_local_group(const Geo &g, const CclGeo &q, c
             const int px = smin[fat(v)];
             const int64_t first = (int64_t)(2 * by + (px >> 7)) * g.W + tx * 128 + (px & 127);
             if ((nodes >> s) & 1)
-                glb(ncanon_)[node0 + (int)spre[lane] + __popcll(nodes & below(s))] = (int32_t)first;
+                glb(ncanon_)[node0 + (int)spre[lr] + __popcll(nodes & below(s))] = (int32_t)first;
             else
                 glb(icanon_)[(int64_t)by * g.BW + tx * 64 + s] = (int32_t)first;
         }
@@ -336,13 +340,13 @@ __device__ __forceinline__ void ccl_local_group(const Geo &g, const CclGeo &q, c
         // border tables: rank | block bits << 8, 0 for a background block
         VLG_GLOBAL uint16_t *per = glb(a.per);
         const int side0 = q.ud ? 2 * q.tw : 0;
-        if (wave < 2 && q.lr && tx < q.ntx && rr < q.th) {
+        if (wave < 2 && seg == 0 && q.lr && tx < q.ntx && rr < q.th) {
             const int l = wave ? 63 : 0;
             uint32_t e = 0;
             if ((m.fg() >> l) & 1) {
                 const uint32_t bits = (uint32_t)((m.t0 >> l) & 1) | (uint32_t)((m.t1 >> l) & 1) << 1 |
                                       (uint32_t)((m.b0 >> l) & 1) << 2 | (uint32_t)((m.b1 >> l) & 1) << 3;
-                e = (uint32_t)(L[fat(lane * 64 + run_of(m.starts, l))] & 0xFF) | bits << 8;
+                e = (uint32_t)(L[fat(lr * 64 + run_of(m.starts, l))] & 0xFF) | bits << 8;
             }
             per[(int64_t)tile * q.np + side0 + wave * q.th + rr] = (uint16_t)e;
         }
@@ -468,7 +472,7 @@ __device__ __forceinline__ void ccl_flag_tile(const CclGeo &q, const CclArrays &
 template <int TBH>
 __device__ __forceinline__ uint64_t stage_rows(const Geo &g, const MRef &x, int gx, int ty, int tid, uint64_t *sb,
                                                RowMasks &rm) {
-    using G = Grp<TBH>;
+    using G = Grp<TBH, 64>;
     const int p = tid / G::SW, w = tid % G::SW, row = ty * G::PR + p, word = gx * G::SW + w;
     uint64_t v = 0;
     if (row < g.H && word < g.wpr) v = ldm(x, (int64_t)row * g.wpr + word) & keep_of(g, word);
@@ -488,7 +492,7 @@ __device__ __forceinline__ uint64_t stage_rows(const Geo &g, const MRef &x, int 
 template <int TBH>
 __device__ __forceinline__ void ccl_reseed_group(const Geo &g, const CclGeo &q, const CclArrays &a, const MRef &b,
                                                  const MRef &sm, int user, int gx, int ty, const LoopGuard &gd) {
-    using G = Grp<TBH>;
+    using G = Grp<TBH, 64>;
     __shared__ uint64_t sb[G::PR * G::SBP];
     __shared__ RowMasks rm, rs;
     __shared__ uint32_t sin[64][2];        // seeded inner roots, by row
@@ -549,7 +553,7 @@ template <int TBH>
 __device__ __forceinline__ void ccl_gather_group(const Geo &g, const CclGeo &q, const CclArrays &a, const MRef &b,
                                                  const MRef &y, const MRef &z, int user, bool multi, uint64_t *out,
                                                  int gx, int ty, const LoopGuard &gd) {
-    using G = Grp<TBH>;
+    using G = Grp<TBH, 64>;
     __shared__ uint64_t sb[G::PR * G::SBP];
     __shared__ RowMasks rm;
     __shared__ uint32_t sin[64][2], sz[64][2];
@@ -622,22 +626,22 @@ __device__ __forceinline__ void ccl_gather_group(const Geo &g, const CclGeo &q, 
 }
 
 // ------------------------------------------------------------------ kernels
-__device__ __forceinline__ void group_at(const CclGeo &q, int i, int &gx, int &ty) {
-    const int n = ccl_groups_x(q);
+__device__ __forceinline__ void group_at(const CclGeo &q, int rows, int i, int &gx, int &ty) {
+    const int n = ccl_groups_x(q, rows);
     ty = i / n;
     gx = i - ty * n;
 }
 
 // blockIdx.y: the labelling; the groups go to the XCDs in contiguous ranges
 // (neighbouring groups share the cache lines of their mask rows)
-template <int TBH, int NW, bool CANON>
+template <int TBH, int NR, int NW, bool CANON>
 __global__ __launch_bounds__(64 * NW) void k_ccl_local(Geo g, CclMulti m, int32_t *ncanon, int32_t *icanon) {
     const CclOp &o = m.op[blockIdx.y];
     const CclGeo q = ccl_geo(g, TBH);
     int gx, ty;
-    group_at(q, xcd_contiguous((int)blockIdx.x, (int)gridDim.x), gx, ty);
+    group_at(q, NR, xcd_contiguous((int)blockIdx.x, (int)gridDim.x), gx, ty);
     if (CANON && blockIdx.x == 0 && threadIdx.x < 2 && m.counters) glb(m.counters)[threadIdx.x] = 0;
-    ccl_local_group<TBH, NW, CANON>(g, q, ccl_arrays(o.ws, g, q), o.b, o.y, o.z, o.multi, gx, ty, m.guard, ncanon, icanon);
+    ccl_local_group<TBH, NR, NW, CANON>(g, q, ccl_arrays(o.ws, g, q), o.b, o.y, o.z, o.multi, gx, ty, m.guard, ncanon, icanon);
 }
 
 __global__ __launch_bounds__(kThreads) void k_ccl_merge(Geo g, CclMulti m) {
@@ -667,7 +671,7 @@ __global__ __launch_bounds__(kThreads) void k_ccl_reseed(Geo g, CclMulti m) {
     const CclOp &o = m.op[blockIdx.y];
     const CclGeo q = ccl_geo(g, TBH);
     int gx, ty;
-    group_at(q, xcd_contiguous((int)blockIdx.x, (int)gridDim.x), gx, ty);
+    group_at(q, 64, xcd_contiguous((int)blockIdx.x, (int)gridDim.x), gx, ty);
     ccl_reseed_group<TBH>(g, q, ccl_arrays(o.ws, g, q), o.b, o.y, o.user, gx, ty, m.guard);
 }
 
@@ -676,7 +680,7 @@ __global__ __launch_bounds__(kThreads) void k_ccl_gather(Geo g, CclMulti m) {
     const CclOp &o = m.op[blockIdx.y];
     const CclGeo q = ccl_geo(g, TBH);
     int gx, ty;
-    group_at(q, xcd_contiguous((int)blockIdx.x, (int)gridDim.x), gx, ty);
+    group_at(q, 64, xcd_contiguous((int)blockIdx.x, (int)gridDim.x), gx, ty);
     ccl_gather_group<TBH>(g, q, ccl_arrays(o.ws, g, q), o.b, o.y, o.z, o.user, o.multi, o.out, gx, ty, m.guard);
 }
 
@@ -726,7 +730,7 @@ typedef int32_t lab2 __attribute__((ext_vector_type(2), aligned(4)));
 template <int TBH>
 __global__ __launch_bounds__(kThreads) void k_ccl_labels(Geo g, CclMulti m, const int32_t *ncanon_,
                                                          const int32_t *icanon_, int32_t *labels_) {
-    using G = Grp<TBH>;
+    using G = Grp<TBH, 64>;
     __shared__ uint64_t sb[G::PR * G::SBP];
     __shared__ RowMasks rm;
     __shared__ int V[kForest];
@@ -737,7 +741,7 @@ __global__ __launch_bounds__(kThreads) void k_ccl_labels(Geo g, CclMulti m, cons
     const VLG_GLOBAL int32_t *ncanon = glb(ncanon_), *icanon = glb(icanon_);
     VLG_GLOBAL int32_t *labels = glb(labels_);
     int gx, ty;
-    group_at(q, xcd_contiguous((int)blockIdx.x, (int)gridDim.x), gx, ty);
+    group_at(q, 64, xcd_contiguous((int)blockIdx.x, (int)gridDim.x), gx, ty);
     const int tid = (int)threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     stage_rows<TBH>(g, o.b, gx, ty, tid, sb, rm);
     bool ok = true;
@@ -792,8 +796,8 @@ __global__ __launch_bounds__(kThreads) void kb_ccl_local(BatchArgs a, BCcl o) {
         VLG_BATCH_IMG(a)
         const CclGeo q = ccl_geo(d.g, TBH);
         int gx, ty;
-        group_at(q, (int)(u_ - a.prefix[ii]), gx, ty);
-        ccl_local_group<TBH, 4, false>(d.g, q, ccl_arrays(d.ws + d.off_ccl, d.g, q), bref(d, o.b), bref(d, o.y),
+        group_at(q, 64, (int)(u_ - a.prefix[ii]), gx, ty);
+        ccl_local_group<TBH, 64, 4, false>(d.g, q, ccl_arrays(d.ws + d.off_ccl, d.g, q), bref(d, o.b), bref(d, o.y),
                                     bref(d, o.z), o.multi, gx, ty, a.guard, nullptr, nullptr);
         __syncthreads();  // the next group reuses the LDS
     }
@@ -829,7 +833,7 @@ __global__ __launch_bounds__(kThreads) void kb_ccl_reseed(BatchArgs a, BCcl o) {
         VLG_BATCH_IMG(a)
         const CclGeo q = ccl_geo(d.g, TBH);
         int gx, ty;
-        group_at(q, (int)(u_ - a.prefix[ii]), gx, ty);
+        group_at(q, 64, (int)(u_ - a.prefix[ii]), gx, ty);
         ccl_reseed_group<TBH>(d.g, q, ccl_arrays(d.ws + d.off_ccl, d.g, q), bref(d, o.b), bref(d, o.y), o.user, gx,
                               ty, a.guard);
         __syncthreads();
@@ -842,7 +846,7 @@ __global__ __launch_bounds__(kThreads) void kb_ccl_gather(BatchArgs a, BCcl o) {
         VLG_BATCH_IMG(a)
         const CclGeo q = ccl_geo(d.g, TBH);
         int gx, ty;
-        group_at(q, (int)(u_ - a.prefix[ii]), gx, ty);
+        group_at(q, 64, (int)(u_ - a.prefix[ii]), gx, ty);
         ccl_gather_group<TBH>(d.g, q, ccl_arrays(d.ws + d.off_ccl, d.g, q), bref(d, o.b), bref(d, o.y), bref(d, o.z),
                               o.user, o.multi, bptr(d, o.out), gx, ty, a.guard);
         __syncthreads();
@@ -858,19 +862,25 @@ __global__ __launch_bounds__(kThreads) void kb_ccl_gather(BatchArgs a, BCcl o) {
     }
 
 bool bad_multi(const CclMulti &m) { return m.n < 1 || m.n > kMaxMulti || !valid_tile_bh(m.tbh); }
-dim3 group_grid(const Geo &g, const CclMulti &m) {
+dim3 group_grid(const Geo &g, const CclMulti &m, int rows) {
     const CclGeo q = ccl_geo(g, m.tbh);
-    return dim3((unsigned)(ccl_groups_x(q) * q.nty), (unsigned)m.n);
+    return dim3((unsigned)(ccl_groups_x(q, rows) * q.nty), (unsigned)m.n);
 }
-// Waves per group of the local pass.  Up to two groups per compute unit the
-// pass waits on its own chain of LDS round trips, which more waves shorten by
-// sharing the columns; beyond that, the mask logic that every wave repeats
-// fills the VALUs.  8 against 4 waves: 9.5 against 10.2 us on smoothed noise
-// at 1024^2 (64 groups) and 16 against 20 us on coin noise, but 18.1 against
-// 15.7 us at 4096^2 (1024 groups).
-bool eight_waves(const Geo &g, const CclMulti &m) {
+// Block rows and waves per group of the local pass.  Up to two groups of 64
+// rows per compute unit the pass waits on its own chain of LDS round trips,
+// which more waves shorten by sharing the columns; beyond that, the mask logic
+// that every wave repeats fills the VALUs.  And while groups of 16 rows still
+// find a compute unit each (64 groups of 64), they take a quarter of the
+// columns per lane and a quarter of the unions per wave.  us, 64 rows and 4
+// waves / 64 and 8 / 16 and 8: smoothed noise at 1024^2 (64 groups of 64 rows)
+// 10.2 / 9.4 / 8.2, coin noise 20 / 16.0 / 10.1; at 1500^2 (141 groups)
+// - / 9.6 / 11.7 and - / 16.3 / 15.2; smoothed noise at 4096^2 (1024 groups)
+// 15.7 / 18.1 / -.  Tiles of 32 rows do not fit a group of 16.
+enum class Split { few, some, many };  // 16 rows, 8 waves; 64 rows, 8 waves; 64 rows, 4 waves
+Split local_split(const Geo &g, const CclMulti &m) {
     const CclGeo q = ccl_geo(g, m.tbh);
-    return (int64_t)ccl_groups_x(q) * q.nty * m.n <= 512;
+    const int64_t n = (int64_t)ccl_groups_x(q, 64) * q.nty * m.n;
+    return m.tbh <= 16 && n <= 64 ? Split::few : n <= 512 ? Split::some : Split::many;
 }
 // per: waves per tile
 dim3 tile_grid(const Geo &g, const CclMulti &m, int per) {
@@ -882,10 +892,14 @@ dim3 tile_grid(const Geo &g, const CclMulti &m, int per) {
 hipError_t launch_ccl_local(hipStream_t s, const Geo &g, const CclMulti &m) {
     if (g.nwords == 0 || m.n == 0) return hipSuccess;
     if (bad_multi(m)) return hipErrorInvalidValue;
-    const bool eight = eight_waves(g, m);
-#define K(T)                                                                                                      \
-    if (eight) k_ccl_local<T, 8, false><<<group_grid(g, m), 512, 0, s>>>(g, m, nullptr, nullptr);          \
-    else k_ccl_local<T, 4, false><<<group_grid(g, m), 256, 0, s>>>(g, m, nullptr, nullptr)
+    const Split sp = local_split(g, m);
+#define K(T)                                                                                             \
+    if (sp == Split::few)                                                                                \
+        k_ccl_local<T, T <= 16 ? 16 : 64, 8, false><<<group_grid(g, m, 16), 512, 0, s>>>(g, m, nullptr, nullptr); \
+    else if (sp == Split::some)                                                                          \
+        k_ccl_local<T, 64, 8, false><<<group_grid(g, m, 64), 512, 0, s>>>(g, m, nullptr, nullptr);       \
+    else                                                                                                 \
+        k_ccl_local<T, 64, 4, false><<<group_grid(g, m, 64), 256, 0, s>>>(g, m, nullptr, nullptr)
     VLG_BY_TBH(m.tbh, K)
 #undef K
     return hipGetLastError();
@@ -912,7 +926,7 @@ hipError_t launch_ccl_flag(hipStream_t s, const Geo &g, const CclMulti &m) {
 hipError_t launch_ccl_reseed(hipStream_t s, const Geo &g, const CclMulti &m) {
     if (g.nwords == 0 || m.n == 0) return hipSuccess;
     if (bad_multi(m)) return hipErrorInvalidValue;
-#define K(T) k_ccl_reseed<T><<<group_grid(g, m), kThreads, 0, s>>>(g, m)
+#define K(T) k_ccl_reseed<T><<<group_grid(g, m, 64), kThreads, 0, s>>>(g, m)
     VLG_BY_TBH(m.tbh, K)
 #undef K
     return hipGetLastError();
@@ -921,7 +935,7 @@ hipError_t launch_ccl_reseed(hipStream_t s, const Geo &g, const CclMulti &m) {
 hipError_t launch_ccl_gather(hipStream_t s, const Geo &g, const CclMulti &m) {
     if (g.nwords == 0 || m.n == 0) return hipSuccess;
     if (bad_multi(m)) return hipErrorInvalidValue;
-#define K(T) k_ccl_gather<T><<<group_grid(g, m), kThreads, 0, s>>>(g, m)
+#define K(T) k_ccl_gather<T><<<group_grid(g, m, 64), kThreads, 0, s>>>(g, m)
     VLG_BY_TBH(m.tbh, K)
 #undef K
     return hipGetLastError();
@@ -931,17 +945,21 @@ hipError_t launch_ccl_labels(hipStream_t s, const Geo &g, const CclMulti &m, int
                              int32_t *labels) {
     if (g.nwords == 0) return hipSuccess;
     if (bad_multi(m) || m.n != 1) return hipErrorInvalidValue;
-    const bool eight = eight_waves(g, m);
-#define K(T)                                                                                                      \
-    if (eight) k_ccl_local<T, 8, true><<<group_grid(g, m), 512, 0, s>>>(g, m, ncanon, icanon);             \
-    else k_ccl_local<T, 4, true><<<group_grid(g, m), 256, 0, s>>>(g, m, ncanon, icanon)
+    const Split sp = local_split(g, m);
+#define K(T)                                                                                             \
+    if (sp == Split::few)                                                                                \
+        k_ccl_local<T, T <= 16 ? 16 : 64, 8, true><<<group_grid(g, m, 16), 512, 0, s>>>(g, m, ncanon, icanon); \
+    else if (sp == Split::some)                                                                          \
+        k_ccl_local<T, 64, 8, true><<<group_grid(g, m, 64), 512, 0, s>>>(g, m, ncanon, icanon);          \
+    else                                                                                                 \
+        k_ccl_local<T, 64, 4, true><<<group_grid(g, m, 64), 256, 0, s>>>(g, m, ncanon, icanon)
     VLG_BY_TBH(m.tbh, K)
 #undef K
     if (ccl_geo(g, m.tbh).np > 0) {
         k_ccl_merge<<<tile_grid(g, m, 2), kThreads, 0, s>>>(g, m);
         k_ccl_canon<<<tile_grid(g, m, 1), kThreads, 0, s>>>(g, m, ncanon);
     }
-#define K(T) k_ccl_labels<T><<<group_grid(g, m), kThreads, 0, s>>>(g, m, ncanon, icanon, labels)
+#define K(T) k_ccl_labels<T><<<group_grid(g, m, 64), kThreads, 0, s>>>(g, m, ncanon, icanon, labels)
     VLG_BY_TBH(m.tbh, K)
 #undef K
     return hipGetLastError();

@@ -112,8 +112,9 @@ __host__ __device__ inline CclGeo ccl_geo(const Geo &g, int tbh) {
     q.sb = (q.tw + 7) / 8;
     return q;
 }
-// A workgroup of the tile passes takes 64 block rows: 64 / tbh tiles side by side.
-__host__ __device__ inline int ccl_groups_x(const CclGeo &q) { return (q.ntx * q.tbh + 63) / 64; }
+// A workgroup of the tile passes takes `rows` block rows (64, the local pass of a
+// small image 16): rows / tbh tiles side by side.
+__host__ __device__ inline int ccl_groups_x(const CclGeo &q, int rows) { return (q.ntx * q.tbh + rows - 1) / rows; }
 struct CclArrays {
     uint16_t *lab;
     int32_t *par;

@@ -763,7 +763,7 @@ int64_t batch_units(const Geo &g, int kind, int tbh) {
     case BK_WORDS: return (g.nwords + kThreads - 1) / kThreads;
     case BK_LOGIC: return (g.nwords + kThreads * kLogicUnroll - 1) / (kThreads * kLogicUnroll);
     case BK_NEAR: return (near_tasks(g, kBatchNearRows) + kThreads / 64 - 1) / (kThreads / 64);
-    case BK_TILES: return (int64_t)ccl_groups_x(q) * q.nty;
+    case BK_TILES: return (int64_t)ccl_groups_x(q, 64) * q.nty;
     case BK_MERGE: return (2 * ntiles + kThreads / 64 - 1) / (kThreads / 64);
     case BK_FLAG: return (ntiles + kThreads / 64 - 1) / (kThreads / 64);
     case BK_UNPACK: return (unpack_pieces(g) + kThreads * kUnpackPieces - 1) / (kThreads * kUnpackPieces);

@@ -82,3 +82,15 @@ def test_labels_of_narrow_images(ctx):
         lab = vlg.ccl_labels(ctx, torch.from_numpy(vlg.pack(m)).cuda(), h, w)
         vlg.sync(ctx)
         assert np.array_equal(lab.cpu().numpy(), oracle.ccl(m)), (h, w)
+
+
+@pytest.mark.parametrize("tbh", [8, 16])
+@pytest.mark.parametrize("h,w", [(1024, 1020), (1041, 1024), (1030, 1300)])
+def test_rows_per_group(ctx, tbh, h, w):
+    """Images on both sides of the line between groups of 16 and of 64 block rows."""
+    vlg.set_tunable(ctx, "ccl_tile_rows", tbh)
+    try:
+        img = image(h, w, "noise")
+        assert_same(SHARED, img, gpu_run(ctx, SHARED, img, "fused"), oracle.run(SHARED, img), tag=f"{h}x{w}")
+    finally:
+        vlg.set_tunable(ctx, "ccl_tile_rows", 0)
