@@ -330,7 +330,7 @@ constexpr int kSegMaxRegs = 16;
 constexpr int kSegMaxPtrs = 32;
 constexpr uint8_t kSegNone = 255;  // operand "no register": the all-zero mask
 enum SegOpcode : uint8_t { SEG_LOAD = 0, SEG_AND, SEG_OR, SEG_NEAR_AND, SEG_NEAR_OR, SEG_STORE };
-struct SegIns {
+struct alignas(8) SegIns {
     uint8_t op;
     uint8_t dst;  // register; SEG_STORE: pointer index
     uint8_t a;    // register (kSegNone: zero mask); SEG_LOAD: pointer index

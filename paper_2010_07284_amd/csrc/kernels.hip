@@ -401,21 +401,38 @@ __global__ __launch_bounds__(kThreads) void kb_unpack(BatchArgs a, uint8_t *cons
 #undef VLG_BATCH_IMG
 
 // ------------------------------------------------------------------ segments
+// Instruction k as one scalar load of eight bytes (byte by byte it would be
+// five vector loads, each waited for: most of a segment's time).
+__device__ __forceinline__ SegIns seg_ins(const SegProg &p, int k) {
+    uint64_t raw;
+    __builtin_memcpy(&raw, &p.ins[k], sizeof raw);
+    return SegIns{(uint8_t)raw, (uint8_t)(raw >> 8), (uint8_t)(raw >> 16), (uint8_t)(raw >> 24), (uint8_t)(raw >> 32)};
+}
+
 // Lane tiles: one wave (a workgroup of its own) per tile of one word column
 // and 64 rows, the halo above and below included; lane l takes row r0 + l of
-// every register as three words, the column and its two neighbours.  The
+// every register as 128 bits, the column's word and 32 bits on each side.  The
 // registers live in LDS, each lane reading and writing only its own entries,
 // so no instruction needs a barrier; N takes the rows above and below from
-// the adjacent lanes by DPP.  64 - 2 * halo rows are stored.  The neighbour
-// words lose one bit per N at their far edge and the edge lanes one row, all
-// within the halo.
+// the adjacent lanes by DPP.  64 - 2 * halo rows are stored.  The window
+// loses one bit per N at its ends and the edge lanes one row, all within the
+// halo (at most 24).  Bound by the issue of one wave's instructions and, at
+// 1024^2, half of the SIMDs without one: 9.3 us for a segment of 18 operators
+// and halo 16 with three words per row and byte-wise instructions, 7.6 now.
 //   LOAD    dst = ptr[a]
 //   AND/OR  dst = ((a ^ ia) OP (b ^ ib)) ^ io
 //   NEAR_*  dst = (N(a ^ ia) ^ io) OP (b ^ ib), N over the image's pixels only
 //           (operand words outside the image and padding bits are background)
 //   STORE   ptr[dst] = a ^ ia over the tile's centre (padding bits cleared)
+struct SegRow {  // bits -32 .. 95 of the column
+    uint32_t d[4];
+};
+__device__ __forceinline__ SegRow seg_row(uint64_t l, uint64_t c, uint64_t r) {
+    return SegRow{{(uint32_t)(l >> 32), (uint32_t)c, (uint32_t)(c >> 32), (uint32_t)r}};
+}
 __global__ __launch_bounds__(64) void k_segment_lane(Geo g, SegProg p, int nty) {
-    extern __shared__ uint64_t lreg[];  // [register][word l, c, r][lane]
+    typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+    extern __shared__ u4 lreg[];  // [register][lane]
     // each XCD takes a contiguous range of tiles, so the neighbour words and
     // halo rows that adjacent tiles load again come from that XCD's L2
     const int tile = xcd_contiguous((int)blockIdx.x, (int)gridDim.x);
@@ -423,69 +440,70 @@ __global__ __launch_bounds__(64) void k_segment_lane(Geo g, SegProg p, int nty) 
     const int tx = tile % g.wpr, ty = tile / g.wpr;
     const int row = ty * TR - p.halo + lane;
     const bool rin = row >= 0 && row < g.H;
-    // the image's pixels among the lane's three words (background elsewhere)
+    // the image's pixels in the window (background elsewhere)
     const uint64_t ml = rin && tx >= 1 ? ~0ull : 0ull;
     const uint64_t mc = rin ? (tx == g.wpr - 1 ? g.tail : ~0ull) : 0ull;
     const uint64_t mr = rin && tx + 1 < g.wpr ? (tx + 1 == g.wpr - 1 ? g.tail : ~0ull) : 0ull;
-    auto at = [&](int x, int w) -> uint64_t & { return lreg[(x * 3 + w) * 64 + lane]; };
+    const SegRow m = seg_row(ml, mc, mr);
+    auto put = [&](int x, const SegRow &v) { lreg[x * 64 + lane] = u4{v.d[0], v.d[1], v.d[2], v.d[3]}; };
+    auto get = [&](int x, uint32_t inv) {  // (kSegNone: the all-zero mask)
+        const u4 v = x != kSegNone ? lreg[x * 64 + lane] : u4{0u, 0u, 0u, 0u};
+        return SegRow{{v[0] ^ inv, v[1] ^ inv, v[2] ^ inv, v[3] ^ inv}};
+    };
     // the leading loads, all in flight together
     int nl = 0;
-    while (nl < p.nins && p.ins[nl].op == SEG_LOAD) nl++;
+    while (nl < p.nins && seg_ins(p, nl).op == SEG_LOAD) nl++;
     {
         const int64_t base = rin ? (int64_t)row * g.wpr + tx : 0;
-        uint64_t v[kSegMaxRegs][3];
+        SegRow v[kSegMaxRegs];
 #pragma unroll
         for (int j = 0; j < kSegMaxRegs; j++)
             if (j < nl) {
-                const VLG_GLOBAL uint64_t *src = glb(p.ptr[p.ins[j].a]);
-                v[j][0] = ml ? src[base - 1] : 0ull;
-                v[j][1] = rin ? src[base] : 0ull;
-                v[j][2] = mr ? src[base + 1] : 0ull;
+                const VLG_GLOBAL uint64_t *src = glb(p.ptr[seg_ins(p, j).a]);
+                v[j] = seg_row(ml ? src[base - 1] : 0ull, rin ? src[base] : 0ull, mr ? src[base + 1] : 0ull);
             }
 #pragma unroll
         for (int j = 0; j < kSegMaxRegs; j++)
-            if (j < nl)
-                for (int w = 0; w < 3; w++) at(p.ins[j].dst, w) = v[j][w];
+            if (j < nl) put(seg_ins(p, j).dst, v[j]);
     }
+    SegIns next = seg_ins(p, min(nl, kSegMaxIns - 1));
     for (int k = nl; k < p.nins; k++) {
-        const SegIns in = p.ins[k];
-        const uint64_t ia = (in.inv & 1) ? ~0ull : 0ull, ib = (in.inv & 2) ? ~0ull : 0ull,
-                       io = (in.inv & 4) ? ~0ull : 0ull;
-        const bool ha = in.a != kSegNone, hb = in.b != kSegNone;  // (kSegNone: the all-zero mask)
+        const SegIns in = next;
+        next = seg_ins(p, min(k + 1, kSegMaxIns - 1));
+        const uint32_t ia = (in.inv & 1) ? ~0u : 0u, ib = (in.inv & 2) ? ~0u : 0u, io = (in.inv & 4) ? ~0u : 0u;
+        const SegRow a = get(in.a, ia);
         if (in.op == SEG_STORE) {
             if (lane >= p.halo && lane < p.halo + TR && rin) {
-                const uint64_t v = (ha ? at(in.a, 1) : 0ull) ^ ia;
+                const uint64_t v = (uint64_t)a.d[1] | (uint64_t)a.d[2] << 32;
                 glb(p.ptr[in.dst])[(int64_t)row * g.wpr + tx] = tx == g.wpr - 1 ? (v & g.tail) : v;
             }
             continue;
         }
-        const uint64_t al = (ha ? at(in.a, 0) : 0ull) ^ ia, ac = (ha ? at(in.a, 1) : 0ull) ^ ia,
-                       ar = (ha ? at(in.a, 2) : 0ull) ^ ia;
-        const uint64_t bl = (hb ? at(in.b, 0) : 0ull) ^ ib, bc = (hb ? at(in.b, 1) : 0ull) ^ ib,
-                       br = (hb ? at(in.b, 2) : 0ull) ^ ib;
-        uint64_t dl, dc, dr;
+        const SegRow b = get(in.b, ib);
+        SegRow r;
         if (in.op == SEG_AND || in.op == SEG_OR) {
             const bool o = in.op == SEG_OR;
-            dl = (o ? (al | bl) : (al & bl)) ^ io;
-            dc = (o ? (ac | bc) : (ac & bc)) ^ io;
-            dr = (o ? (ar | br) : (ar & br)) ^ io;
+#pragma unroll
+            for (int w = 0; w < 4; w++) r.d[w] = (o ? a.d[w] | b.d[w] : a.d[w] & b.d[w]) ^ io;
         } else {
             // N over the image's pixels only
-            const uint64_t xl = al & ml, xc = ac & mc, xr = ar & mr;
-            const uint64_t hl = xl | (xl << 1) | (xl >> 1) | (xc << 63);
-            const uint64_t hc = xc | (xc << 1) | (xc >> 1) | (xl >> 63) | (xr << 63);
-            const uint64_t hr = xr | (xr << 1) | (xr >> 1) | (xc >> 63);
-            const uint64_t nl_ = (hl | lane_prev64(hl) | lane_next64(hl)) ^ io;
-            const uint64_t nc = (hc | lane_prev64(hc) | lane_next64(hc)) ^ io;
-            const uint64_t nr = (hr | lane_prev64(hr) | lane_next64(hr)) ^ io;
+            uint32_t x[4], n[4];
+#pragma unroll
+            for (int w = 0; w < 4; w++) x[w] = a.d[w] & m.d[w];
+#pragma unroll
+            for (int w = 0; w < 4; w++) {
+                const uint32_t lo = __builtin_amdgcn_alignbit(x[w], w > 0 ? x[w - 1] : 0u, 31),
+                               hi = __builtin_amdgcn_alignbit(w < 3 ? x[w + 1] : 0u, x[w], 1);
+                n[w] = x[w] | lo | hi;
+            }
+#pragma unroll
+            for (int w = 0; w < 4; w++)
+                n[w] = (n[w] | (uint32_t)lane_prev((int)n[w]) | (uint32_t)lane_next((int)n[w])) ^ io;
             const bool o = in.op == SEG_NEAR_OR;
-            dl = o ? (nl_ | bl) : (nl_ & bl);
-            dc = o ? (nc | bc) : (nc & bc);
-            dr = o ? (nr | br) : (nr & br);
+#pragma unroll
+            for (int w = 0; w < 4; w++) r.d[w] = o ? n[w] | b.d[w] : n[w] & b.d[w];
         }
-        at(in.dst, 0) = dl;
-        at(in.dst, 1) = dc;
-        at(in.dst, 2) = dr;
+        put(in.dst, r);
     }
 }
 
@@ -507,11 +525,11 @@ __global__ __launch_bounds__(kSegWideThreads) void k_segment_wide(Geo g, SegProg
     const bool win = w >= 0 && w < g.wpr;
     const uint64_t keep = w == g.wpr - 1 ? g.tail : ~0ull;
     int nl = 0;
-    while (nl < p.nins && p.ins[nl].op == SEG_LOAD) nl++;
+    while (nl < p.nins && seg_ins(p, nl).op == SEG_LOAD) nl++;
     // the leading loads: for each input, all of this thread's rows in flight
     for (int j = 0; j < nl; j++) {
-        const VLG_GLOBAL uint64_t *src = glb((const uint64_t *)p.ptr[p.ins[j].a]);
-        uint64_t *dst = sreg + p.ins[j].dst * NI;
+        const VLG_GLOBAL uint64_t *src = glb((const uint64_t *)p.ptr[seg_ins(p, j).a]);
+        uint64_t *dst = sreg + seg_ins(p, j).dst * NI;
         for (int rb = wave; rb < RR; rb += kSegWideWaves * 8) {
             uint64_t v[8];
 #pragma unroll
@@ -529,7 +547,7 @@ __global__ __launch_bounds__(kSegWideThreads) void k_segment_wide(Geo g, SegProg
     }
     __syncthreads();
     for (int k = nl; k < p.nins; k++) {
-        const SegIns in = p.ins[k];
+        const SegIns in = seg_ins(p, k);
         const uint64_t ia = (in.inv & 1) ? ~0ull : 0ull, ib = (in.inv & 2) ? ~0ull : 0ull,
                        io = (in.inv & 4) ? ~0ull : 0ull;
         const uint64_t *A = in.a != kSegNone ? sreg + in.a * NI : nullptr;
@@ -713,7 +731,7 @@ hipError_t launch_segment(hipStream_t s, const Geo &g, const SegProg &p) {
         // lane tiles: one wave per word column and 64 - 2 * halo rows
         if (p.halo > kLaneSegMaxHalo) return hipErrorInvalidValue;
         const int lnty = (g.H + (64 - 2 * p.halo) - 1) / (64 - 2 * p.halo);
-        const size_t lds = (size_t)p.nregs * 3 * 64 * 8;
+        const size_t lds = (size_t)p.nregs * 64 * 16;
         k_segment_lane<<<(int)((int64_t)g.wpr * lnty), 64, lds, s>>>(g, p, lnty);
     } else {
         if (t.lds_bytes > kSegWideLdsBudget) return hipErrorInvalidValue;
