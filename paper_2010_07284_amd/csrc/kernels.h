@@ -27,9 +27,9 @@ struct Geo {
 
 Geo make_geo(int H, int W);
 
-// near works on bands of rows 64 words wide.  For one image the band height
-// grows with the image (4 .. 32 rows) while at least 2048 bands remain to
-// fill the chip; a batch always has bands enough and uses kBatchNearRows.
+// near works on bands of rows, a lane per word column.  For one image the band
+// height grows with the image (4 .. 32 rows) while at least 2048 strips of 64
+// words remain to fill the chip; a batch always has bands enough and uses kBatchNearRows.
 __host__ __device__ inline int near_band_rows(const Geo &g) {
     const int64_t rows = (int64_t)g.H * ((g.wpr + 63) / 64);
     int R = 4;
@@ -43,9 +43,8 @@ constexpr int64_t kPctUnit = 65536;
 constexpr int kBatchGridDefault = 8192;
 inline bool valid_batch_grid(int n) { return n == 1024 || n == 2048 || n == 4096 || n == 8192; }
 __host__ __device__ inline int64_t near_tasks(const Geo &g, int R) {
-    return (int64_t)((g.H + R - 1) / R) * ((g.wpr + 63) / 64);
+    return ((int64_t)((g.H + R - 1) / R) * g.wpr + 63) / 64;  // waves
 }
-__host__ __device__ inline int64_t near_tasks(const Geo &g) { return near_tasks(g, near_band_rows(g)); }
 
 // Tile geometry of the reachability labelling: TBH x 64 blocks per tile
 // (2*TBH pixel rows x 128 pixel columns); TBH is tunable (8, 16 or 32).

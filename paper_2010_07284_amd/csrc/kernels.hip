@@ -58,17 +58,29 @@ __device__ __forceinline__ void logic_words(const Geo &g, const MRef &x, const M
 
 // ------------------------------------------------------------------ near
 // out = (N(x) ^ inv_out) OP z, OP = and (zop 0) / or (zop 1).  N over the
-// in-image 3x3 block, as a vertical sliding window: a wave owns 64
-// consecutive words of a band of rows and walks down it, loading every row
-// word once (the two edge lanes also load the word beyond the wave's edge),
-// taking the left and right neighbour words from the adjacent lanes, and
-// keeping the horizontally dilated rows y-1, y, y+1 in registers.  Each input
-// word is fetched once per band instead of three times (by the workgroups of
-// rows y-1, y, y+1, which sit on different XCDs with separate L2s).
+// in-image 3x3 block, as a vertical sliding window: a lane owns a word column
+// of a band of rows and walks down it, loading every row word once (the two
+// edge lanes also load the word beyond the wave's edge), taking the left and
+// right neighbour words from the adjacent lanes, and keeping the horizontally
+// dilated rows y-1, y, y+1 in registers.  Each input word is fetched once per
+// band instead of three times (by the workgroups of rows y-1, y, y+1, which
+// sit on different XCDs with separate L2s).  The word columns of all bands are
+// numbered in one sequence, 64 to a wave, so that the lanes of a wave are in
+// use whatever the width: with one strip of a single band per wave, a batch of 128
+// images of 128 to 2048 columns (2 to 32 words) took 46.5 us, 22.3 now.
 // Complemented inputs have their padding bits cleared first so nothing leaks
 // in from beyond the right border.
 // Loads are issued unconditionally from clamped addresses and masked
 // afterwards, so a chunk of CH rows has all its loads in flight at once.
+// the band and the word column of this lane in a wave's task
+__device__ __forceinline__ void near_column(const Geo &g, int64_t task, int R, int lane, bool &valid, int &band,
+                                            int &w) {
+    const uint32_t n = (uint32_t)((g.H + R - 1) / R) * (uint32_t)g.wpr, t = (uint32_t)task * 64u + (uint32_t)lane;
+    valid = t < n;
+    const uint32_t c = valid ? t : n - 1;
+    band = (int)fdiv(c, g.wpr_mul, g.wpr_shift);
+    w = (int)(c - (uint32_t)band * (uint32_t)g.wpr);
+}
 template <int CH, bool HZ>
 __device__ __forceinline__ void near_band(const Geo &g, const uint64_t *__restrict__ xg, uint64_t xinv,
                                           uint64_t inv_out, const uint64_t *__restrict__ zg, uint64_t zinv, int zop,
@@ -76,16 +88,15 @@ __device__ __forceinline__ void near_band(const Geo &g, const uint64_t *__restri
     const VLG_GLOBAL uint64_t *xp = glb(xg), *zp = glb(zg);
     VLG_GLOBAL uint64_t *out = glb(outg);
     const int lane = lane_id();
-    const int nstrips = (g.wpr + 63) >> 6;
-    const int64_t band = task / nstrips;
-    const int w = (int)(task - band * nstrips) * 64 + lane;
-    const bool valid = w < g.wpr, last = w == g.wpr - 1;
-    const int wc = valid ? w : g.wpr - 1;
-    const int nb = lane == 0 ? w - 1 : (lane == 63 ? w + 1 : -1);  // word beyond the wave's edge
-    const bool nbv = nb >= 0 && nb < g.wpr;
+    bool valid;
+    int band, wc;
+    near_column(g, task, R, lane, valid, band, wc);
+    const bool last = wc == g.wpr - 1;
+    const int nb = lane == 0 ? wc - 1 : (lane == 63 ? wc + 1 : -1);  // word beyond the wave's edge
+    const bool nbv = valid && nb >= 0 && nb < g.wpr;
     const int nbc = nbv ? nb : wc;
     const uint64_t keep = last ? g.tail : ~0ull;
-    const int y0 = (int)band * R, y1 = min(y0 + R, g.H);
+    const int y0 = band * R, y1 = min(y0 + R, g.H);
     // raw loads of row y (clamped into the image) and their masking; the empty
     // asm consumes every raw value of a chunk after all its loads are issued,
     // which keeps the compiler from sinking a load into a conditional block
@@ -95,9 +106,11 @@ __device__ __forceinline__ void near_band(const Geo &g, const uint64_t *__restri
         return (y >= 0 && y <= lim && valid) ? ((raw ^ xinv) & keep) : 0ull;
     };
     auto mask_e = [&](int y, int lim, uint64_t raw) { return (y >= 0 && y <= lim && nbv) ? (raw ^ xinv) : 0ull; };
-    // horizontal dilation of one row: lanes beyond the row hold c = 0
+    // horizontal dilation of one row: the lanes beside may be of other bands
+    // (all lanes take part)
+    const uint64_t kl = wc > 0 ? ~0ull : 0ull, kr = last ? 0ull : ~0ull;
     auto hrow = [&](uint64_t c, uint64_t e) {
-        uint64_t l = __shfl_up(c, 1), r = __shfl_down(c, 1);
+        uint64_t l = lane_prev64(c) & kl, r = lane_next64(c) & kr;
         if (lane == 0) l = e;
         if (lane == 63) r = e;
         return c | (c << 1) | (c >> 1) | (l >> 63) | (r << 63);
@@ -111,7 +124,7 @@ __device__ __forceinline__ void near_band(const Geo &g, const uint64_t *__restri
         h0 = hrow(mask_c(y0, g.H - 1, rc1), mask_e(y0, g.H - 1, re1));
     }
     const int lim = min(y1, g.H - 1);
-    for (int yb = y0; yb < y1; yb += CH) {
+    for (int yb = y0; __any(yb < y1); yb += CH) {
         uint64_t c[CH], e[CH], zz[CH];
 #pragma unroll
         for (int k = 0; k < CH; k++) {
@@ -131,7 +144,7 @@ __device__ __forceinline__ void near_band(const Geo &g, const uint64_t *__restri
             const uint64_t n = (hm | h0 | hp) ^ inv_out;
             const uint64_t zv = HZ ? (zz[k] ^ zinv) : zinv;
             const uint64_t res = (zop ? (n | zv) : (n & zv)) & keep;
-            if (valid && yb + k < y1) out[(int64_t)(yb + k) * g.wpr + w] = res;
+            if (valid && yb + k < y1) out[(int64_t)(yb + k) * g.wpr + wc] = res;
             hm = h0;
             h0 = hp;
         }
@@ -141,12 +154,12 @@ __device__ __forceinline__ void near_band(const Geo &g, const uint64_t *__restri
 // N of a constant mask (x.p == nullptr) is that constant over the image.
 __device__ __forceinline__ void near_const_band(Geo g, uint64_t xinv, uint64_t inv_out, MRef z, int zop, uint64_t *out,
                                              int64_t task, int R) {
-    const int nstrips = (g.wpr + 63) >> 6;
-    const int64_t band = task / nstrips;
-    const int w = (int)(task - band * nstrips) * 64 + lane_id();
-    if (w >= g.wpr) return;
+    bool valid;
+    int band, w;
+    near_column(g, task, R, lane_id(), valid, band, w);
+    if (!valid) return;
     const uint64_t keep = w == g.wpr - 1 ? g.tail : ~0ull;
-    const int y0 = (int)band * R, y1 = min(y0 + R, g.H);
+    const int y0 = band * R, y1 = min(y0 + R, g.H);
     for (int y = y0; y < y1; y++) {
         const int64_t i = (int64_t)y * g.wpr + w;
         const uint64_t n = xinv ^ inv_out, zz = ldm(z, i);
@@ -154,7 +167,7 @@ __device__ __forceinline__ void near_const_band(Geo g, uint64_t xinv, uint64_t i
     }
 }
 
-// band `task` of height R (4, 8, 16 or 32 rows)
+// 64 word columns of bands of R (4, 8, 16 or 32) rows
 __device__ __forceinline__ void near_task(const Geo &g, const MRef &x, uint64_t inv_out, const MRef &z, int zop,
                                           uint64_t *out, int64_t task, int R) {
     if (!x.p) near_const_band(g, x.inv, inv_out, z, zop, out, task, R);
