@@ -127,10 +127,11 @@ __device__ __forceinline__ void ccl_local_group(const Geo &g, const CclGeo &q, c
         }
         if (tid < 256) (&sbits[0][0][0])[tid] = 0;
 #pragma unroll
-        for (int k = 0; k < NR * 64 / NT; k++) {
+        for (int k = 0; k < (NR * kRowStep + NT - 1) / NT; k++) {
             const int x = tid + k * NT;
-            L[fat(x)] = x;
-            if (CANON) smin[fat(x)] = 0x7fffffff;
+            if (x >= NR * kRowStep) break;
+            L[x] = x;
+            if (CANON) smin[x] = 0x7fffffff;
         }
         if (tid < G::NW) sb[p * G::SBP + w] = in ? (v ^ b.inv) & keep_of(g, word) : 0ull;
         if (seeds) {
@@ -173,7 +174,9 @@ __device__ __forceinline__ void ccl_local_group(const Geo &g, const CclGeo &q, c
     const Row m = rm.row(lr);
     const int tx = gx * G::SUB + sub, by = ty * TBH + rr, tile = ty * q.ntx + tx;
     const int c0 = CW * (wave * G::SEG + seg);  // this lane's columns
-    const uint64_t mine = below(CW) << c0;
+    const Window<CW> win{c0};
+    const int row0 = lr * kRowStep;
+    const RunStarts sm = run_starts(win, m.starts);
     bool ok = true;
     {
         // (lane shifts outside any branch: every lane has to take part)
@@ -181,26 +184,26 @@ __device__ __forceinline__ void ccl_local_group(const Geo &g, const CclGeo &q, c
                        us = lane_prev64(m.starts);
         const uint64_t ub0 = rr ? p0 : 0ull, ub1 = rr ? p1 : 0ull;
         const uint64_t u = (m.t0 | m.t1) & (ub0 | ub1), ul = m.t0 & (ub1 << 1), ur = m.t1 & (ub0 >> 1);
-        uint64_t um = u & ~(m.conn & ((uc & (u << 1)) | (ur << 1)));
-        uint64_t lm = ul & ~((u & uc) | (m.conn & (u << 1)));
-        uint64_t rm_ = ur & ~(u & (uc >> 1));
+        const uint64_t um64 = u & ~(m.conn & ((uc & (u << 1)) | (ur << 1)));
+        const uint64_t lm64 = ul & ~((u & uc) | (m.conn & (u << 1)));
+        const uint64_t rm64 = ur & ~(u & (uc >> 1));
         // A run's first contact makes the touched run its parent at once (no
         // one else writes its entry before the barrier); only the others are
         // unions.
-        const uint64_t all = um | lm | rm_;
-        const uint64_t f = all & ~(m.conn & (fill_up(m.conn, all) << 1)) & mine;
-        auto first = [&](uint64_t x, int off) {
-            for (; x; x &= x - 1) {
-                const int l = __builtin_ctzll(x);
-                L[fat(lr * 64 + run_of(m.starts, l))] = lr * 64 - 64 + run_of(us, l + off);
-            }
-        };
-        first(um & f, 0);
-        first(lm & f & ~um, -1);
-        first(rm_ & f & ~(um | lm), 1);
-        rm_ &= mine & ~(f & ~(um | lm));
-        lm &= mine & ~(f & ~um);
-        um &= mine & ~f;
+        const uint64_t all = um64 | lm64 | rm64;
+        const uint32_t f = win.own(all & ~(m.conn & (fill_up(m.conn, all) << 1)));
+        const RunStarts su = run_starts(win, us);
+        // this row's run at window bit i, the upper row's at bit i
+        auto here = [&](int i) { return row0 + sm(c0 - 1, i); };
+        auto above = [&](int i) { return row0 - kRowStep + su(c0 - 1, i); };
+        uint32_t um = win.own(um64), lm = win.own(lm64), rm_ = win.own(rm64);
+        for (uint32_t x = f; x; x &= x - 1) {
+            const int i = __builtin_ctz(x);
+            L[here(i)] = above(i + ((um >> i) & 1 ? 0 : (lm >> i) & 1 ? -1 : 1));
+        }
+        rm_ &= ~(f & ~(um | lm));
+        lm &= ~(f & ~um);
+        um &= ~f;
         __syncthreads();
         // The pairs go through a queue, so that a row with many of them does
         // not hold up the wave: every round appends at most one pair per
@@ -215,23 +218,23 @@ __device__ __forceinline__ void ccl_local_group(const Geo &g, const CclGeo &q, c
             }
             wave_lds_handoff();
         };
-        auto list = [&](uint64_t x, int off) {  // contacts of block l with block l + off of the row above
-            for (uint64_t act = __ballot(x != 0); act; act = __ballot(x != 0)) {
-                if (x) {
-                    const int l = __builtin_ctzll(x);
-                    x &= x - 1;
-                    const int at = n + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(act >> 32),
-                                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)act, 0u));
-                    pairs[wave][at] = (lr * 64 + run_of(m.starts, l)) |
-                                      (lr * 64 - 64 + run_of(us, l + off)) << 16;
-                }
-                n += __popcll(act);
-                if (n >= 64) take(64);
+        for (;;) {
+            const uint32_t x = um | lm | rm_;
+            const uint64_t act = __ballot(x != 0);
+            if (!act) break;
+            if (x) {
+                const int i = __builtin_ctz(x);
+                const uint32_t bit = x & (0u - x), isu = um & bit, isl = isu | (lm & bit);
+                const int at = n + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(act >> 32),
+                                                                 __builtin_amdgcn_mbcnt_lo((uint32_t)act, 0u));
+                pairs[wave][at] = here(i) | above(i + (isu ? 0 : isl ? -1 : 1)) << 16;
+                um &= ~bit;
+                if (!isu) lm &= ~bit;
+                if (!isl) rm_ &= ~bit;
             }
-        };
-        list(um, 0);
-        list(lm, -1);
-        list(rm_, 1);
+            n += __popcll(act);
+            if (n >= 64) take(64);
+        }
         if (n > 0) take(n);
     }
     __syncthreads();
@@ -249,41 +252,42 @@ __device__ __forceinline__ void ccl_local_group(const Geo &g, const CclGeo &q, c
     // Two runs at a time, so that their walks overlap; path halving through
     // atomicMin: a stale store never replaces a root that a run's own lane
     // has written.
-    for (uint64_t st = m.starts & mine; st;) {
+    const uint32_t bsw = win.of(bs), ssw = win.of(ss);
+    for (uint32_t st = sm.w & win.kOwn; st;) {
         int s[2], x[2];
-        s[0] = __builtin_ctzll(st);
+        s[0] = __builtin_ctz(st);
         st &= st - 1;
         const int nr = st ? 2 : 1;
-        s[1] = st ? __builtin_ctzll(st) : s[0];
+        s[1] = st ? __builtin_ctz(st) : s[0];
         st &= st - 1;
-        x[0] = lr * 64 + s[0];
-        x[1] = lr * 64 + s[1];
+        x[0] = row0 + win.col(s[0]);
+        x[1] = row0 + win.col(s[1]);
         for (int it = 0;; it++) {
-            const int p0 = lds_ld(&L[fat(x[0])]), p1 = lds_ld(&L[fat(x[1])]);
+            const int p0 = lds_ld(&L[x[0]]), p1 = lds_ld(&L[x[1]]);
             if (p0 == x[0] && p1 == x[1]) break;
             if (it >= gd.cap) {
                 ok = false;
                 break;
             }
-            const int g0 = lds_ld(&L[fat(p0)]), g1 = lds_ld(&L[fat(p1)]);
-            if (g0 != p0) atomicMin(&L[fat(x[0])], g0);
-            if (g1 != p1) atomicMin(&L[fat(x[1])], g1);
+            const int g0 = lds_ld(&L[p0]), g1 = lds_ld(&L[p1]);
+            if (g0 != p0) atomicMin(&L[x[0]], g0);
+            if (g1 != p1) atomicMin(&L[x[1]], g1);
             x[0] = g0;
             x[1] = g1;
         }
 #pragma unroll
         for (int j = 0; j < 2; j++) {
             if (j >= nr) break;
-            const int v = lr * 64 + s[j], xr = x[j] >> 6, xc = x[j] & 63;
-            if (x[j] != v) L[fat(v)] = x[j];
-            if ((bs >> s[j]) & 1) atomicOr(&sbits[0][xr][xc >> 5], 1u << (xc & 31));
-            if ((ss >> s[j]) & 1) atomicOr(&sbits[1][xr][xc >> 5], 1u << (xc & 31));
+            const int v = row0 + win.col(s[j]), xr = forest_row(x[j]), xc = x[j] - xr * kRowStep;
+            if (x[j] != v) L[v] = x[j];
+            if ((bsw >> s[j]) & 1) atomicOr(&sbits[0][xr][xc >> 5], 1u << (xc & 31));
+            if ((ssw >> s[j]) & 1) atomicOr(&sbits[1][xr][xc >> 5], 1u << (xc & 31));
             if (CANON && xr == lr) {
                 // the run's first pixel: in its top pixel row if it has one there
-                const uint64_t run = fill_up(m.conn, 1ull << s[j]), top = (m.t0 | m.t1) & run;
+                const uint64_t run = fill_up(m.conn, 1ull << win.col(s[j])), top = (m.t0 | m.t1) & run;
                 const int l = __builtin_ctzll(top ? top : (m.b0 | m.b1) & run);
                 const int col = 2 * l + ((((top ? m.t0 : m.b0) >> l) & 1) ? 0 : 1);
-                atomicMin(&smin[fat(x[j])], (top ? 0 : 128) + col);
+                atomicMin(&smin[x[j]], (top ? 0 : 128) + col);
             }
         }
     }
@@ -306,9 +310,9 @@ __device__ __forceinline__ void ccl_local_group(const Geo &g, const CclGeo &q, c
     VLG_GLOBAL uint16_t *lab = glb(a.lab) + (int64_t)by * g.BW + tx * 64;
     const int node0 = tile * q.np + 1;
     int k = __popcll(m.starts & below(c0));
-    for (uint64_t st = m.starts & mine; st; st &= st - 1, k++) {
-        const int s = __builtin_ctzll(st), v = lr * 64 + s;
-        const int x = L[fat(v)], xr = x >> 6, xc = x & 63;
+    for (uint32_t st = sm.w & win.kOwn; st; st &= st - 1, k++) {
+        const int s = win.col(__builtin_ctz(st)), v = row0 + s;
+        const int x = L[v], xr = forest_row(x), xc = x - xr * kRowStep;
         const uint64_t xn = (uint64_t)sbits[0][xr][0] | ((uint64_t)sbits[0][xr][1] << 32);
         uint32_t lb;
         if ((xn >> xc) & 1)
@@ -325,14 +329,14 @@ __device__ __forceinline__ void ccl_local_group(const Geo &g, const CclGeo &q, c
             if (multi) glb(a.flag)[id] = seeded ? 2 : 0;
         }
         if (CANON && x == v) {
-            const int px = smin[fat(v)];
+            const int px = smin[v];
             const int64_t first = (int64_t)(2 * by + (px >> 7)) * g.W + tx * 128 + (px & 127);
             if ((nodes >> s) & 1)
                 glb(ncanon_)[node0 + (int)spre[lr] + __popcll(nodes & below(s))] = (int32_t)first;
             else
                 glb(icanon_)[(int64_t)by * g.BW + tx * 64 + s] = (int32_t)first;
         }
-        L[fat(v)] = (int)lb;
+        L[v] = (int)lb;
     }
     if (gx == 0 && ty == 0 && tid == 0) glb(a.par)[0] = 0;
     if (q.np > 0) {
@@ -346,7 +350,7 @@ __device__ __forceinline__ void ccl_local_group(const Geo &g, const CclGeo &q, c
             if ((m.fg() >> l) & 1) {
                 const uint32_t bits = (uint32_t)((m.t0 >> l) & 1) | (uint32_t)((m.t1 >> l) & 1) << 1 |
                                       (uint32_t)((m.b0 >> l) & 1) << 2 | (uint32_t)((m.b1 >> l) & 1) << 3;
-                e = (uint32_t)(L[fat(lr * 64 + run_of(m.starts, l))] & 0xFF) | bits << 8;
+                e = (uint32_t)(L[row0 + run_of(m.starts, l)] & 0xFF) | bits << 8;
             }
             per[(int64_t)tile * q.np + side0 + wave * q.th + rr] = (uint16_t)e;
         }
@@ -358,7 +362,7 @@ __device__ __forceinline__ void ccl_local_group(const Geo &g, const CclGeo &q, c
                 const int jx = gx * G::SUB + (j >> 1), R = (j >> 1) * TBH + (bottom ? TBH - 1 : 0);
                 const uint32_t bits = ((rm.e[h][R] >> l) & 1) | ((rm.o[h][R] >> l) & 1) << 1 |
                                       ((rm.e[2 + h][R] >> l) & 1) << 2 | ((rm.o[2 + h][R] >> l) & 1) << 3;
-                const int lb = L[fat(R * 64 + run_of(read_lane64(m.starts, R), lane))];
+                const int lb = L[R * kRowStep + run_of(read_lane64(m.starts, R), lane)];
                 if (lane < q.tw && jx < q.ntx && (bottom ? ty < q.nty - 1 : ty > 0))
                     per[(int64_t)(ty * q.ntx + jx) * q.np + bottom * q.tw + lane] =
                         (uint16_t)(bits ? (uint32_t)(lb & 0xFF) | bits << 8 : 0u);

@@ -66,10 +66,39 @@ __device__ __forceinline__ uint64_t starts_of(uint64_t conn, uint64_t s) {
     return __builtin_bitreverse64(((c + (r & c)) | r) & ~c);
 }
 
-// LDS forest of a group: entry v = row * 64 + start column, one extra slot per
-// row so that the rows' entries of one column lie in different banks.
-__device__ __forceinline__ int fat(int v) { return v + (v >> 6); }
+// LDS forest of a group: entry v = row * 65 + start column (one extra slot per
+// row so that the rows' entries of one column lie in different banks).
+constexpr int kRowStep = 65;
+__device__ __forceinline__ int forest_row(int v) { return (int)(((uint32_t)v * 4033u) >> 18); }  // v / 65, v < 64 * 65
 constexpr int kForest = 64 * 65;
+
+// A lane's CW columns c0 .. c0 + CW - 1 of a row, and one more on each side, as a
+// 32-bit window: bit i is column c0 - 1 + i.  The loops over runs and contacts
+// work on windows, in half the instructions of 64-bit masks.
+template <int CW>
+struct Window {
+    static_assert(CW <= 16, "a window has 32 bits");
+    static constexpr uint32_t kOwn = ((1u << CW) - 1u) << 1;
+    int c0;
+    __device__ __forceinline__ uint32_t of(uint64_t x) const {
+        return (c0 > 0 ? (uint32_t)(x >> (c0 - 1)) : (uint32_t)x << 1) & ((1u << (CW + 2)) - 1u);
+    }
+    __device__ __forceinline__ uint32_t own(uint64_t x) const { return of(x) & kOwn; }
+    __device__ __forceinline__ int col(int i) const { return c0 - 1 + i; }
+};
+// Start columns of the runs of a row by window bit.
+struct RunStarts {
+    uint32_t w;
+    int in;  // start of a run that reaches the window from the left
+    __device__ __forceinline__ int operator()(int first_col, int i) const {
+        const uint32_t t = w & ((2u << i) - 1u);
+        return t ? first_col + 31 - __builtin_clz(t) : in;
+    }
+};
+template <int CW>
+__device__ __forceinline__ RunStarts run_starts(const Window<CW> &win, uint64_t starts) {
+    return RunStarts{win.of(starts), run_of(starts, max(win.c0 - 1, 0))};
+}
 
 __device__ __forceinline__ uint64_t keep_of(const Geo &g, int word) { return word == g.wpr - 1 ? g.tail : ~0ull; }
 
@@ -98,22 +127,22 @@ __device__ __forceinline__ int node_root(const VLG_GLOBAL int32_t *par, int id, 
 __device__ __forceinline__ bool lds_unite(int *L, int a, int b, int cap) {
     for (int it = 0; a != b; it++) {
         if (it >= cap) return false;
-        const int pa = lds_ld(&L[fat(a)]), pb = lds_ld(&L[fat(b)]);
+        const int pa = lds_ld(&L[a]), pb = lds_ld(&L[b]);
         if (pa == a && pb == b) {
             const int hi = a > b ? a : b, lo = a > b ? b : a;
-            const int old = atomicMin(&L[fat(hi)], lo);
+            const int old = atomicMin(&L[hi], lo);
             if (old == hi) return true;
             a = old;
             b = lo;
             continue;
         }
-        const int ga = pa != a ? lds_ld(&L[fat(pa)]) : pa, gb = pb != b ? lds_ld(&L[fat(pb)]) : pb;
+        const int ga = pa != a ? lds_ld(&L[pa]) : pa, gb = pb != b ? lds_ld(&L[pb]) : pb;
         if (pa != a) {
-            if (ga != pa) L[fat(a)] = ga;
+            if (ga != pa) L[a] = ga;
             a = ga;
         }
         if (pb != b) {
-            if (gb != pb) L[fat(b)] = gb;
+            if (gb != pb) L[b] = gb;
             b = gb;
         }
     }

@@ -233,9 +233,9 @@ __global__ __launch_bounds__(kV3Threads) void k_v3_local(Geo g, VlGeo q, MRef b,
         if (seeds) vl_stage_seeds(g, q, t, y, z, tid, sa);
         sb[(w.z * 16 + w.y) * 3 + w.half] = v;
 #pragma unroll
-        for (int k = 0; k < 4096 / kV3Threads; k++) {
+        for (int k = 0; k < (kForest + kV3Threads - 1) / kV3Threads; k++) {
             const int x = tid + k * kV3Threads;
-            L[fat(x)] = x;
+            if (x < kForest) L[x] = x;
         }
         if (tid < 128) (&sbits[0][0])[tid] = 0;
     }
@@ -252,9 +252,12 @@ __global__ __launch_bounds__(kV3Threads) void k_v3_local(Geo g, VlGeo q, MRef b,
     }
     __syncthreads();
     const int lz = lane >> 3, ly = lane & 7, bz = t.tz * 8 + lz, by = t.ty * 8 + ly;
-    const uint64_t mine = below(CW) << (CW * wave);
-    VContacts ct[kRel];
-    uint64_t us[kRel];
+    const Window<CW> win{CW * wave};
+    const int row0 = lane * kRowStep, c0 = win.c0;
+    const RunStarts sm = run_starts(win, m.starts);
+    auto here = [&](int i) { return row0 + sm(c0 - 1, i); };  // this row's run at window bit i
+    uint32_t um[kRel], lm[kRel], rm[kRel];
+    RunStarts us[kRel];
     uint64_t has = 0;  // blocks of the runs that have a parent
 #pragma unroll
     for (int r = 0; r < kRel; r++) {
@@ -264,21 +267,22 @@ __global__ __launch_bounds__(kV3Threads) void k_v3_local(Geo g, VlGeo q, MRef b,
                        a1 = vl_or(kRelMine[r], [&](int k) { return m.o[k]; });
         const uint64_t b0 = in ? vl_or(kRelTheirs[r], [&](int k) { return vm.even(k, nl); }) : 0ull,
                        b1 = in ? vl_or(kRelTheirs[r], [&](int k) { return vm.odd(k, nl); }) : 0ull;
-        us[r] = sstart[nl];
-        VContacts c = vl_contacts(m.conn, a0, a1, b0, b1, sconn[nl]);
+        us[r] = run_starts(win, sstart[nl]);
+        const VContacts c = vl_contacts(m.conn, a0, a1, b0, b1, sconn[nl]);
         // the first contact of a run becomes its parent without a union
-        const uint64_t all = c.um | c.lm | c.rm, f = all & ~(m.conn & (fill_up(m.conn, all) << 1)) & ~has & mine;
+        const uint64_t all = c.um | c.lm | c.rm;
+        const uint32_t f = win.own(all & ~(m.conn & (fill_up(m.conn, all) << 1)) & ~has);
         has |= fill_up(m.conn, starts_of(m.conn, all));
-        auto first = [&](uint64_t x, int off) {
-            for (; x; x &= x - 1) {
-                const int l = __builtin_ctzll(x);
-                L[fat(lane * 64 + run_of(m.starts, l))] = nl * 64 + run_of(us[r], l + off);
-            }
-        };
-        first(c.um & f, 0);
-        first(c.lm & f & ~c.um, -1);
-        first(c.rm & f & ~(c.um | c.lm), 1);
-        ct[r] = VContacts{c.um & mine & ~f, c.lm & mine & ~(f & ~c.um), c.rm & mine & ~(f & ~(c.um | c.lm))};
+        um[r] = win.own(c.um);
+        lm[r] = win.own(c.lm);
+        rm[r] = win.own(c.rm);
+        for (uint32_t x = f; x; x &= x - 1) {
+            const int i = __builtin_ctz(x), off = (um[r] >> i) & 1 ? 0 : (lm[r] >> i) & 1 ? -1 : 1;
+            L[here(i)] = nl * kRowStep + us[r](c0 - 1, i + off);
+        }
+        rm[r] &= ~(f & ~(um[r] | lm[r]));
+        lm[r] &= ~(f & ~um[r]);
+        um[r] &= ~f;
     }
     __syncthreads();
     bool ok = true;
@@ -295,67 +299,69 @@ __global__ __launch_bounds__(kV3Threads) void k_v3_local(Geo g, VlGeo q, MRef b,
         };
 #pragma unroll
         for (int r = 0; r < kRel; r++) {
-            const int nl = lane + 8 * kRelZ[r] + kRelY[r];
-            auto list = [&](uint64_t x, int off) {
-                for (uint64_t act = __ballot(x != 0); act; act = __ballot(x != 0)) {
-                    if (x) {
-                        const int l = __builtin_ctzll(x);
-                        x &= x - 1;
-                        const int at = n + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(act >> 32),
-                                                                         __builtin_amdgcn_mbcnt_lo((uint32_t)act, 0u));
-                        pairs[wave][at] = (lane * 64 + run_of(m.starts, l)) | (nl * 64 + run_of(us[r], l + off)) << 16;
-                    }
-                    n += __popcll(act);
-                    if (n >= 64) take(64);
+            const int nrow0 = row0 + (8 * kRelZ[r] + kRelY[r]) * kRowStep;
+            for (;;) {
+                const uint32_t x = um[r] | lm[r] | rm[r];
+                const uint64_t act = __ballot(x != 0);
+                if (!act) break;
+                if (x) {
+                    const int i = __builtin_ctz(x);
+                    const uint32_t bit = x & (0u - x), isu = um[r] & bit, isl = isu | (lm[r] & bit);
+                    const int at = n + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(act >> 32),
+                                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)act, 0u));
+                    pairs[wave][at] = here(i) | (nrow0 + us[r](c0 - 1, i + (isu ? 0 : isl ? -1 : 1))) << 16;
+                    um[r] &= ~bit;
+                    if (!isu) lm[r] &= ~bit;
+                    if (!isl) rm[r] &= ~bit;
                 }
-            };
-            list(ct[r].um, 0);
-            list(ct[r].lm, -1);
-            list(ct[r].rm, 1);
+                n += __popcll(act);
+                if (n >= 64) take(64);
+            }
         }
         if (n > 0) take(n);
     }
     __syncthreads();
     // every run's root (two walks at a time), and the roots that meet the seeds
     const uint64_t ss = seeds ? starts_of(m.conn, vl_seed_row(sseed, lane)) : 0ull;
-    for (uint64_t st = m.starts & mine; st;) {
+    const uint32_t ssw = win.of(ss);
+    for (uint32_t st = sm.w & win.kOwn; st;) {
         int s[2], x[2];
-        s[0] = __builtin_ctzll(st);
+        s[0] = __builtin_ctz(st);
         st &= st - 1;
         const int nr = st ? 2 : 1;
-        s[1] = st ? __builtin_ctzll(st) : s[0];
+        s[1] = st ? __builtin_ctz(st) : s[0];
         st &= st - 1;
-        x[0] = lane * 64 + s[0];
-        x[1] = lane * 64 + s[1];
+        x[0] = row0 + win.col(s[0]);
+        x[1] = row0 + win.col(s[1]);
         for (int it = 0;; it++) {
-            const int p0 = lds_ld(&L[fat(x[0])]), p1 = lds_ld(&L[fat(x[1])]);
+            const int p0 = lds_ld(&L[x[0]]), p1 = lds_ld(&L[x[1]]);
             if (p0 == x[0] && p1 == x[1]) break;
             if (it >= gd.cap) {
                 ok = false;
                 break;
             }
-            const int g0 = lds_ld(&L[fat(p0)]), g1 = lds_ld(&L[fat(p1)]);
-            if (g0 != p0) atomicMin(&L[fat(x[0])], g0);
-            if (g1 != p1) atomicMin(&L[fat(x[1])], g1);
+            const int g0 = lds_ld(&L[p0]), g1 = lds_ld(&L[p1]);
+            if (g0 != p0) atomicMin(&L[x[0]], g0);
+            if (g1 != p1) atomicMin(&L[x[1]], g1);
             x[0] = g0;
             x[1] = g1;
         }
 #pragma unroll
         for (int j = 0; j < 2; j++) {
             if (j >= nr) break;
-            const int v = lane * 64 + s[j], xr = x[j] >> 6, xc = x[j] & 63;
-            if (x[j] != v) L[fat(v)] = x[j];
-            if ((ss >> s[j]) & 1) atomicOr(&sbits[xr][xc >> 5], 1u << (xc & 31));
+            const int v = row0 + win.col(s[j]), xr = forest_row(x[j]), xc = x[j] - xr * kRowStep;
+            if (x[j] != v) L[v] = x[j];
+            if ((ssw >> s[j]) & 1) atomicOr(&sbits[xr][xc >> 5], 1u << (xc & 31));
         }
     }
     __syncthreads();
     VLG_GLOBAL int32_t *par = glb(par_);
     auto id_of = [&](int v) {
-        const int r = v >> 6;
-        return vl_id(q, t.tz * 8 + (r >> 3), t.ty * 8 + (r & 7), t.tx * 64 + (v & 63));
+        const int r = forest_row(v);
+        return vl_id(q, t.tz * 8 + (r >> 3), t.ty * 8 + (r & 7), t.tx * 64 + v - r * kRowStep);
     };
-    for (uint64_t st = m.starts & mine; st; st &= st - 1) {
-        const int s = __builtin_ctzll(st), v = lane * 64 + s, x = L[fat(v)], id = id_of(v);
+    for (uint32_t st = sm.w & win.kOwn; st; st &= st - 1) {
+        const int s = win.col(__builtin_ctz(st)), v = row0 + s, x = L[v], id = id_of(v);
         const bool seeded = x == v && ((sbits[lane][s >> 5] >> (s & 31)) & 1);
         par[id] = seeded ? 0 : id_of(x);
         if (multi) glb(flag_)[id] = 0;
@@ -374,8 +380,8 @@ __global__ __launch_bounds__(kV3Threads) void k_v3_local(Geo g, VlGeo q, MRef b,
     // the tile's last column has entries of its own: the tile to the right
     // touches it without knowing its run
     if (wave == kV3Waves - 1 && (m.conn >> 63)) {
-        const int id = id_of(lane * 64 + 63);
-        par[id] = id_of(L[fat(lane * 64 + run_of(m.starts, 63))]);
+        const int id = id_of(row0 + 63);
+        par[id] = id_of(L[row0 + run_of(m.starts, 63)]);
         if (multi) glb(flag_)[id] = 0;
     }
     if (!multi && blockIdx.x == 0 && tid == 0) par[0] = 0;
