@@ -182,6 +182,7 @@ struct Tuning {
     int v[kNumTunables] = {};
 };
 
+constexpr int kCounterWords = (1 + kCounterSlots) * kCounterStep;
 struct vlg_ctx {
     int device = 0;
     std::string arch;
@@ -195,11 +196,12 @@ struct vlg_ctx {
     void *ws = nullptr;
     size_t ws_size = 0;
     bool ws_external = false;       // workspace lent by a server slot
-    // device [4]: merge unions, merge retries, then the 32-bit give-up flag of
-    // the labelling loops (status) and padding
+    // device: the 32-bit give-up flag of the labelling loops (status, at [2]),
+    // and from [kCounterStep] on the slots of the merge counters
     unsigned long long *counters = nullptr;
     unsigned int *status_host = nullptr;     // pinned staging of the flag
     unsigned int *status() const { return (unsigned int *)(counters + 2); }
+    unsigned long long *ccl_counters() const { return counters + kCounterStep; }  // kCounterSlots slots
     LoopGuard guard() const { return LoopGuard{status(), loop_cap}; }
     bool count_ccl = false;         // collect merge counters (VLG_CCL_COUNTERS=1)
     // pointer-jumping labellings since the counters were last read: main
@@ -657,7 +659,7 @@ int enqueue_plan(vlg_ctx *c, const Plan &P, const vlg_image *img, const Layout &
     float *pct = (float *)(base + L.off_pct);
     CclMulti m0;
     std::memset(&m0, 0, sizeof m0);
-    m0.counters = c->count_ccl ? c->counters : nullptr;
+    m0.counters = c->count_ccl ? c->ccl_counters() : nullptr;
     m0.guard = c->guard();
     m0.tbh = tuning_for(c, img->H, img->W).ccl_tbh;
     const CclPlan cp = ccl_plan(P);
@@ -1478,7 +1480,7 @@ int ccl_labels_on(vlg_ctx *c, const Geo &g, const uint64_t *mask_dev, int32_t *l
     m.n = 1;
     m.tbh = ls.tbh;
     m.guard = c->guard();
-    m.counters = c->counters;
+    m.counters = c->ccl_counters();
     m.op[0].b = MRef{mask_dev, 0ull};
     m.op[0].ws = scratch;
     HIP_TRY(launch_ccl_labels(c->stream, g, m, (int32_t *)((char *)scratch + ls.off_ncanon),
@@ -1517,10 +1519,10 @@ int vlg_create(vlg_ctx **out, int device, void *hip_stream) {
     }
     const char *cc = std::getenv("VLG_CCL_COUNTERS");
     c->count_ccl = cc && cc[0] == '1';
-    HIP_TRY(hipMalloc(&c->counters, 4 * sizeof(unsigned long long)));
+    HIP_TRY(hipMalloc(&c->counters, kCounterWords * sizeof(unsigned long long)));
     HIP_TRY(hipHostMalloc((void **)&c->status_host, 256, hipHostMallocDefault));
     *c->status_host = 0;
-    HIP_TRY(launch_fill_i64(c->stream, c->counters, 4, 0));
+    HIP_TRY(launch_fill_i64(c->stream, c->counters, kCounterWords, 0));
     HIP_TRY(hipStreamSynchronize(c->stream));
     void *scratch_dev = nullptr;  // set-up of vlg_ccl_labels_noalloc on this device
     const int rc = noalloc_scratch(device, &scratch_dev);
@@ -2348,12 +2350,15 @@ int vlg_tune_load(vlg_ctx *c, const char *path) {
 int vlg_ccl_read_counters(vlg_ctx *c, vlg_ccl_counters *out) {
     if (!c || !out) return fail(VLG_EINVAL, "null argument");
     DeviceGuard dg(c->device);
-    unsigned long long h[2] = {0, 0};
-    HIP_TRY(hipMemcpyAsync(h, c->counters, sizeof h, hipMemcpyDeviceToHost, c->stream));
+    unsigned long long h[kCounterSlots * kCounterStep];
+    HIP_TRY(hipMemcpyAsync(h, c->ccl_counters(), sizeof h, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
-    out->merge_unions = h[0];
-    out->merge_retries = h[1];
-    HIP_TRY(launch_fill_i64(c->stream, c->counters, 2, 0));
+    out->merge_unions = out->merge_retries = 0;
+    for (int k = 0; k < kCounterSlots; k++) {
+        out->merge_unions += (int64_t)h[k * kCounterStep];
+        out->merge_retries += (int64_t)h[k * kCounterStep + 1];
+    }
+    HIP_TRY(launch_fill_i64(c->stream, c->ccl_counters(), kCounterSlots * kCounterStep, 0));
     out->launches_per_ccl = 4;
     out->pj_labellings = c->pj_labellings;
     out->pj_main_iterations = c->pj_iters;

@@ -186,10 +186,11 @@ struct CclOp {
     int32_t user, multi;
     uint64_t *out;  // gather: (y & z) | components of b that meet the seeds
 };
+constexpr int kCounterSlots = 64, kCounterStep = 16;  // a slot: two counters on a line of its own
 struct CclMulti {
     int n, tbh;     // labellings, block rows per tile
     LoopGuard guard;
-    unsigned long long *counters;  // [2] merge unions, merge retries (may be null)
+    unsigned long long *counters;  // merge unions, merge retries: the sums over the slots (may be null)
     CclOp op[kMaxMulti];
 };
 hipError_t launch_ccl_local(hipStream_t s, const Geo &g, const CclMulti &m);
