@@ -182,7 +182,7 @@ struct Tuning {
     int v[kNumTunables] = {};
 };
 
-constexpr int kCounterWords = (1 + kCounterSlots) * kCounterStep;
+constexpr int kCounterWords = kCounterSlots * kCounterStep;
 struct vlg_ctx {
     int device = 0;
     std::string arch;
@@ -196,13 +196,12 @@ struct vlg_ctx {
     void *ws = nullptr;
     size_t ws_size = 0;
     bool ws_external = false;       // workspace lent by a server slot
-    // device: the 32-bit give-up flag of the labelling loops (status, at [2]),
-    // and from [kCounterStep] on the slots of the merge counters
+    // device: the slots of the merge counters
     unsigned long long *counters = nullptr;
-    unsigned int *status_host = nullptr;     // pinned staging of the flag
-    unsigned int *status() const { return (unsigned int *)(counters + 2); }
-    unsigned long long *ccl_counters() const { return counters + kCounterStep; }  // kCounterSlots slots
-    LoopGuard guard() const { return LoopGuard{status(), loop_cap}; }
+    // pinned words the kernels write: [0] the give-up flag of the labelling
+    // loops, [1] a pointer-jumping round's check
+    unsigned int *status_host = nullptr;
+    LoopGuard guard() const { return LoopGuard{status_host, loop_cap}; }
     bool count_ccl = false;         // collect merge counters (VLG_CCL_COUNTERS=1)
     // pointer-jumping labellings since the counters were last read: main
     // iterations, rounds (reconnect + termination check), kernel launches
@@ -213,6 +212,7 @@ struct vlg_ctx {
     void *desc_host = nullptr;
     size_t desc_host_size = 0;
     hipEvent_t desc_done = nullptr;
+    hipEvent_t order = nullptr;       // vlg_order_stream
     hipEvent_t pj_checked = nullptr;  // a pointer-jumping round's check is on the host
 
     // an executable graph may still be running from an earlier launch: wait
@@ -231,12 +231,9 @@ namespace {
 // context's stream.  VLG_ENOCONV when a loop stopped at its iteration cap in
 // work enqueued since the last check.
 int check_status(vlg_ctx *c) {
-    HIP_TRY(hipMemcpyAsync(c->status_host, c->status(), sizeof(unsigned int), hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
     if (*c->status_host) {
         *c->status_host = 0;
-        HIP_TRY(launch_fill_i64(c->stream, c->counters + 2, 1, 0));
-        HIP_TRY(hipStreamSynchronize(c->stream));
         return fail(VLG_ENOCONV, "a labelling loop stopped at its iteration cap (" + std::to_string(c->loop_cap) +
                                      "): the results of the work since the last synchronisation are not valid");
     }
@@ -659,7 +656,7 @@ int enqueue_plan(vlg_ctx *c, const Plan &P, const vlg_image *img, const Layout &
     float *pct = (float *)(base + L.off_pct);
     CclMulti m0;
     std::memset(&m0, 0, sizeof m0);
-    m0.counters = c->count_ccl ? c->ccl_counters() : nullptr;
+    m0.counters = c->count_ccl ? c->counters : nullptr;
     m0.guard = c->guard();
     m0.tbh = tuning_for(c, img->H, img->W).ccl_tbh;
     const CclPlan cp = ccl_plan(P);
@@ -1480,7 +1477,7 @@ int ccl_labels_on(vlg_ctx *c, const Geo &g, const uint64_t *mask_dev, int32_t *l
     m.n = 1;
     m.tbh = ls.tbh;
     m.guard = c->guard();
-    m.counters = c->ccl_counters();
+    m.counters = c->counters;
     m.op[0].b = MRef{mask_dev, 0ull};
     m.op[0].ws = scratch;
     HIP_TRY(launch_ccl_labels(c->stream, g, m, (int32_t *)((char *)scratch + ls.off_ncanon),
@@ -1542,8 +1539,20 @@ void vlg_destroy(vlg_ctx *c) {
     if (c->desc_host) (void)hipHostFree(c->desc_host);
     if (c->desc_done) (void)hipEventDestroy(c->desc_done);
     if (c->pj_checked) (void)hipEventDestroy(c->pj_checked);
+    if (c->order) (void)hipEventDestroy(c->order);
     if (c->own_stream) (void)hipStreamDestroy(c->stream);
     delete c;
+}
+
+int vlg_order_stream(vlg_ctx *c, void *hip_stream, int ctx_waits) {
+    if (!c) return fail(VLG_EINVAL, "null context");
+    hipStream_t other = (hipStream_t)hip_stream;
+    if (other == c->stream) return VLG_OK;
+    DeviceGuard dg(c->device);
+    if (!c->order) HIP_TRY(hipEventCreateWithFlags(&c->order, hipEventDisableTiming));
+    HIP_TRY(hipEventRecord(c->order, ctx_waits ? other : c->stream));
+    HIP_TRY(hipStreamWaitEvent(ctx_waits ? c->stream : other, c->order, 0));
+    return VLG_OK;
 }
 
 int vlg_sync(vlg_ctx *c) {
@@ -1590,10 +1599,22 @@ int vlg_load_image(vlg_ctx *c, const void *data, int dtype, int channels, int he
         (void)hipGetLastError();
         return fail(VLG_ENOMEM, "image allocation failed");
     }
-    HIP_TRY(hipMemsetAsync(im->dev, 0, im->bytes, c->stream));
-    if ((int64_t)height * width > 0) {
+    const int64_t rows = (int64_t)channels * height;
+    // pixels in this device's memory are read by a kernel, any others copied
+    hipPointerAttribute_t at;
+    bool here = false;
+    if (where == VLG_DEVICE && rows * width > 0 && rows * (im->pitch * (int64_t)es / 16) < (1ll << 32)) {
+        here = hipPointerGetAttributes(&at, data) == hipSuccess && at.type == hipMemoryTypeDevice &&
+               at.device == c->device;
+        if (!here) (void)hipGetLastError();
+    }
+    if (here) {
+        HIP_TRY(launch_load_rows(c->stream, data, pitch_elems * (int64_t)es, width * (int64_t)es, rows, im->dev,
+                                 im->pitch * (int64_t)es));
+    } else {
+        HIP_TRY(hipMemsetAsync(im->dev, 0, im->bytes, c->stream));
         const hipMemcpyKind kind = where == VLG_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice;
-        for (int ch = 0; ch < channels; ch++) {
+        for (int ch = 0; rows * width > 0 && ch < channels; ch++) {
             const char *src = (const char *)data + (size_t)ch * height * pitch_elems * es;
             HIP_TRY(hipMemcpy2DAsync((char *)im->dev + (size_t)ch * height * im->pitch * es, im->pitch * es, src,
                                      (size_t)pitch_elems * es, (size_t)width * es, (size_t)height, kind,
@@ -2350,15 +2371,15 @@ int vlg_tune_load(vlg_ctx *c, const char *path) {
 int vlg_ccl_read_counters(vlg_ctx *c, vlg_ccl_counters *out) {
     if (!c || !out) return fail(VLG_EINVAL, "null argument");
     DeviceGuard dg(c->device);
-    unsigned long long h[kCounterSlots * kCounterStep];
-    HIP_TRY(hipMemcpyAsync(h, c->ccl_counters(), sizeof h, hipMemcpyDeviceToHost, c->stream));
+    unsigned long long h[kCounterWords];
+    HIP_TRY(hipMemcpyAsync(h, c->counters, sizeof h, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
     out->merge_unions = out->merge_retries = 0;
     for (int k = 0; k < kCounterSlots; k++) {
         out->merge_unions += (int64_t)h[k * kCounterStep];
         out->merge_retries += (int64_t)h[k * kCounterStep + 1];
     }
-    HIP_TRY(launch_fill_i64(c->stream, c->ccl_counters(), kCounterSlots * kCounterStep, 0));
+    HIP_TRY(launch_fill_i64(c->stream, c->counters, kCounterWords, 0));
     out->launches_per_ccl = 4;
     out->pj_labellings = c->pj_labellings;
     out->pj_main_iterations = c->pj_iters;

@@ -144,12 +144,12 @@ __device__ __forceinline__ uint64_t lane_prev64(uint64_t v) {
 __device__ __forceinline__ uint64_t lane_next64(uint64_t v) {
     return (uint64_t)(uint32_t)lane_next((int)(uint32_t)v) | ((uint64_t)(uint32_t)lane_next((int)(v >> 32)) << 32);
 }
-// Raise the give-up flag of a launch (one vector atomic per wave).
+// Raise the give-up flag of a launch, a word of the host (one store per wave).
 // Called by every lane of the wave.
 __device__ __forceinline__ void guard_report(const LoopGuard &gd, bool ok) {
     const uint64_t bad = __ballot(!ok);
     if (bad && lane_id() == __builtin_ctzll(bad) && gd.status)
-        __hip_atomic_fetch_or(glb(gd.status), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(glb(gd.status), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // Cross-lane handoff through LDS inside one wave: every lane's LDS writes

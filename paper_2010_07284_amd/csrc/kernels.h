@@ -73,7 +73,7 @@ inline int default_tile_bh(Tiles tiles) {
 // into VLG_ENOCONV.  A correct labelling never comes near the default cap.
 constexpr int kLoopCapDefault = 1 << 20;
 struct LoopGuard {
-    unsigned int *status;  // device word, set to 1 when a loop gives up
+    unsigned int *status;  // pinned host word, set to 1 when a loop gives up
     int cap;               // iterations per walk (>= 1)
 };
 
@@ -355,6 +355,10 @@ struct SegTile {
 };
 SegTile seg_tile(const Geo &g, int halo, int nregs);
 hipError_t launch_segment(hipStream_t s, const Geo &g, const SegProg &p);
+// rows of row_bytes, src_pitch bytes apart, to rows dst_pitch (a multiple of
+// 16) bytes apart, the rest of each row zero
+hipError_t launch_load_rows(hipStream_t s, const void *src, int64_t src_pitch, int64_t row_bytes, int64_t rows,
+                            void *dst, int64_t dst_pitch);
 hipError_t launch_fill_i64(hipStream_t s, unsigned long long *p, int n, unsigned long long v);
 // bytes (a multiple of width) copied in width-byte units (8 or 16)
 hipError_t launch_stream_copy(hipStream_t s, void *dst, const void *src, int64_t bytes, int width);

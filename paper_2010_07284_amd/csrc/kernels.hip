@@ -343,6 +343,31 @@ __global__ __launch_bounds__(kThreads) void k_unpack(Geo g, const uint64_t *mask
     unpack_piece(g, mask, out, (int64_t)blockIdx.x * kThreads + threadIdx.x);
 }
 
+// Rows of an image into its padded rows, the padding zero: 16 bytes of the
+// destination per lane.  One launch and one pass instead of a fill and a
+// pitched copy (loading 1000 x 750 uint16 pixels: 29.5 -> 18.8 us, launch bound).
+__global__ __launch_bounds__(kThreads) void k_load_rows(const char *src, int64_t src_pitch, int64_t row_bytes,
+                                                        uint32_t n, uint32_t mul, uint32_t shift, uint32_t pieces,
+                                                        char *dst) {
+    typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+    typedef uint32_t u4u __attribute__((ext_vector_type(4), aligned(1)));
+    const uint64_t stride = (uint64_t)gridDim.x * kThreads;
+    for (uint64_t i = (uint64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += stride) {
+        const uint32_t row = fdiv((uint32_t)i, mul, shift);
+        const int64_t off = (int64_t)((uint32_t)i - row * pieces) * 16, left = row_bytes - off;
+        const VLG_GLOBAL char *p = glb(src) + (int64_t)row * src_pitch + off;
+        u4 v = {0u, 0u, 0u, 0u};
+        if (left >= 16) {
+            v = *(const VLG_GLOBAL u4u *)p;
+        } else {
+#pragma unroll
+            for (int k = 0; k < 15; k++)
+                if (k < left) v[k >> 2] |= (uint32_t)(uint8_t)p[k] << (8 * (k & 3));
+        }
+        *(VLG_GLOBAL u4 *)(glb(dst) + i * 16) = v;
+    }
+}
+
 __global__ void k_fill_i64(unsigned long long *p, int n, unsigned long long v) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = v;
@@ -611,6 +636,14 @@ __global__ __launch_bounds__(kSegWideThreads) void k_segment_wide(Geo g, SegProg
 
 }  // namespace
 
+// n / d = (umulhi(n, mul) + n) >> shift, valid for all 32-bit n
+static void fast_div(uint32_t d, uint32_t &mul, uint32_t &shift) {
+    uint32_t s = 0;
+    while ((1ull << s) < d) s++;
+    mul = (uint32_t)(((1ull << 32) * ((1ull << s) - d)) / d + 1);
+    shift = s;
+}
+
 Geo make_geo(int H, int W) {
     Geo g;
     g.H = H;
@@ -620,12 +653,21 @@ Geo make_geo(int H, int W) {
     g.nwords = (int64_t)H * g.wpr;
     g.BH = (H + 1) / 2;
     g.BW = (W + 1) / 2;
-    // n / d = (umulhi(n, mul) + n) >> shift, valid for all 32-bit n
-    uint32_t d = (uint32_t)(g.wpr > 0 ? g.wpr : 1), s = 0;
-    while ((1ull << s) < d) s++;
-    g.wpr_mul = (uint32_t)(((1ull << 32) * ((1ull << s) - d)) / d + 1);
-    g.wpr_shift = s;
+    fast_div((uint32_t)(g.wpr > 0 ? g.wpr : 1), g.wpr_mul, g.wpr_shift);
     return g;
+}
+
+hipError_t launch_load_rows(hipStream_t s, const void *src, int64_t src_pitch, int64_t row_bytes, int64_t rows,
+                            void *dst, int64_t dst_pitch) {
+    if (dst_pitch % 16 || row_bytes > dst_pitch || rows * (dst_pitch / 16) >= (1ll << 32))
+        return hipErrorInvalidValue;
+    const uint32_t n = (uint32_t)(rows * (dst_pitch / 16));
+    if (n == 0) return hipSuccess;
+    uint32_t mul, shift;
+    fast_div((uint32_t)(dst_pitch / 16), mul, shift);
+    k_load_rows<<<grid_for(n, kThreads, 16384), kThreads, 0, s>>>((const char *)src, src_pitch, row_bytes, n, mul,
+                                                                  shift, (uint32_t)(dst_pitch / 16), (char *)dst);
+    return hipGetLastError();
 }
 
 hipError_t launch_logic(hipStream_t s, const Geo &g, MRef x, MRef y, int op, int inv_out, uint64_t *out) {
