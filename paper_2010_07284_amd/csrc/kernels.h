@@ -49,7 +49,6 @@ __host__ __device__ inline int64_t near_tasks(const Geo &g, int R) {
 // Tile geometry of the reachability labelling: TBH x 64 blocks per tile
 // (2*TBH pixel rows x 128 pixel columns); TBH is tunable (8, 16 or 32).
 constexpr int kTileBW = 64;
-constexpr int kTileBHDefault = 16;
 inline bool valid_tile_bh(int t) { return t == 8 || t == 16 || t == 32; }
 inline int64_t tile_count(int H, int W, int tbh) {
     const int64_t bh = (H + 1) / 2, bw = (W + 1) / 2;
