@@ -106,11 +106,6 @@ void vlg_destroy(vlg_ctx *ctx);
  * stopped at its iteration cap: the outputs of the work enqueued since the
  * previous synchronisation are then not valid. */
 int vlg_sync(vlg_ctx *ctx);
-/* Order the context's stream against another stream of its device, without
- * waiting on the host: work enqueued on ctx after this call starts when the
- * work enqueued on hip_stream before it is done (ctx_waits != 0), or the other
- * way round (ctx_waits = 0). */
-int vlg_order_stream(vlg_ctx *ctx, void *hip_stream, int ctx_waits);
 /* Iteration cap of every loop of the labelling kernels (union-find walks,
  * hooks and their retries, the root walks of the flag pass), per walk.  The
  * paper's labelling ends by a termination check after each iteration (Sect. 3,

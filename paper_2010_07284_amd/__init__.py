@@ -91,13 +91,15 @@ class _Ordered:
         self.ctx = ctx
 
     def __enter__(self):
-        self.cur = _torch().cuda.current_stream(self.ctx.device).cuda_stream
-        _lib.call("vlg_order_stream", self.ctx.handle, self.cur, 1)
+        torch = _torch()
+        self.cur = torch.cuda.current_stream(self.ctx.device)
+        if self.cur.cuda_stream != self.ctx.stream.cuda_stream:
+            self.ctx.stream.wait_stream(self.cur)
         return self
 
     def __exit__(self, *exc):
-        if exc[0] is None:
-            _lib.call("vlg_order_stream", self.ctx.handle, self.cur, 0)
+        if exc[0] is None and self.cur.cuda_stream != self.ctx.stream.cuda_stream:
+            self.cur.wait_stream(self.ctx.stream)
         return False
 
 

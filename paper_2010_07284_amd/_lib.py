@@ -75,7 +75,6 @@ def lib():
             "vlg_create": ([P, I, P], I),
             "vlg_destroy": ([P], None),
             "vlg_sync": ([P], I),
-            "vlg_order_stream": ([P, P, I], I),
             "vlg_set_loop_cap": ([P, I], I),
             "vlg_set_mode": ([P, I], I),
             "vlg_load_image": ([P, P, I, I, I, I, I64, I, P], I),

@@ -212,7 +212,6 @@ struct vlg_ctx {
     void *desc_host = nullptr;
     size_t desc_host_size = 0;
     hipEvent_t desc_done = nullptr;
-    hipEvent_t order = nullptr;       // vlg_order_stream
     hipEvent_t pj_checked = nullptr;  // a pointer-jumping round's check is on the host
 
     // an executable graph may still be running from an earlier launch: wait
@@ -1539,20 +1538,8 @@ void vlg_destroy(vlg_ctx *c) {
     if (c->desc_host) (void)hipHostFree(c->desc_host);
     if (c->desc_done) (void)hipEventDestroy(c->desc_done);
     if (c->pj_checked) (void)hipEventDestroy(c->pj_checked);
-    if (c->order) (void)hipEventDestroy(c->order);
     if (c->own_stream) (void)hipStreamDestroy(c->stream);
     delete c;
-}
-
-int vlg_order_stream(vlg_ctx *c, void *hip_stream, int ctx_waits) {
-    if (!c) return fail(VLG_EINVAL, "null context");
-    hipStream_t other = (hipStream_t)hip_stream;
-    if (other == c->stream) return VLG_OK;
-    DeviceGuard dg(c->device);
-    if (!c->order) HIP_TRY(hipEventCreateWithFlags(&c->order, hipEventDisableTiming));
-    HIP_TRY(hipEventRecord(c->order, ctx_waits ? other : c->stream));
-    HIP_TRY(hipStreamWaitEvent(ctx_waits ? c->stream : other, c->order, 0));
-    return VLG_OK;
 }
 
 int vlg_sync(vlg_ctx *c) {
