@@ -84,8 +84,11 @@ struct PctQ {  // of one rank
     uint32_t nlist, pad[27];
     PctSeg seg[kSegs];
     uint32_t hist[2048];   // of the candidates' leading digit
-    uint32_t list[kList];  // candidates in the rank's bucket of hist
+    // candidates in the rank's bucket of hist (nlist of them), or, when there
+    // are too many (nlist = kCrowded), the histograms of the next two digits
+    uint32_t list[kList];
 };
+constexpr uint32_t kCrowded = ~0u;
 static_assert(sizeof(PctQ) <= kPctStateBytes, "percentile state");
 __device__ __forceinline__ VLG_GLOBAL PctQ *qstate(void *states, int slot) {
     return (VLG_GLOBAL PctQ *)((char *)states + (size_t)slot * kPctStateBytes);
@@ -255,6 +258,7 @@ __device__ __forceinline__ void pct_bracket_wg(uint32_t n, const PctSel &sel, co
         for (int q = 0; q < sel.n; q++) {
             VLG_GLOBAL PctQ *st = qstate(states, sel.slot[q]);
             for (int i = tid; i < 2048; i += kSelThreads) st->hist[i] = 0;
+            for (int i = tid; i < kList; i += kSelThreads) st->list[i] = 0;
             if (tid < kSegs * 4) (&st->seg[tid >> 2].ncand)[tid & 3] = 0;
         }
     __syncthreads();  // the next image of a persistent workgroup reuses the LDS
@@ -513,11 +517,12 @@ __device__ __forceinline__ void pct_candidate_hist(VLG_GLOBAL PctQ *st, const Ca
     __syncthreads();
 }
 
-// Many candidates: those in the rank's bucket of the leading digit go to the
-// state's list, `parts` workgroups of kSelThreads per rank.
-__device__ __forceinline__ uint32_t pct_bucket(const VLG_GLOBAL PctQ *st, uint32_t &r, uint32_t *h, uint32_t *found) {
+// The bucket of a histogram of 2048 that holds rank r; r: the rank in it.
+__device__ __forceinline__ uint32_t pct_bucket(const VLG_GLOBAL uint32_t *hist, uint32_t &r, uint32_t *h,
+                                               uint32_t *found) {
     const int tid = (int)threadIdx.x;
-    for (int i = tid; i < 2048; i += kSelThreads) h[i] = st->hist[i];
+    __syncthreads();
+    for (int i = tid; i < 2048; i += kSelThreads) h[i] = hist[i];
     __syncthreads();
     if (tid < 64) {
         uint32_t rr = r;
@@ -531,30 +536,81 @@ __device__ __forceinline__ uint32_t pct_bucket(const VLG_GLOBAL PctQ *st, uint32
     r = found[1];
     return found[0];
 }
+// Digits of the candidates (11 bits, 11 and the rest): their low ends.
+__device__ __forceinline__ int digit1(uint32_t bits) { return bits > 11 ? (int)bits - 11 : 0; }
+__device__ __forceinline__ int digit2(uint32_t bits) { return bits > 22 ? (int)bits - 22 : 0; }
+
+// Many candidates: those in the rank's bucket of the leading digit go to the
+// state's list, `parts` workgroups of kSelThreads per rank.  A bucket of more
+// than the list holds (ties, or keys that crowd into one 2048th of the
+// bracket, as flat regions do) is counted by the next digit instead, and by
+// the last one in pct_refine: one workgroup going over a million such
+// candidates three times made a formula with two ranks at 4096^2 (flat ellipses)
+// take 1.16 ms, which takes 0.35 so; where no bucket is crowded the extra launch
+// costs 5 us per step, 17 in a batch of 128 images.
 __device__ __forceinline__ void pct_list(VLG_GLOBAL PctQ *st, const Cand &cand, int j, int part, int parts, uint32_t *h,
                                          uint32_t *found) {
     const PctFound f = pct_found(st, cand);
-    if (!f.candidate || f.n <= kFewCandidates) return;
-    const int sh = f.bits > 11 ? (int)f.bits - 11 : 0;
+    const int sh = digit1(f.bits), sh2 = digit2(f.bits);
+    if (!f.candidate || f.n <= kFewCandidates || sh == 0) return;
     uint32_t r = f.r;
-    const uint32_t bucket = pct_bucket(st, r, h, found);
+    const uint32_t bucket = pct_bucket(st->hist, r, h, found);
+    if (st->hist[bucket] > (uint32_t)kList) {
+        __syncthreads();  // every thread has read found
+        for (int i = (int)threadIdx.x; i < 2048; i += kSelThreads) h[i] = 0;
+        __syncthreads();
+        each_candidate(st, cand, j, part, parts, [&](uint32_t c) {
+            const uint32_t v = c - f.base;
+            if (v >> sh == bucket) atomicAdd(&h[(v >> sh2) & ((1u << (sh - sh2)) - 1u)], 1u);
+        });
+        __syncthreads();
+        for (int i = (int)threadIdx.x; i < 2048; i += kSelThreads)
+            if (h[i]) __hip_atomic_fetch_add(&st->list[i], h[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (threadIdx.x == 0) st->nlist = kCrowded;
+        __syncthreads();  // h and found are rewritten for the next image
+        return;
+    }
     // collected in LDS first: one addition to the shared count per workgroup
-    // (beyond 2048, which takes ties, the list is too long in any case)
     __syncthreads();  // every thread has read found
     if (threadIdx.x == 0) found[0] = 0;
     __syncthreads();
     each_candidate(st, cand, j, part, parts, [&](uint32_t c) {
         if ((c - f.base) >> sh != bucket) return;
         const uint32_t at = atomicAdd(&found[0], 1u);
-        if (at < 2048) h[at] = c - f.base;
+        if (at < 2048)
+            h[at] = c - f.base;
+        else  // (the bucket holds at most kList in all)
+            st->list[__hip_atomic_fetch_add(&st->nlist, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)] = c - f.base;
     });
     __syncthreads();
-    const uint32_t n = found[0] <= 2048 ? found[0] : kList + 1;
+    const uint32_t n = found[0] < 2048 ? found[0] : 2048;
     if (threadIdx.x == 0 && n)
         found[1] = __hip_atomic_fetch_add(&st->nlist, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
-    for (uint32_t i = threadIdx.x; i < n && found[1] + i < kList; i += kSelThreads)
-        if (i < 2048) st->list[found[1] + i] = h[i];
+    for (uint32_t i = threadIdx.x; i < n; i += kSelThreads) st->list[found[1] + i] = h[i];
+    __syncthreads();  // h and found are rewritten for the next image
+}
+
+// The last digit of a crowded bucket (float32): counted behind the second.
+__device__ __forceinline__ void pct_refine(VLG_GLOBAL PctQ *st, const Cand &cand, int j, int part, int parts,
+                                           uint32_t *h, uint32_t *found) {
+    if (st->nlist != kCrowded) return;
+    const PctFound f = pct_found(st, cand);
+    const int sh = digit1(f.bits), sh2 = digit2(f.bits);
+    if (!f.candidate || f.n <= kFewCandidates || sh2 == 0) return;
+    uint32_t r = f.r;
+    uint32_t top = pct_bucket(st->hist, r, h, found);
+    top = top << (sh - sh2) | pct_bucket(st->list, r, h, found);
+    __syncthreads();  // every thread has read found
+    for (int i = (int)threadIdx.x; i < 2048; i += kSelThreads) h[i] = 0;
+    __syncthreads();
+    each_candidate(st, cand, j, part, parts, [&](uint32_t c) {
+        const uint32_t v = c - f.base;
+        if (v >> sh2 == top) atomicAdd(&h[v & ((1u << sh2) - 1u)], 1u);
+    });
+    __syncthreads();
+    for (int i = (int)threadIdx.x; i < 2048; i += kSelThreads)
+        if (h[i]) __hip_atomic_fetch_add(&st->list[2048 + i], h[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();  // h and found are rewritten for the next image
 }
 
@@ -602,15 +658,18 @@ __device__ __forceinline__ void pct_pick_wg(const Geo &g, const T *img_, VLG_GLO
         each_candidate(st, cand, j, -1, cand.nseg, [&](uint32_t c) { fn(c - f.base); });
     };
     if (many) {
-        const int sh = f.bits > 11 ? (int)f.bits - 11 : 0;
-        uint32_t r = f.r;
-        const uint32_t bucket = pct_bucket(st, r, h, found), n = st->nlist;
-        if (n <= kList)
-            key = f.base + (bucket << sh) + radix(sh, r, [&](auto fn) {
-                for (uint32_t i = tid; i < n; i += kSelThreads) fn(st->list[i] & ((1u << sh) - 1u));
-            });
-        else  // (ties)
-            key = f.base + radix(f.bits, f.r, all);
+        const int sh = digit1(f.bits), sh2 = digit2(f.bits);
+        uint32_t r = f.r, v = pct_bucket(st->hist, r, h, found);
+        const uint32_t n = st->nlist;
+        if (sh > 0 && n == kCrowded) {
+            v = v << (sh - sh2) | pct_bucket(st->list, r, h, found);
+            if (sh2 > 0) v = v << sh2 | pct_bucket(st->list + 2048, r, h, found);
+        } else if (sh > 0) {
+            v = (v << sh) + radix(sh, r, [&](auto fn) {
+                    for (uint32_t i = tid; i < n; i += kSelThreads) fn(st->list[i] & ((1u << sh) - 1u));
+                });
+        }
+        key = f.base + v;
     } else if (f.candidate) {
         key = f.base + radix(f.bits, f.r, all);
     } else if (f.failed) {
@@ -664,6 +723,12 @@ __global__ __launch_bounds__(kSelThreads) void k_pct_list(PctSel sel, void *stat
     __shared__ uint32_t h[2048], found[2];
     const int j = (int)blockIdx.y;
     pct_list(qstate(states, sel.slot[j]), cand, j, (int)blockIdx.x, (int)gridDim.x, h, found);
+}
+
+__global__ __launch_bounds__(kSelThreads) void k_pct_refine(PctSel sel, void *states, Cand cand) {
+    __shared__ uint32_t h[2048], found[2];
+    const int j = (int)blockIdx.y;
+    pct_refine(qstate(states, sel.slot[j]), cand, j, (int)blockIdx.x, (int)gridDim.x, h, found);
 }
 
 template <typename T>
@@ -724,6 +789,15 @@ __global__ __launch_bounds__(kSelThreads) void kb_pct_candidates(BatchArgs a, Pc
     }
 }
 
+__global__ __launch_bounds__(kSelThreads) void kb_pct_refine(BatchArgs a, PctSel sel) {
+    __shared__ uint32_t h[2048], found[2];
+    const int j = (int)blockIdx.y;
+    VLG_BATCH_LOOP(a) {
+        VLG_BATCH_IMG(a)
+        pct_refine(qstate(d.ws + d.off_pctst, sel.slot[j]), bcand(d), j, (int)blockIdx.z, (int)gridDim.z, h, found);
+    }
+}
+
 __global__ __launch_bounds__(kSelThreads) void kb_pct_list(BatchArgs a, PctSel sel) {
     __shared__ uint32_t h[2048], found[2];
     const int j = (int)blockIdx.y;
@@ -775,6 +849,7 @@ hipError_t percentile_sampled(hipStream_t s, const Geo &g, const T *img, const P
         const dim3 parts(cand.nseg > 1 ? 4 * cand.nseg : 8, sel.n);
         k_pct_candidates<<<parts, kSelThreads, 0, s>>>(sel, states, cand);
         k_pct_list<<<parts, kSelThreads, 0, s>>>(sel, states, cand);
+        if (F32) k_pct_refine<<<parts, kSelThreads, 0, s>>>(sel, states, cand);
     }
     k_pct_pick<T><<<sel.n, kSelThreads, 0, s>>>(g, img, sel, states, cand, results);
     return hipGetLastError();
@@ -796,6 +871,7 @@ hipError_t b_percentile_sampled(hipStream_t s, const BatchArgs &one, int64_t tot
     const dim3 parts(g1, sel.n, 4);
     kb_pct_candidates<<<parts, kSelThreads, 0, s>>>(one, sel);
     kb_pct_list<<<parts, kSelThreads, 0, s>>>(one, sel);
+    if (F32) kb_pct_refine<<<parts, kSelThreads, 0, s>>>(one, sel);
     kb_pct_pick<T><<<dim3(g1, sel.n), kSelThreads, 0, s>>>(one, chan, sel);
     return hipGetLastError();
 }

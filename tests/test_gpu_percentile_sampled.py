@@ -106,3 +106,16 @@ def test_nan_and_infinities_keep_their_order():
     x.view(np.uint32)[rng.random(x.shape) < 0.002] = 0x7FFFFFFF
     check(x, (0.06, 0.5, 0.93))
     check(x, (0.0, 1.0, 0.0001, 0.9999))
+
+
+@pytest.mark.parametrize("dtype", ["float32", "uint16"])
+@pytest.mark.parametrize("width", [0.0, 2e-6, 1e-4])
+def test_crowded_bucket(dtype, width):
+    # a twentieth of the pixels in one narrow range (or one value) within the
+    # bracket of the median, whose ends lie far from it
+    rng = np.random.default_rng(int(width * 1e7))
+    x = rng.choice([0.02, 0.9], (2049, 2050)) + 0.08 * rng.random((2049, 2050))
+    crowd = rng.random(x.shape) < 0.045
+    x[crowd] = 0.5 + width * rng.random(int(crowd.sum()))
+    x = (x * 2 - 0.5).astype(np.float32) if dtype == "float32" else (x * 60000).astype(dtype)
+    check(x, (0.49, 0.5, 0.505))
