@@ -105,6 +105,19 @@ struct Cand {
 };
 __host__ __device__ inline uint32_t pixels_of(const Geo &g) { return (uint32_t)g.H * (uint32_t)g.W; }
 
+// h[bin] += 1 for every active lane; many lanes with the first lane's bin add
+// once together (a constant background would otherwise serialise the wave: two
+// ranks at 4096^2 with 58% zeros 173 -> 139 us; without ties 113 -> 117).
+__device__ __forceinline__ void hist_add(uint32_t *h, uint32_t bin) {
+    const uint32_t b = (uint32_t)__builtin_amdgcn_readfirstlane((int)bin);
+    const uint64_t same = __ballot(bin == b);
+    if (__popcll(same) > 8) {
+        if (lane_id() == __builtin_ctzll(same)) atomicAdd(&h[b], (uint32_t)__popcll(same));
+        if (bin == b) return;
+    }
+    atomicAdd(&h[bin], 1u);
+}
+
 // Bucket of rank r in a histogram of 2048 bins in LDS, by one wave; r becomes
 // the rank inside the bucket (both wave-uniform).
 __device__ __forceinline__ int wave_find(const uint32_t *h, uint32_t &r) {
@@ -189,7 +202,7 @@ __device__ __forceinline__ void pct_bracket_wg(uint32_t n, const PctSel &sel, co
         // first digit: one histogram for all targets
 #pragma unroll
         for (int j = 0; j < PER; j++)
-            if ((uint32_t)(tid + j * kSelThreads) < sn) atomicAdd(&h[0][key[j] >> S1], 1u);
+            if ((uint32_t)(tid + j * kSelThreads) < sn) hist_add(h[0], key[j] >> S1);
         __syncthreads();
         if (wave < nt) {
             uint32_t r = trank[wave];
@@ -213,7 +226,7 @@ __device__ __forceinline__ void pct_bracket_wg(uint32_t n, const PctSel &sel, co
 #pragma unroll
                 for (int j = 0; j < PER; j++)
                     if ((uint32_t)(tid + j * kSelThreads) < sn && (key[j] >> above) == pre)
-                        atomicAdd(&h[q][(key[j] >> sh) & dm], 1u);
+                        hist_add(h[q], (key[j] >> sh) & dm);
             }
             __syncthreads();
             if (wave < nt) {
