@@ -51,6 +51,12 @@ __device__ __forceinline__ float value_of(uint32_t k) {
     if constexpr (sizeof(T) == 4) return key_f32(k);
     else return (float)k;
 }
+// The largest key of an open bracket: uint16 keys end there; the largest
+// float32 key stands for no element in the pass.  Brackets are no wider than
+// the keys, so uint16 candidates have two digits (11 bits, 5) and only float32
+// ones a third.
+template <bool F32>
+constexpr uint32_t kTopKey = F32 ? 0xFFFFFFFEu : 0xFFFFu;
 
 // ------------------------------------------------------------------ sampled select
 constexpr int kSelThreads = 1024;
@@ -257,9 +263,8 @@ __device__ __forceinline__ void pct_bracket_wg(uint32_t n, const PctSel &sel, co
             // (or more than the candidates' room, a sixteenth, holds with a margin)
             if (in > min(span + span / 2 + 64, sn * 17 / 320)) mode = PCT_HEAVY;
             // ranks near an end: the bracket takes everything on that side
-            // (but the largest key, which stands for no element in the pass)
             if (rl < 0) lo = 0;
-            if (rh >= (int)sn) hi = 0xFFFFFFFEu;
+            if (rh >= (int)sn) hi = kTopKey<F32>;
         }
         st->k = ranks[tid];
         st->lo = lo;
@@ -676,7 +681,7 @@ __device__ __forceinline__ void pct_pick_wg(const Geo &g, const T *img_, VLG_GLO
         const uint32_t n = st->nlist;
         if (sh > 0 && n == kCrowded) {
             v = v << (sh - sh2) | pct_bucket(st->list, r, h, found);
-            if (sh2 > 0) v = v << sh2 | pct_bucket(st->list + 2048, r, h, found);
+            if (sizeof(T) == 4 && sh2 > 0) v = v << sh2 | pct_bucket(st->list + 2048, r, h, found);
         } else if (sh > 0) {
             v = (v << sh) + radix(sh, r, [&](auto fn) {
                     for (uint32_t i = tid; i < n; i += kSelThreads) fn(st->list[i] & ((1u << sh) - 1u));
