@@ -37,7 +37,10 @@ int fail(int code, const std::string &msg) {
 #define HIP_TRY(expr)                                                                     \
     do {                                                                                  \
         hipError_t e_ = (expr);                                                           \
-        if (e_ != hipSuccess) return fail(VLG_EHIP, std::string(#expr) + ": " + hipGetErrorString(e_)); \
+        if (e_ != hipSuccess) {                                                           \
+            (void)hipGetLastError(); /* reported here, not by the thread's next launch */ \
+            return fail(VLG_EHIP, std::string(#expr) + ": " + hipGetErrorString(e_));     \
+        }                                                                                 \
     } while (0)
 
 size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
@@ -1587,12 +1590,20 @@ int vlg_load_image(vlg_ctx *c, const void *data, int dtype, int channels, int he
         return fail(VLG_ENOMEM, "image allocation failed");
     }
     const int64_t rows = (int64_t)channels * height;
-    // pixels in this device's memory are read by a kernel, any others copied
-    hipPointerAttribute_t at;
+    // pixels that lie within one allocation of this device's memory are read by
+    // a kernel, any others copied: the copy refuses rows beyond an allocation,
+    // which the kernel would read
     bool here = false;
     if (where == VLG_DEVICE && rows * width > 0 && rows * (im->pitch * (int64_t)es / 16) < (1ll << 32)) {
-        here = hipPointerGetAttributes(&at, data) == hipSuccess && at.type == hipMemoryTypeDevice &&
-               at.device == c->device;
+        hipPointerAttribute_t at;
+        hipDeviceptr_t base = nullptr;
+        size_t size = 0;
+        const size_t extent = ((size_t)(rows - 1) * (size_t)pitch_elems + (size_t)width) * es;
+        if (hipPointerGetAttributes(&at, data) == hipSuccess && at.type == hipMemoryTypeDevice &&
+            at.device == c->device && hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)data) == hipSuccess) {
+            const size_t off = (size_t)((const char *)data - (const char *)base);
+            here = off <= size && extent <= size - off;
+        }
         if (!here) (void)hipGetLastError();
     }
     if (here) {

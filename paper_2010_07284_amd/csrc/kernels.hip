@@ -661,13 +661,14 @@ hipError_t launch_load_rows(hipStream_t s, const void *src, int64_t src_pitch, i
                             void *dst, int64_t dst_pitch) {
     if (dst_pitch % 16 || row_bytes > dst_pitch || rows * (dst_pitch / 16) >= (1ll << 32))
         return hipErrorInvalidValue;
-    const uint32_t n = (uint32_t)(rows * (dst_pitch / 16));
+    uint32_t n = (uint32_t)(rows * (dst_pitch / 16));
     if (n == 0) return hipSuccess;
     uint32_t mul, shift;
     fast_div((uint32_t)(dst_pitch / 16), mul, shift);
-    k_load_rows<<<grid_for(n, kThreads, 16384), kThreads, 0, s>>>((const char *)src, src_pitch, row_bytes, n, mul,
-                                                                  shift, (uint32_t)(dst_pitch / 16), (char *)dst);
-    return hipGetLastError();
+    // (its own status: an error that the caller's thread left behind is not this launch's)
+    uint32_t pieces = (uint32_t)(dst_pitch / 16);
+    void *args[] = {&src, &src_pitch, &row_bytes, &n, &mul, &shift, &pieces, &dst};
+    return hipLaunchKernel((const void *)k_load_rows, dim3(grid_for(n, kThreads, 16384)), dim3(kThreads), args, 0, s);
 }
 
 hipError_t launch_logic(hipStream_t s, const Geo &g, MRef x, MRef y, int op, int inv_out, uint64_t *out) {
