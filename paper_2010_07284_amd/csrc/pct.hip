@@ -81,9 +81,14 @@ enum PctMode : uint32_t { PCT_LIGHT = 0, PCT_HEAVY, PCT_DIRECT };
 // Counts of the pass.  The workgroups of a large single image would all add to
 // the same four addresses when they end (2048 of them: 40 us), so they share
 // kSegs sets of counts and candidate segments, each on a cache line of its
-// own.
+// own.  A workgroup's first segment is a hash of its index, and a segment
+// that is full passes the rest on to the next: with the index modulo kSegs
+// the segment followed the rows, and an image periodic over 8 to 256 rows
+// filled a few of them and left the others empty.
 struct PctSeg {
-    uint32_t ncand, below, eqlo, eqhi, pad[28];
+    // ncand: places asked for (beyond the segment's room: passed on); lost:
+    // candidates for which no segment had room
+    uint32_t ncand, below, eqlo, eqhi, lost, pad[27];
 };
 struct PctQ {  // of one rank
     uint32_t k, lo, hi, mode;
@@ -105,8 +110,15 @@ struct Cand {
     uint32_t cap;
     int nseg;
     __device__ __forceinline__ uint32_t seg_cap() const { return cap / (uint32_t)nseg; }
-    __device__ __forceinline__ VLG_GLOBAL uint32_t *seg(int j, int s) const {
-        return glb(buf) + (size_t)j * cap + (size_t)s * seg_cap();
+    __device__ __forceinline__ VLG_GLOBAL uint32_t *rank(int j) const { return glb(buf) + (size_t)j * cap; }
+    // keys in segment s of a rank
+    __device__ __forceinline__ uint32_t held(const VLG_GLOBAL PctQ *st, int s) const {
+        return min((uint32_t)st->seg[s].ncand, seg_cap());
+    }
+    // Places for n keys in segment s: how many it has room for, from its place `at` on.
+    __device__ __forceinline__ uint32_t reserve(VLG_GLOBAL PctQ *st, int s, uint32_t n, uint32_t &at) const {
+        at = __hip_atomic_fetch_add(&st->seg[s].ncand, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return at < seg_cap() ? min(n, seg_cap() - at) : 0u;
     }
 };
 __host__ __device__ inline uint32_t pixels_of(const Geo &g) { return (uint32_t)g.H * (uint32_t)g.W; }
@@ -277,7 +289,7 @@ __device__ __forceinline__ void pct_bracket_wg(uint32_t n, const PctSel &sel, co
             VLG_GLOBAL PctQ *st = qstate(states, sel.slot[q]);
             for (int i = tid; i < 2048; i += kSelThreads) st->hist[i] = 0;
             for (int i = tid; i < kList; i += kSelThreads) st->list[i] = 0;
-            if (tid < kSegs * 4) (&st->seg[tid >> 2].ncand)[tid & 3] = 0;
+            if (tid < kSegs * 8) (&st->seg[tid >> 3].ncand)[tid & 7] = 0;
         }
     __syncthreads();  // the next image of a persistent workgroup reuses the LDS
 }
@@ -289,9 +301,14 @@ __device__ __forceinline__ void pct_bracket_wg(uint32_t n, const PctSel &sel, co
 // issue (about 15 vector and 20 scalar instructions per 64 elements with
 // three ranks) next to the read of the channel.
 constexpr int kQueue = 512;  // flushed when four more elements of every lane might not fit
-struct WaveSums {  // per wave of a workgroup, and the place of its candidates
+struct WaveSums {  // per wave of a workgroup
     uint32_t cnt[kThreads / 64][kMaxPctSel], below[kThreads / 64][kMaxPctSel], eqlo[kThreads / 64][kMaxPctSel],
-        eqhi[kThreads / 64][kMaxPctSel], at[kMaxPctSel];
+        eqhi[kThreads / 64][kMaxPctSel];
+    // the places of its candidates: from at[0] on (pieces = 0), or pieces of
+    // the rank's segments, piece p from at[p] on for the workgroup's candidates
+    // first[p] .. first[p + 1] - 1
+    int pieces[kMaxPctSel];
+    uint32_t first[kMaxPctSel][kSegs + 1], at[kMaxPctSel][kSegs];
 };
 template <typename T, int M, bool HEAVY, bool NT>
 __device__ __forceinline__ void pct_collect(const Geo &g, const T *img, const PctSel &sel, void *states,
@@ -319,19 +336,23 @@ __device__ __forceinline__ void pct_collect(const Geo &g, const T *img, const Pc
         width[j] = hv ? hi - lo - 2 : hi - lo;
         below[j] = eqlo[j] = eqhi[j] = cnt[j] = 0;
     }
-    auto put = [&](int j, uint32_t at) {
-        const uint32_t cap = cand.seg_cap();
-        VLG_GLOBAL uint32_t *buf = cand.seg(j, seg);
-        for (uint32_t i = lane; i < cnt[j]; i += 64)
-            if (at + i < cap) buf[at + i] = queue[j][i];
-    };
     auto flush = [&](int j) {
         wave_lds_handoff();
-        uint32_t at = 0;
-        if (lane == 0)
-            at = __hip_atomic_fetch_add(&qstate(states, sel.slot[j])->seg[seg].ncand, cnt[j], __ATOMIC_RELAXED,
-                                        __HIP_MEMORY_SCOPE_AGENT);
-        put(j, __builtin_amdgcn_readfirstlane(at));
+        VLG_GLOBAL PctQ *st = qstate(states, sel.slot[j]);
+        uint32_t done = 0;
+        for (int t = 0; t < cand.nseg; t++) {
+            const int s = (seg + t) & (cand.nseg - 1);
+            uint32_t at = 0, room = 0;
+            if (lane == 0) room = cand.reserve(st, s, cnt[j] - done, at);
+            at = __builtin_amdgcn_readfirstlane(at);
+            room = __builtin_amdgcn_readfirstlane(room);
+            VLG_GLOBAL uint32_t *buf = cand.rank(j) + (size_t)s * cand.seg_cap() + at;
+            for (uint32_t i = lane; i < room; i += 64) buf[i] = queue[j][done + i];
+            done += room;
+            if (done == cnt[j]) break;
+        }
+        if (done < cnt[j] && lane == 0)
+            __hip_atomic_fetch_add(&st->seg[seg].lost, cnt[j] - done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         cnt[j] = 0;
         wave_lds_handoff();
     };
@@ -404,7 +425,8 @@ __device__ __forceinline__ void pct_collect(const Geo &g, const T *img, const Pc
     __syncthreads();
     if ((int)threadIdx.x < M) {
         const int j = (int)threadIdx.x;
-        VLG_GLOBAL PctSeg *st = &qstate(states, sel.slot[j])->seg[seg];
+        VLG_GLOBAL PctQ *q = qstate(states, sel.slot[j]);
+        VLG_GLOBAL PctSeg *st = &q->seg[seg];
         uint32_t t[4] = {0, 0, 0, 0};
         for (int w = 0; w < kThreads / 64; w++) {
             t[0] += sums.cnt[w][j];
@@ -413,19 +435,43 @@ __device__ __forceinline__ void pct_collect(const Geo &g, const T *img, const Pc
             t[3] += sums.eqhi[w][j];
         }
         auto add = [&](VLG_GLOBAL uint32_t *p, uint32_t x) {
-            return x ? __hip_atomic_fetch_add(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+            if (x) __hip_atomic_fetch_add(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         };
-        sums.at[j] = add(&st->ncand, t[0]);
+        // (the place first: the other additions overlap its round trip)
+        uint32_t at = 0, done = t[0] ? cand.reserve(q, seg, t[0], at) : 0u;
         add(&st->below, t[1] - t[2]);
         add(&st->eqlo, t[2]);
         add(&st->eqhi, t[3]);
+        sums.at[j][0] = (uint32_t)seg * cand.seg_cap() + at;
+        int n = 0;
+        if (done < t[0]) {
+            sums.first[j][0] = 0;
+            sums.first[j][n = 1] = done;
+            while (n < cand.nseg && done < t[0]) {
+                const int s = (seg + n) & (cand.nseg - 1);
+                done += cand.reserve(q, s, t[0] - done, at);
+                sums.at[j][n] = (uint32_t)s * cand.seg_cap() + at;
+                sums.first[j][++n] = done;
+            }
+            add(&st->lost, t[0] - done);
+        }
+        sums.pieces[j] = n;
     }
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < M; j++) {
-        uint32_t at = sums.at[j];
-        for (int w = 0; w < wave; w++) at += sums.cnt[w][j];
-        put(j, at);
+        uint32_t w0 = 0;  // this wave's first candidate among the workgroup's
+        for (int w = 0; w < wave; w++) w0 += sums.cnt[w][j];
+        const int pieces = __builtin_amdgcn_readfirstlane(sums.pieces[j]);
+        if (pieces == 0) {  // all in one
+            VLG_GLOBAL uint32_t *buf = cand.rank(j) + sums.at[j][0] + w0;
+            for (uint32_t i = lane; i < cnt[j]; i += 64) buf[i] = queue[j][i];
+        }
+        for (int p = 0; p < pieces; p++) {
+            const uint32_t p0 = sums.first[j][p], a = max(p0, w0), b = min(sums.first[j][p + 1], w0 + cnt[j]);
+            VLG_GLOBAL uint32_t *buf = cand.rank(j) + sums.at[j][p];
+            for (uint32_t i = a + lane; i < b; i += 64) buf[i - p0] = queue[j][i - w0];
+        }
     }
     __syncthreads();  // the next unit of a persistent workgroup reuses the LDS
 }
@@ -455,14 +501,16 @@ __device__ __forceinline__ PctFound pct_found(const VLG_GLOBAL PctQ *st, const C
     // sums over the segments
     const int lane = lane_id();
     uint32_t c = 0, bl = 0, el = 0, eh = 0;
+    bool lost = false;
     if (lane < cand.nseg) {
         const VLG_GLOBAL PctSeg *s = &st->seg[lane];
-        c = s->ncand;
+        c = cand.held(st, lane) + s->lost;
         bl = s->below;
         el = s->eqlo;
         eh = s->eqhi;
+        lost = s->lost != 0;
     }
-    const bool over = __any(c > cand.seg_cap());
+    const bool over = __any(lost);
 #pragma unroll
     for (int d = 1; d < kSegs; d <<= 1) {
         c += __shfl_xor(c, d);
@@ -499,14 +547,14 @@ __device__ __forceinline__ void each_candidate(const VLG_GLOBAL PctQ *st, const 
                                                Fn fn) {
     const uint32_t nthr = blockDim.x, per = (uint32_t)(parts / cand.nseg);
     for (int s = 0; s < cand.nseg; s++) {
-        const uint32_t n = st->seg[s].ncand;
+        const uint32_t n = cand.held(st, s);
         uint32_t i = 0, end = n;
         if (part >= 0) {
             if ((uint32_t)part / per != (uint32_t)s) continue;
             i = (uint32_t)((uint64_t)n * ((uint32_t)part % per) / per);
             end = (uint32_t)((uint64_t)n * ((uint32_t)part % per + 1) / per);
         }
-        const VLG_GLOBAL uint32_t *c = cand.seg(j, s);
+        const VLG_GLOBAL uint32_t *c = cand.rank(j) + (size_t)s * cand.seg_cap();
         i += threadIdx.x;
         for (; i + 7 * nthr < end; i += 8 * nthr) {
             uint32_t v[8];
@@ -726,8 +774,8 @@ __global__ __launch_bounds__(kThreads) void k_pct_collect(Geo g, const T *img, P
     const int64_t n = (int64_t)g.H * g.wpr * 64, chunks = (n + kThreads * 4 - 1) / (kThreads * 4);
     const int64_t per = (chunks + gridDim.x - 1) / gridDim.x * (kThreads * 4);
     const int64_t i0 = (int64_t)blockIdx.x * per, i1 = i0 + per < n ? i0 + per : n;
-    pct_collect_range<T, M, NT>(g, img, sel, states, cand, (int)blockIdx.x & (cand.nseg - 1), i0, i1,
-                                queue[threadIdx.x >> 6], sums);
+    const int seg = (int)((blockIdx.x * 0x9E3779B1u) >> 28) & (cand.nseg - 1);
+    pct_collect_range<T, M, NT>(g, img, sel, states, cand, seg, i0, i1, queue[threadIdx.x >> 6], sums);
 }
 
 // (blockIdx.x: the part, blockIdx.y: the rank)
