@@ -92,7 +92,9 @@ struct PctSeg {
 };
 struct PctQ {  // of one rank
     uint32_t k, lo, hi, mode;
-    uint32_t nlist, pad[27];
+    uint32_t nlist;
+    uint32_t ties;  // the sample holds an end of the bracket kTies times or more
+    uint32_t pad[26];
     PctSeg seg[kSegs];
     uint32_t hist[2048];   // of the candidates' leading digit
     // candidates in the rank's bucket of hist (nlist of them), or, when there
@@ -100,6 +102,7 @@ struct PctQ {  // of one rank
     uint32_t list[kList];
 };
 constexpr uint32_t kCrowded = ~0u;
+constexpr uint32_t kTies = 8;
 static_assert(sizeof(PctQ) <= kPctStateBytes, "percentile state");
 __device__ __forceinline__ VLG_GLOBAL PctQ *qstate(void *states, int slot) {
     return (VLG_GLOBAL PctQ *)((char *)states + (size_t)slot * kPctStateBytes);
@@ -111,10 +114,6 @@ struct Cand {
     int nseg;
     __device__ __forceinline__ uint32_t seg_cap() const { return cap / (uint32_t)nseg; }
     __device__ __forceinline__ VLG_GLOBAL uint32_t *rank(int j) const { return glb(buf) + (size_t)j * cap; }
-    // keys in segment s of a rank
-    __device__ __forceinline__ uint32_t held(const VLG_GLOBAL PctQ *st, int s) const {
-        return min((uint32_t)st->seg[s].ncand, seg_cap());
-    }
     // Places for n keys in segment s: how many it has room for, from its place `at` on.
     __device__ __forceinline__ uint32_t reserve(VLG_GLOBAL PctQ *st, int s, uint32_t n, uint32_t &at) const {
         at = __hip_atomic_fetch_add(&st->seg[s].ncand, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -263,9 +262,10 @@ __device__ __forceinline__ void pct_bracket_wg(uint32_t n, const PctSel &sel, co
     if (tid < sel.n) {
         const int a = 2 * tid, b = a + 1;
         VLG_GLOBAL PctQ *st = qstate(states, sel.slot[tid]);
-        uint32_t mode = PCT_DIRECT, lo = 0, hi = 0;
+        uint32_t mode = PCT_DIRECT, lo = 0, hi = 0, ties = 0;
         if (!direct) {
             mode = PCT_LIGHT;
+            ties = max(teq[a], teq[b]) >= kTies;
             lo = tkey[a];
             hi = tkey[b];
             int rl, rh;
@@ -283,6 +283,7 @@ __device__ __forceinline__ void pct_bracket_wg(uint32_t n, const PctSel &sel, co
         st->hi = hi;
         st->mode = mode;
         st->nlist = 0;
+        st->ties = ties;
     }
     if (!direct)
         for (int q = 0; q < sel.n; q++) {
@@ -488,23 +489,34 @@ __device__ __forceinline__ void pct_collect_range(const Geo &g, const T *img, co
     else pct_collect<T, M, false, NT>(g, img, sel, states, cand, seg, i0, i1, queue, sums);
 }
 
-// Where a rank stands after the pass (the same in every thread).
+// Where a rank stands after the pass (the same in every thread): a key known
+// already, or rank r among keys - base of `bits` bits, those of the candidates
+// or (rank not bracketed, or too many candidates) the n of the whole channel.
+enum PctOf : uint32_t { PCT_KNOWN = 0, PCT_CANDIDATES, PCT_CHANNEL };
 struct PctFound {
-    bool failed, candidate;  // rank not bracketed (or too many candidates) / rank r of the candidates
+    PctOf of;
     uint32_t key, r, base, bits, n;
+    bool ties;      // equal values are expected (hist_add)
+    uint32_t held;  // keys in the lane's segment
 };
-__device__ __forceinline__ PctFound pct_found(const VLG_GLOBAL PctQ *st, const Cand &cand) {
-    const bool heavy = st->mode == PCT_HEAVY;
-    const uint32_t lo = st->lo, hi = st->hi, width = heavy ? hi - lo - 2 : hi - lo, k = st->k;
-    PctFound f{true, false, lo, 0, heavy ? lo + 1 : lo, 0, 0};
-    if (st->mode == PCT_DIRECT) return f;
+template <typename T>
+__device__ __forceinline__ PctFound pct_found(const Geo &g, const VLG_GLOBAL PctQ *st, const Cand &cand) {
+    // (scalars: what follows from them is the same in every lane)
+    auto scalar = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); };
+    const uint32_t mode = scalar(st->mode), lo = scalar(st->lo), hi = scalar(st->hi), k = scalar(st->k);
+    const bool heavy = mode == PCT_HEAVY;
+    const uint32_t width = heavy ? hi - lo - 2 : hi - lo;
+    const PctFound channel{PCT_CHANNEL, 0, k, 0, 8 * sizeof(T), pixels_of(g), true, 0};
+    if (mode == PCT_DIRECT) return channel;
+    PctFound f{PCT_KNOWN, lo, 0, heavy ? lo + 1 : lo, 0, 0, scalar(st->ties) != 0, 0};
     // sums over the segments
     const int lane = lane_id();
     uint32_t c = 0, bl = 0, el = 0, eh = 0;
     bool lost = false;
     if (lane < cand.nseg) {
         const VLG_GLOBAL PctSeg *s = &st->seg[lane];
-        c = cand.held(st, lane) + s->lost;
+        f.held = min((uint32_t)s->ncand, cand.seg_cap());
+        c = f.held + s->lost;
         bl = s->below;
         el = s->eqlo;
         eh = s->eqhi;
@@ -518,65 +530,99 @@ __device__ __forceinline__ PctFound pct_found(const VLG_GLOBAL PctQ *st, const C
         el += __shfl_xor(el, d);
         eh += __shfl_xor(eh, d);
     }
-    f.n = __builtin_amdgcn_readfirstlane(c);
-    const uint32_t below = __builtin_amdgcn_readfirstlane(bl), eqlo = __builtin_amdgcn_readfirstlane(el),
-                   eqhi = __builtin_amdgcn_readfirstlane(eh);
+    f.n = scalar(c);
+    const uint32_t below = scalar(bl), eqlo = scalar(el), eqhi = scalar(eh);
     f.bits = width ? 32 - __builtin_clz(width) : 0;
-    if (k < below) return f;
+    if (k < below) return channel;
     f.r = k - below;
-    f.failed = false;
     if (heavy) {
         if (f.r < eqlo) return f;
         f.r -= eqlo;
     }
     if (f.r < f.n) {
-        f.candidate = !over;
-        f.failed = over;
-        return f;
+        f.of = PCT_CANDIDATES;
+        return over ? channel : f;
     }
     f.r -= f.n;
     f.key = hi;
-    f.failed = !heavy || f.r >= eqhi;
-    return f;
+    return heavy && f.r < eqhi ? f : channel;
 }
 
-// This thread's candidates of part `part` of `parts` (a multiple of the
-// segments: slices of one segment each); part < 0: all of them.
-template <typename Fn>
-__device__ __forceinline__ void each_candidate(const VLG_GLOBAL PctQ *st, const Cand &cand, int j, int part, int parts,
-                                               Fn fn) {
-    const uint32_t nthr = blockDim.x, per = (uint32_t)(parts / cand.nseg);
+// This thread's values (keys - f.base) of part `part` of `parts` (for
+// candidates a multiple of the segments: slices of one segment each); part < 0:
+// all of them.
+template <typename T, typename Fn>
+__device__ __forceinline__ void each_value(const PctFound &f, const Geo &g, const T *img_, const Cand &cand, int j,
+                                           int part, int parts, Fn fn) {
+    const uint32_t nthr = blockDim.x;
+    // part `at` of `of` equal parts of n
+    auto cut = [](uint32_t n, uint32_t at, uint32_t of) { return (uint32_t)((uint64_t)n * at / of); };
+    if (f.of == PCT_CHANNEL) {
+        constexpr int U = 4;
+        const VLG_GLOBAL T *img = glb(img_);
+        const uint32_t W = (uint32_t)g.W;
+        const int64_t pitch = (int64_t)g.wpr * 64;
+        uint32_t i = 0, end = f.n;
+        if (part >= 0) {
+            i = cut(f.n, (uint32_t)part, (uint32_t)parts);
+            end = cut(f.n, (uint32_t)part + 1, (uint32_t)parts);
+        }
+        for (i += threadIdx.x; i < end; i += U * nthr) {
+            T v[U];
+#pragma unroll
+            for (int k = 0; k < U; k++) {
+                const uint32_t p = min(i + k * nthr, end - 1), y = p / W;
+                v[k] = img[(int64_t)y * pitch + (p - y * W)];
+            }
+#pragma unroll
+            for (int k = 0; k < U; k++)
+                if (i + k * nthr < end) fn(key_of<T>(v[k]));
+        }
+        return;
+    }
+    const uint32_t per = (uint32_t)(parts / cand.nseg), cap = cand.seg_cap();
     for (int s = 0; s < cand.nseg; s++) {
-        const uint32_t n = cand.held(st, s);
+        const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)f.held, s);
         uint32_t i = 0, end = n;
         if (part >= 0) {
             if ((uint32_t)part / per != (uint32_t)s) continue;
-            i = (uint32_t)((uint64_t)n * ((uint32_t)part % per) / per);
-            end = (uint32_t)((uint64_t)n * ((uint32_t)part % per + 1) / per);
+            i = cut(n, (uint32_t)part % per, per);
+            end = cut(n, (uint32_t)part % per + 1, per);
         }
-        const VLG_GLOBAL uint32_t *c = cand.rank(j) + (size_t)s * cand.seg_cap();
+        const VLG_GLOBAL uint32_t *c = cand.rank(j) + (size_t)s * cap;
         i += threadIdx.x;
         for (; i + 7 * nthr < end; i += 8 * nthr) {
             uint32_t v[8];
 #pragma unroll
             for (int k = 0; k < 8; k++) v[k] = c[i + k * nthr];
 #pragma unroll
-            for (int k = 0; k < 8; k++) fn(v[k]);
+            for (int k = 0; k < 8; k++) fn(v[k] - f.base);
         }
-        for (; i < end; i += nthr) fn(c[i]);
+        for (; i < end; i += nthr) fn(c[i] - f.base);
     }
 }
 
-// Many candidates: the histogram of their leading digit, `parts` workgroups
-// per rank.
-__device__ __forceinline__ void pct_candidate_hist(VLG_GLOBAL PctQ *st, const Cand &cand, int j, int part, int parts,
-                                                   uint32_t *h) {
-    const PctFound f = pct_found(st, cand);
-    if (!f.candidate || f.n <= kFewCandidates) return;
-    const int sh = f.bits > 11 ? (int)f.bits - 11 : 0;
+// Digits of the values (11 bits, 11 and the rest): their low ends.
+__device__ __forceinline__ int digit1(uint32_t bits) { return bits > 11 ? (int)bits - 11 : 0; }
+__device__ __forceinline__ int digit2(uint32_t bits) { return bits > 22 ? (int)bits - 22 : 0; }
+
+// Many values to choose from: the histogram of their leading digit, `parts`
+// workgroups per rank.
+__device__ __forceinline__ bool pct_many(const PctFound &f) {
+    return f.of == PCT_CHANNEL ? f.n > kDirectPixels : f.of == PCT_CANDIDATES && f.n > kFewCandidates;
+}
+template <typename T>
+__device__ __forceinline__ void pct_value_hist(const Geo &g, const T *img, VLG_GLOBAL PctQ *st, const Cand &cand, int j,
+                                               int part, int parts, uint32_t *h) {
+    const PctFound f = pct_found<T>(g, st, cand);
+    if (!pct_many(f)) return;
+    const int sh = digit1(f.bits);
     for (int i = (int)threadIdx.x; i < 2048; i += (int)blockDim.x) h[i] = 0;
     __syncthreads();
-    each_candidate(st, cand, j, part, parts, [&](uint32_t key) { atomicAdd(&h[(key - f.base) >> sh], 1u); });
+    each_value(f, g, img, cand, j, part, parts, [&](uint32_t v) {
+        if (f.of == PCT_CHANNEL) hist_add(h, v >> sh);
+        else atomicAdd(&h[v >> sh], 1u);
+    });
     __syncthreads();
     for (int i = (int)threadIdx.x; i < 2048; i += (int)blockDim.x)
         if (h[i]) __hip_atomic_fetch_add(&st->hist[i], h[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -602,32 +648,29 @@ __device__ __forceinline__ uint32_t pct_bucket(const VLG_GLOBAL uint32_t *hist, 
     r = found[1];
     return found[0];
 }
-// Digits of the candidates (11 bits, 11 and the rest): their low ends.
-__device__ __forceinline__ int digit1(uint32_t bits) { return bits > 11 ? (int)bits - 11 : 0; }
-__device__ __forceinline__ int digit2(uint32_t bits) { return bits > 22 ? (int)bits - 22 : 0; }
-
-// Many candidates: those in the rank's bucket of the leading digit go to the
+// Many values: those in the rank's bucket of the leading digit go to the
 // state's list, `parts` workgroups of kSelThreads per rank.  A bucket of more
 // than the list holds (ties, or keys that crowd into one 2048th of the
 // bracket, as flat regions do) is counted by the next digit instead, and by
 // the last one in pct_refine: one workgroup going over a million such
 // candidates three times made a formula with two ranks at 4096^2 (flat ellipses)
 // take 1.16 ms, which takes 0.35 so; where no bucket is crowded the extra launch
-// costs 5 us per step, 17 in a batch of 128 images.
-__device__ __forceinline__ void pct_list(VLG_GLOBAL PctQ *st, const Cand &cand, int j, int part, int parts, uint32_t *h,
-                                         uint32_t *found) {
-    const PctFound f = pct_found(st, cand);
+// costs 5 us per step, 17 in a batch of 128 images.  A rank that its bracket
+// missed is found in the same launches, over the whole channel.
+template <typename T>
+__device__ __forceinline__ void pct_list(const Geo &g, const T *img, VLG_GLOBAL PctQ *st, const Cand &cand, int j,
+                                         int part, int parts, uint32_t *h, uint32_t *found) {
+    const PctFound f = pct_found<T>(g, st, cand);
     const int sh = digit1(f.bits), sh2 = digit2(f.bits);
-    if (!f.candidate || f.n <= kFewCandidates || sh == 0) return;
+    if (!pct_many(f) || sh == 0) return;
     uint32_t r = f.r;
     const uint32_t bucket = pct_bucket(st->hist, r, h, found);
     if (st->hist[bucket] > (uint32_t)kList) {
         __syncthreads();  // every thread has read found
         for (int i = (int)threadIdx.x; i < 2048; i += kSelThreads) h[i] = 0;
         __syncthreads();
-        each_candidate(st, cand, j, part, parts, [&](uint32_t c) {
-            const uint32_t v = c - f.base;
-            if (v >> sh == bucket) atomicAdd(&h[(v >> sh2) & ((1u << (sh - sh2)) - 1u)], 1u);
+        each_value(f, g, img, cand, j, part, parts, [&](uint32_t v) {
+            if (v >> sh == bucket) hist_add(h, (v >> sh2) & ((1u << (sh - sh2)) - 1u));
         });
         __syncthreads();
         for (int i = (int)threadIdx.x; i < 2048; i += kSelThreads)
@@ -640,13 +683,13 @@ __device__ __forceinline__ void pct_list(VLG_GLOBAL PctQ *st, const Cand &cand, 
     __syncthreads();  // every thread has read found
     if (threadIdx.x == 0) found[0] = 0;
     __syncthreads();
-    each_candidate(st, cand, j, part, parts, [&](uint32_t c) {
-        if ((c - f.base) >> sh != bucket) return;
+    each_value(f, g, img, cand, j, part, parts, [&](uint32_t v) {
+        if (v >> sh != bucket) return;
         const uint32_t at = atomicAdd(&found[0], 1u);
         if (at < 2048)
-            h[at] = c - f.base;
+            h[at] = v;
         else  // (the bucket holds at most kList in all)
-            st->list[__hip_atomic_fetch_add(&st->nlist, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)] = c - f.base;
+            st->list[__hip_atomic_fetch_add(&st->nlist, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)] = v;
     });
     __syncthreads();
     const uint32_t n = found[0] < 2048 ? found[0] : 2048;
@@ -658,21 +701,21 @@ __device__ __forceinline__ void pct_list(VLG_GLOBAL PctQ *st, const Cand &cand, 
 }
 
 // The last digit of a crowded bucket (float32): counted behind the second.
-__device__ __forceinline__ void pct_refine(VLG_GLOBAL PctQ *st, const Cand &cand, int j, int part, int parts,
-                                           uint32_t *h, uint32_t *found) {
+template <typename T>
+__device__ __forceinline__ void pct_refine(const Geo &g, const T *img, VLG_GLOBAL PctQ *st, const Cand &cand, int j,
+                                           int part, int parts, uint32_t *h, uint32_t *found) {
     if (st->nlist != kCrowded) return;
-    const PctFound f = pct_found(st, cand);
+    const PctFound f = pct_found<T>(g, st, cand);
     const int sh = digit1(f.bits), sh2 = digit2(f.bits);
-    if (!f.candidate || f.n <= kFewCandidates || sh2 == 0) return;
+    if (!pct_many(f) || sh2 == 0) return;
     uint32_t r = f.r;
     uint32_t top = pct_bucket(st->hist, r, h, found);
     top = top << (sh - sh2) | pct_bucket(st->list, r, h, found);
     __syncthreads();  // every thread has read found
     for (int i = (int)threadIdx.x; i < 2048; i += kSelThreads) h[i] = 0;
     __syncthreads();
-    each_candidate(st, cand, j, part, parts, [&](uint32_t c) {
-        const uint32_t v = c - f.base;
-        if (v >> sh2 == top) atomicAdd(&h[v & ((1u << sh2) - 1u)], 1u);
+    each_value(f, g, img, cand, j, part, parts, [&](uint32_t v) {
+        if (v >> sh2 == top) hist_add(h, v & ((1u << sh2) - 1u));
     });
     __syncthreads();
     for (int i = (int)threadIdx.x; i < 2048; i += kSelThreads)
@@ -680,18 +723,23 @@ __device__ __forceinline__ void pct_refine(VLG_GLOBAL PctQ *st, const Cand &cand
     __syncthreads();  // h and found are rewritten for the next image
 }
 
-// The rank's value, one workgroup of kSelThreads: among the listed candidates
-// (many), all candidates (few), an end of the bracket, or the whole channel
-// (direct, or the bracket missed).
+// The rank's value, one workgroup of kSelThreads: from what the launches above
+// counted or listed (spread: they ran, and there were many values), among all
+// values (few), or an end of the bracket.
 template <typename T>
-__device__ __forceinline__ void pct_pick_wg(const Geo &g, const T *img_, VLG_GLOBAL PctQ *st, const Cand &cand, int j,
-                                            VLG_GLOBAL float *result, uint32_t *h, uint32_t *found) {
+__device__ __forceinline__ void pct_pick_wg(const Geo &g, const T *img, VLG_GLOBAL PctQ *st, const Cand &cand, int j,
+                                            bool spread, VLG_GLOBAL float *result, uint32_t *h, uint32_t *found) {
     const int tid = (int)threadIdx.x;
-    const PctFound f = pct_found(st, cand);
-    const bool many = f.candidate && f.n > kFewCandidates;
+    PctFound f = pct_found<T>(g, st, cand);
+    if (f.of == PCT_CHANNEL && f.n <= kDirectPixels && f.n > 0) {
+        // no sample: ties when a wave's first pixels are mostly equal
+        const uint32_t W = (uint32_t)g.W, i = min((uint32_t)tid * (f.n / kSelThreads + 1), f.n - 1), y = i / W;
+        const uint32_t v = key_of<T>(glb(img)[(int64_t)y * g.wpr * 64 + (i - y * W)]);
+        f.ties = __builtin_amdgcn_readfirstlane(__syncthreads_or(__popcll(__ballot(v == (uint32_t)__builtin_amdgcn_readfirstlane((int)v))) > 8));
+    }
     uint32_t key = f.key;
-    // the rank r value of bits-bit values, 11 bits at a time from the top,
-    // over what each(fn) calls fn(value) for
+    // the rank r value of bits-bit values, 11 bits at a time from the top, over
+    // what each(fn) calls fn(value) for
     auto radix = [&](uint32_t bits, uint32_t r, auto each) {
         uint32_t pre = 0;
         int sh = (int)bits;
@@ -701,9 +749,16 @@ __device__ __forceinline__ void pct_pick_wg(const Geo &g, const T *img_, VLG_GLO
             __syncthreads();
             for (int i = tid; i < 2048; i += kSelThreads) h[i] = 0;
             __syncthreads();
-            each([&](uint32_t v) {
-                if ((sh < 32 ? v >> sh : 0u) == want) atomicAdd(&h[(v >> ns) & dm], 1u);
-            });
+            // (two loops: the time of one workgroup is also that of fetching its code)
+            auto in = [&](uint32_t v) { return (sh < 32 ? v >> sh : 0u) == want; };
+            if (f.ties)
+                each([&](uint32_t v) {
+                    if (in(v)) hist_add(h, (v >> ns) & dm);
+                });
+            else
+                each([&](uint32_t v) {
+                    if (in(v)) atomicAdd(&h[(v >> ns) & dm], 1u);
+                });
             __syncthreads();
             if (tid < 64) {
                 uint32_t rr = r;
@@ -714,16 +769,13 @@ __device__ __forceinline__ void pct_pick_wg(const Geo &g, const T *img_, VLG_GLO
                 }
             }
             __syncthreads();
-            pre |= found[0] << ns;
+            pre |= (uint32_t)__builtin_amdgcn_readfirstlane((int)found[0]) << ns;
             r = found[1];
             sh = ns;
         }
         return pre;
     };
-    auto all = [&](auto fn) {
-        each_candidate(st, cand, j, -1, cand.nseg, [&](uint32_t c) { fn(c - f.base); });
-    };
-    if (many) {
+    if (spread && pct_many(f)) {
         const int sh = digit1(f.bits), sh2 = digit2(f.bits);
         uint32_t r = f.r, v = pct_bucket(st->hist, r, h, found);
         const uint32_t n = st->nlist;
@@ -736,18 +788,8 @@ __device__ __forceinline__ void pct_pick_wg(const Geo &g, const T *img_, VLG_GLO
                 });
         }
         key = f.base + v;
-    } else if (f.candidate) {
-        key = f.base + radix(f.bits, f.r, all);
-    } else if (f.failed) {
-        const VLG_GLOBAL T *img = glb(img_);
-        const uint32_t n = pixels_of(g), W = (uint32_t)g.W;
-        const int64_t pitch = (int64_t)g.wpr * 64;
-        key = radix(sizeof(T) == 4 ? 32 : 16, st->k, [&](auto fn) {
-            for (uint32_t p = tid; p < n; p += kSelThreads) {
-                const uint32_t y = p / W;
-                fn(key_of<T>(img[(int64_t)y * pitch + (p - y * W)]));
-            }
-        });
+    } else if (f.of != PCT_KNOWN) {
+        key = f.base + radix(f.bits, f.r, [&](auto fn) { each_value(f, g, img, cand, j, -1, 1, fn); });
     }
     if (tid == 0) *result = value_of<T>(key);
     __syncthreads();  // h and found are rewritten for the next image
@@ -779,30 +821,34 @@ __global__ __launch_bounds__(kThreads) void k_pct_collect(Geo g, const T *img, P
 }
 
 // (blockIdx.x: the part, blockIdx.y: the rank)
-__global__ __launch_bounds__(kSelThreads) void k_pct_candidates(PctSel sel, void *states, Cand cand) {
+template <typename T>
+__global__ __launch_bounds__(kSelThreads) void k_pct_candidates(Geo g, const T *img, PctSel sel, void *states,
+                                                                Cand cand) {
     __shared__ uint32_t h[2048];
     const int j = (int)blockIdx.y;
-    pct_candidate_hist(qstate(states, sel.slot[j]), cand, j, (int)blockIdx.x, (int)gridDim.x, h);
+    pct_value_hist(g, img, qstate(states, sel.slot[j]), cand, j, (int)blockIdx.x, (int)gridDim.x, h);
 }
 
-__global__ __launch_bounds__(kSelThreads) void k_pct_list(PctSel sel, void *states, Cand cand) {
+template <typename T>
+__global__ __launch_bounds__(kSelThreads) void k_pct_list(Geo g, const T *img, PctSel sel, void *states, Cand cand) {
     __shared__ uint32_t h[2048], found[2];
     const int j = (int)blockIdx.y;
-    pct_list(qstate(states, sel.slot[j]), cand, j, (int)blockIdx.x, (int)gridDim.x, h, found);
+    pct_list(g, img, qstate(states, sel.slot[j]), cand, j, (int)blockIdx.x, (int)gridDim.x, h, found);
 }
 
-__global__ __launch_bounds__(kSelThreads) void k_pct_refine(PctSel sel, void *states, Cand cand) {
+template <typename T>
+__global__ __launch_bounds__(kSelThreads) void k_pct_refine(Geo g, const T *img, PctSel sel, void *states, Cand cand) {
     __shared__ uint32_t h[2048], found[2];
     const int j = (int)blockIdx.y;
-    pct_refine(qstate(states, sel.slot[j]), cand, j, (int)blockIdx.x, (int)gridDim.x, h, found);
+    pct_refine(g, img, qstate(states, sel.slot[j]), cand, j, (int)blockIdx.x, (int)gridDim.x, h, found);
 }
 
 template <typename T>
 __global__ __launch_bounds__(kSelThreads) void k_pct_pick(Geo g, const T *img, PctSel sel, void *states, Cand cand,
-                                                          float *results) {
+                                                          bool spread, float *results) {
     __shared__ uint32_t h[2048], found[2];
     const int j = (int)blockIdx.x;
-    pct_pick_wg<T>(g, img, qstate(states, sel.slot[j]), cand, j, glb(results) + sel.slot[j], h, found);
+    pct_pick_wg<T>(g, img, qstate(states, sel.slot[j]), cand, j, spread, glb(results) + sel.slot[j], h, found);
 }
 
 // ---- batches: states, results and candidates live in each image's workspace
@@ -846,30 +892,36 @@ __global__ __launch_bounds__(kThreads) void kb_pct_collect(BatchArgs a, int chan
 }
 
 // (blockIdx.y: the rank, blockIdx.z: the part)
-__global__ __launch_bounds__(kSelThreads) void kb_pct_candidates(BatchArgs a, PctSel sel) {
+template <typename T>
+__global__ __launch_bounds__(kSelThreads) void kb_pct_candidates(BatchArgs a, int chan, PctSel sel) {
     __shared__ uint32_t h[2048];
     const int j = (int)blockIdx.y;
     VLG_BATCH_LOOP(a) {
         VLG_BATCH_IMG(a)
-        pct_candidate_hist(qstate(d.ws + d.off_pctst, sel.slot[j]), bcand(d), j, (int)blockIdx.z, (int)gridDim.z, h);
+        pct_value_hist(d.g, bchan<T>(d, chan), qstate(d.ws + d.off_pctst, sel.slot[j]), bcand(d), j, (int)blockIdx.z,
+                       (int)gridDim.z, h);
     }
 }
 
-__global__ __launch_bounds__(kSelThreads) void kb_pct_refine(BatchArgs a, PctSel sel) {
+template <typename T>
+__global__ __launch_bounds__(kSelThreads) void kb_pct_list(BatchArgs a, int chan, PctSel sel) {
     __shared__ uint32_t h[2048], found[2];
     const int j = (int)blockIdx.y;
     VLG_BATCH_LOOP(a) {
         VLG_BATCH_IMG(a)
-        pct_refine(qstate(d.ws + d.off_pctst, sel.slot[j]), bcand(d), j, (int)blockIdx.z, (int)gridDim.z, h, found);
+        pct_list(d.g, bchan<T>(d, chan), qstate(d.ws + d.off_pctst, sel.slot[j]), bcand(d), j, (int)blockIdx.z,
+                 (int)gridDim.z, h, found);
     }
 }
 
-__global__ __launch_bounds__(kSelThreads) void kb_pct_list(BatchArgs a, PctSel sel) {
+template <typename T>
+__global__ __launch_bounds__(kSelThreads) void kb_pct_refine(BatchArgs a, int chan, PctSel sel) {
     __shared__ uint32_t h[2048], found[2];
     const int j = (int)blockIdx.y;
     VLG_BATCH_LOOP(a) {
         VLG_BATCH_IMG(a)
-        pct_list(qstate(d.ws + d.off_pctst, sel.slot[j]), bcand(d), j, (int)blockIdx.z, (int)gridDim.z, h, found);
+        pct_refine(d.g, bchan<T>(d, chan), qstate(d.ws + d.off_pctst, sel.slot[j]), bcand(d), j, (int)blockIdx.z,
+                   (int)gridDim.z, h, found);
     }
 }
 
@@ -879,7 +931,7 @@ __global__ __launch_bounds__(kSelThreads) void kb_pct_pick(BatchArgs a, int chan
     const int j = (int)blockIdx.y;
     VLG_BATCH_LOOP(a) {
         VLG_BATCH_IMG(a)
-        pct_pick_wg<T>(d.g, bchan<T>(d, chan), qstate(d.ws + d.off_pctst, sel.slot[j]), bcand(d), j,
+        pct_pick_wg<T>(d.g, bchan<T>(d, chan), qstate(d.ws + d.off_pctst, sel.slot[j]), bcand(d), j, true,
                        glb((float *)(d.ws + d.off_pct)) + sel.slot[j], h, found);
     }
 }
@@ -913,11 +965,11 @@ hipError_t percentile_sampled(hipStream_t s, const Geo &g, const T *img, const P
     const bool many = npix > kDirectPixels && cand.cap > kFewCandidates;
     if (many) {
         const dim3 parts(cand.nseg > 1 ? 4 * cand.nseg : 8, sel.n);
-        k_pct_candidates<<<parts, kSelThreads, 0, s>>>(sel, states, cand);
-        k_pct_list<<<parts, kSelThreads, 0, s>>>(sel, states, cand);
-        if (F32) k_pct_refine<<<parts, kSelThreads, 0, s>>>(sel, states, cand);
+        k_pct_candidates<T><<<parts, kSelThreads, 0, s>>>(g, img, sel, states, cand);
+        k_pct_list<T><<<parts, kSelThreads, 0, s>>>(g, img, sel, states, cand);
+        if (F32) k_pct_refine<T><<<parts, kSelThreads, 0, s>>>(g, img, sel, states, cand);
     }
-    k_pct_pick<T><<<sel.n, kSelThreads, 0, s>>>(g, img, sel, states, cand, results);
+    k_pct_pick<T><<<sel.n, kSelThreads, 0, s>>>(g, img, sel, states, cand, many, results);
     return hipGetLastError();
 }
 
@@ -935,9 +987,9 @@ hipError_t b_percentile_sampled(hipStream_t s, const BatchArgs &one, int64_t tot
     VLG_BY_RANKS(sel.n, K)
 #undef K
     const dim3 parts(g1, sel.n, 4);
-    kb_pct_candidates<<<parts, kSelThreads, 0, s>>>(one, sel);
-    kb_pct_list<<<parts, kSelThreads, 0, s>>>(one, sel);
-    if (F32) kb_pct_refine<<<parts, kSelThreads, 0, s>>>(one, sel);
+    kb_pct_candidates<T><<<parts, kSelThreads, 0, s>>>(one, chan, sel);
+    kb_pct_list<T><<<parts, kSelThreads, 0, s>>>(one, chan, sel);
+    if (F32) kb_pct_refine<T><<<parts, kSelThreads, 0, s>>>(one, chan, sel);
     kb_pct_pick<T><<<dim3(g1, sel.n), kSelThreads, 0, s>>>(one, chan, sel);
     return hipGetLastError();
 }

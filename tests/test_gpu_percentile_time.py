@@ -1,14 +1,15 @@
-"""Percentiles of channels whose candidates lie in a few rows of each period:
-the same values as a sort gives, in at most three times the time of noise of
-the same size (one workgroup selecting over the whole channel takes over a
-hundred times as long)."""
+"""Percentiles of channels whose candidates lie in a few rows of each period, and
+of channels made so that every bracket misses its rank or holds most pixels:
+the same values as a sort gives, in at most three (periodic) or eight times
+the time of noise of the same size (one workgroup selecting over the whole
+channel takes over a hundred times as long)."""
 import time
 
 import numpy as np
 import pytest
 
 import paper_2010_07284_amd as vlg
-from tests.test_gpu_percentile_sampled import check
+from tests.test_gpu_percentile_sampled import check, sampled_places
 
 pytestmark = pytest.mark.gpu
 
@@ -52,3 +53,23 @@ def test_periodic_rows(shape, dtype):
         check(img, (0.5, 0.95, 0.86))
         for qs, most in limit.items():
             assert time_of(img, qs) < most, (period, qs)
+
+
+@pytest.mark.parametrize("dtype", ["float32", "uint16"])
+@pytest.mark.parametrize("shape", [(4096, 4096), (1999, 3001)])
+def test_channels_that_the_sample_misjudges(shape, dtype):
+    rng = np.random.default_rng(shape)
+    n, at = shape[0] * shape[1], sampled_places(shape[0] * shape[1])
+    noise = rng.random(shape, dtype=np.float32)
+    qs = (0.5, 0.9)
+    limit = 8 * time_of(typed(noise, dtype), qs)
+    missed = noise.reshape(-1).copy()
+    missed[at] = 0.25 + 0.0001 * rng.random(len(at), dtype=np.float32)
+    flooded = (0.5 + 0.001 * noise).reshape(-1)  # one place in the order of the samples, most pixels in their bracket
+    flooded[at] = rng.random(len(at), dtype=np.float32)
+    ties = np.where(noise < 0.3, noise, np.float32(0.5)).reshape(-1)
+    ties[at] = rng.random(len(at), dtype=np.float32)
+    for name, x in (("missed", missed), ("flooded", flooded), ("ties", ties)):
+        img = typed(x.reshape(shape), dtype)
+        check(img, qs)
+        assert time_of(img, qs) < limit, name
