@@ -8,19 +8,20 @@
 // Sampled select (float32 and uint16): one workgroup takes 16384 samples and
 // brackets every rank between two sample keys, five standard deviations of
 // the sampling wide; one pass over the channel counts the keys below each
-// bracket and collects those inside (1 to 4% of the channel per rank); a last
-// kernel finds the rank's key among the collected ones.  Exact: when the
-// bracket missed its rank, or too many keys fell inside, the last kernel
-// selects over the whole channel by itself.  A bracket that one value fills (a
-// constant background) counts that value instead of collecting it.
+// bracket and collects those inside (1 to 4% of the channel per rank); the
+// rank's key is then found among the collected ones.  Exact: when the bracket
+// missed its rank, or too many keys fell inside, the same launches go over the
+// whole channel instead.  A bracket that one value fills (a constant
+// background) counts that value instead of collecting it.
 // It reads the channel once where a radix select reads it three times (uint16:
 // twice).  One rank of a 4096^2 float32 channel: 109 -> 52 us (the pass itself
 // 16 us, 4.1 TB/s); three ranks of 128 images of 0.16 Gpixel: 585 -> 320 us
 // (the pass 186 us, 3.5 TB/s, the gather of samples 43 us).
 //
-// Radix select (uint8, one pass; and plans without room for candidates): each
-// pass histograms one digit of the keys that agree with the digits chosen so
-// far, then one workgroup finds the bucket holding the rank.
+// Radix select (uint8, one pass; four ranks of a large uint16 channel; plans
+// without room for candidates): each pass histograms one digit of the keys that
+// agree with the digits chosen so far, then one workgroup finds the bucket
+// holding the rank.
 #include "dev.h"
 
 namespace vlg {
@@ -1257,7 +1258,13 @@ __global__ __launch_bounds__(kThreads) void kb_pct_select(BatchArgs a, PctSel se
 hipError_t launch_percentile(hipStream_t s, const Geo &g, const void *chan, int dtype, const PctSel &sel,
                              void *states, float *results, uint32_t *cand, uint32_t cap) {
     if (sel.n < 1 || sel.n > kMaxPctSel) return hipErrorInvalidValue;
-    if (dtype != 1 && g.nwords > 0 && cap > 0) {
+    // Four ranks of a large uint16 channel keep the radix select: its two passes
+    // serve four ranks as fast as one, the sampled pass does not.  us, radix and
+    // sampled, a formula with four ranks at 2048^2: 107 / 96 (middle ranks) and
+    // 111 / 99 (two of them near the ends); at 3000 x 3100: 131 / 136, 135 / 147;
+    // at 5000 x 5100: 158 / 163, 162 / 179; three ranks there: 156 / 141.
+    const bool radix = dtype == 2 && sel.n == 4 && (int64_t)g.H * g.W > (1 << 22);
+    if (dtype != 1 && g.nwords > 0 && cap > 0 && !radix) {
         const Cand c{cand, cap, 1};
         return dtype == 2 ? percentile_sampled(s, g, (const uint16_t *)chan, sel, states, results, c)
                           : percentile_sampled(s, g, (const float *)chan, sel, states, results, c);

@@ -29,9 +29,9 @@ def channel(kind, shape, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["float32", "uint16"])
-@pytest.mark.parametrize("kind,shape", [("spread", (5200, 5000)), ("ends", (5200, 5000)), ("levels", (4099, 4200)),
-                                        ("spread", (8192, 8192))])
+@pytest.mark.parametrize("kind,shape", [("spread", (5200, 5000)), ("ends", (5200, 5000)), ("levels", (4099, 4200))])
 def test_open_brackets(kind, shape, dtype):
     img = channel(kind, shape, dtype)
-    check(img, TOP)
-    check(img, LOW)
+    for qs in (TOP, LOW):  # (four ranks of a large uint16 image take the radix select)
+        check(img, qs[:2])
+        check(img, qs[2:])
