@@ -464,7 +464,7 @@ __device__ __forceinline__ void ccl_merge_tile(const Geo &g, const CclGeo &q, co
     for (int i = lane; i < n; i += 64) {
         const int2 pr = pairs[i];
         unions++;
-        tries += g_unite(glb(a.par), pr.x, pr.y, gd.cap, ok);
+        tries += g_unite<true>(glb(a.par), pr.x, pr.y, gd.cap, ok);
     }
     guard_report(gd, ok);
     wave_lds_handoff();  // the list is rewritten by the wave's next tile

@@ -156,20 +156,23 @@ __device__ __forceinline__ bool lds_unite(int *L, int a, int b, int cap) {
 // of tiles whose components join left to right (a corridor crossing the
 // image) into a chain as long as the row, because every tile hooks under its
 // left neighbour at the same time; pseudo-random priorities keep the expected
-// depth logarithmic.  (Two rounds of mixing: neighbouring tiles' nodes are a
-// fixed stride apart, and after one multiplication by the golden ratio alone
-// their priorities ran monotonically over whole rows of tiles at a stride of
-// 144: lines across a 64 x 60000 image were chains of over 192 nodes, 16 now.)
-// Node 0 (meets the seeds) has the smallest priority and
+// depth logarithmic.  Node 0 (meets the seeds) has the smallest priority and
 // is never hooked.  Plain loads and stores may see stale values (the L2 of
 // one XCD is not coherent with another's within a kernel); that costs
 // retries, never correctness: every value ever stored in P[x] is an ancestor
 // of x, sets only grow, and a hook is a compare-and-swap that succeeds only
 // on a current root and otherwise hands back the current parent, which is
 // then united in turn.
+// MIXED (images): the ids are of nodes, a fixed stride apart in neighbouring
+// tiles, and after one multiplication by the golden ratio alone their priorities
+// ran monotonically over whole rows of tiles at a stride of 144: lines across
+// a 64 x 60000 image were chains of over 192 nodes, 16 with a second round of
+// mixing.  Volumes (ids of blocks, tiles 64 apart) keep one round: merging a coin
+// mask of 256^3 takes 109 us with it, 170 with two.
+template <bool MIXED>
 __device__ __forceinline__ uint32_t uf_prio(int x) {
-    uint32_t h = (uint32_t)x * 0x9E3779B1u;  // odd multipliers and xor-shifts: a bijection, 0 stays 0
-    h = (h ^ (h >> 15)) * 0x85EBCA77u;
+    uint32_t h = (uint32_t)x * 0x9E3779B1u;  // odd multipliers and xor-shifts: bijections, 0 stays 0
+    if (MIXED) h = (h ^ (h >> 15)) * 0x85EBCA77u;
     return h ^ (h >> 16);
 }
 
@@ -195,6 +198,7 @@ __device__ __forceinline__ bool g_find2(VLG_GLOBAL int *P, int &a, int &b, int &
 
 // Unite a and b; returns the number of hook attempts, and clears ok when the
 // walk used up `cap` rounds (finds and hooks together) before it finished.
+template <bool MIXED>
 __device__ int g_unite(VLG_GLOBAL int *P, int a, int b, int cap, bool &ok) {
     int tries = 0, budget = cap;
     while (true) {
@@ -204,7 +208,7 @@ __device__ int g_unite(VLG_GLOBAL int *P, int a, int b, int cap, bool &ok) {
             return tries;
         }
         if (a == b) return tries;
-        if (uf_prio(a) < uf_prio(b)) {
+        if (uf_prio<MIXED>(a) < uf_prio<MIXED>(b)) {
             const int t = a;
             a = b;
             b = t;

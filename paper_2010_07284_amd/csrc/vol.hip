@@ -435,7 +435,7 @@ __global__ __launch_bounds__(kV3Threads) void k_v3_merge(Geo g, VlGeo q, MRef b,
         n -= cnt;
         if (lane < cnt) {
             const int2 pr = pairs[wave][n + lane];
-            g_unite(par, pr.x, pr.y, gd.cap, ok);
+            g_unite<false>(par, pr.x, pr.y, gd.cap, ok);
         }
         wave_lds_handoff();
     };
