@@ -116,6 +116,38 @@ __device__ __forceinline__ int node_root(const VLG_GLOBAL int32_t *par, int id, 
     return id;
 }
 
+// The roots of id[0 .. N) by walks in lockstep, so that their loads overlap
+// (entries that are done load their root again).
+template <int N>
+__device__ __forceinline__ void node_roots(const VLG_GLOBAL int32_t *par, int (&id)[N], int cap, bool &ok) {
+    int p[N];
+#pragma unroll
+    for (int j = 0; j < N; j++) p[j] = par[id[j]];
+    for (int it = 0;; it++) {
+        bool done = true;
+#pragma unroll
+        for (int j = 0; j < N; j++) done &= p[j] == id[j];
+        if (done) break;
+        if (it >= cap) {
+            ok = false;
+            break;
+        }
+#pragma unroll
+        for (int j = 0; j < N; j++) {
+            id[j] = p[j];
+            p[j] = par[p[j]];
+        }
+    }
+}
+
+// x without its n lowest set bits
+template <int N>
+__device__ __forceinline__ uint64_t drop_bits(uint64_t x) {
+#pragma unroll
+    for (int j = 0; j < N; j++) x &= x - 1;
+    return x;
+}
+
 // Union of a and b on the LDS forest (L[x] <= x, a root is the smallest entry
 // of its set).  Both walks advance together, one path-halving step per round,
 // so their LDS latencies overlap; once both reach roots the larger root is

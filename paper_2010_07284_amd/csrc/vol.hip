@@ -572,29 +572,56 @@ __global__ __launch_bounds__(kV3Threads) void k_v3_canon(Geo g, VlGeo q, MRef b,
     VLG_GLOBAL int32_t *canon = glb(canon_);
     const int row0 = vl_id(q, t.tz * 8 + (lane >> 3), t.ty * 8 + (lane & 7), t.tx * 64);
     bool ok = true;
+    // this wave's runs of each row, four at a time: their walks overlap
     uint64_t st = m.starts;
-    for (int k = 0; __any(st != 0); st &= st - 1, k++) {
-        const bool on = st && (k & (kV3Waves - 1)) == wave;
-        int r = -1, v = 0;
-        if (on) {
-            const int id = row0 + __builtin_ctzll(st);
-            r = node_root(par, id, par[id], gd.cap, ok);
-            v = canon[id];
-            if (r == id) r = -1;
-        }
-        // one atomicMin per distinct root of the wave, and none when the root
-        // already holds a smaller index
-        uint64_t pending = __ballot(r >= 0);
-        while (pending) {
-            const int leader = __builtin_ctzll(pending);  // wave-uniform
-            const int r0 = __builtin_amdgcn_readlane(r, leader);
-            const bool same = r == r0;
-            pending &= ~__ballot(same);
-            int least = same ? v : 0x7fffffff;
+    for (int i = 0; i < wave; i++) st &= st - 1;
+    while (__any(st != 0)) {
+        int id[4], r[4], v[4], c[4];
+        bool on[4];
 #pragma unroll
-            for (int off = 32; off > 0; off >>= 1) least = min(least, __shfl_xor(least, off));
-            if (lane == leader && least < __hip_atomic_load(&canon[r0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-                __hip_atomic_fetch_min(&canon[r0], least, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int j = 0; j < 4; j++) {
+            on[j] = st != 0;
+            id[j] = r[j] = on[j] ? row0 + __builtin_ctzll(st) : row0;
+            st = drop_bits<kV3Waves>(st);
+        }
+#pragma unroll
+        for (int j = 0; j < 4; j++) v[j] = on[j] ? canon[id[j]] : 0;
+#pragma unroll
+        for (int j = 1; j < 4; j++)
+            if (!on[j]) r[j] = r[0];
+        if (on[0]) node_roots(par, r, gd.cap, ok);
+#pragma unroll
+        for (int j = 0; j < 4; j++) on[j] &= r[j] != id[j];
+#pragma unroll
+        for (int j = 3; j > 0; j--)  // neighbours of one root together
+            if (on[j] && on[j - 1] && r[j] == r[j - 1]) {
+                v[j - 1] = min(v[j - 1], v[j]);
+                on[j] = false;
+            }
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            c[j] = on[j] ? __hip_atomic_load(&canon[r[j]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+        }
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            // one atomicMin for all of the wave's runs of one root (a giant
+            // component would otherwise serialise every wave on one address),
+            // none where the root already holds a smaller index; after two
+            // roots every lane by itself
+            uint64_t pending = __ballot(on[j] && v[j] < c[j]);
+            for (int t = 0; t < 2 && pending; t++) {
+                const int leader = __builtin_ctzll(pending);  // wave-uniform
+                const int r0 = __builtin_amdgcn_readlane(r[j], leader);
+                const bool same = on[j] && r[j] == r0;
+                pending &= ~__ballot(same);
+                int least = same ? v[j] : 0x7fffffff;
+#pragma unroll
+                for (int off = 32; off > 0; off >>= 1) least = min(least, __shfl_xor(least, off));
+                if (lane == leader && least < __hip_atomic_load(&canon[r0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                    __hip_atomic_fetch_min(&canon[r0], least, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            if ((pending >> lane) & 1)
+                __hip_atomic_fetch_min(&canon[r[j]], v[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
     guard_report(gd, ok);
@@ -617,10 +644,24 @@ __global__ __launch_bounds__(kV3Threads) void k_v3_labels(Geo g, VlGeo q, MRef b
         const VRow m = vl_row(vm, lane);
         const int row0 = vl_id(q, t.tz * 8 + (lane >> 3), t.ty * 8 + (lane & 7), t.tx * 64);
         uint64_t st = m.starts;
-        for (int k = 0; st; st &= st - 1, k++) {
-            if ((k & (kV3Waves - 1)) != wave) continue;
-            const int s = __builtin_ctzll(st), id = row0 + s;
-            V[lane * 65 + s] = glb(canon)[node_root(glb(par_), id, glb(par_)[id], gd.cap, ok)];
+        for (int i = 0; i < wave; i++) st &= st - 1;
+        while (st) {  // four runs at a time: their walks overlap
+            int at[4], r[4];
+            int n = 0;
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                at[j] = st ? __builtin_ctzll(st) : at[0];
+                n += st != 0;
+                r[j] = row0 + at[j];
+                st = drop_bits<kV3Waves>(st);
+            }
+            node_roots(glb(par_), r, gd.cap, ok);
+            int v[4];
+#pragma unroll
+            for (int j = 0; j < 4; j++) v[j] = glb(canon)[r[j]];
+#pragma unroll
+            for (int j = 0; j < 4; j++)
+                if (j < n) V[lane * 65 + at[j]] = v[j];
         }
     }
     __syncthreads();
