@@ -471,16 +471,27 @@ __device__ __forceinline__ void ccl_merge_tile(const Geo &g, const CclGeo &q, co
 }
 
 // ------------------------------------------------------------------ flags
+// Set a seed bit of the lane's root; the active lanes with the first one's root
+// (a large component's) once together.
+__device__ __forceinline__ void flag_or_wave(VLG_GLOBAL uint8_t *flag, int root, uint32_t bit) {
+    const int r0 = __builtin_amdgcn_readfirstlane(root);
+    const uint64_t same = __ballot(root == r0);
+    if (root != r0 || lane_id() == __builtin_ctzll(same)) flag_or(flag, root, bit);
+}
+
 // Carry the first user's seed flags of a tile's nodes to their roots (one
-// wave per tile).
+// wave per tile), and point every node at its root: each user's reseed and
+// gather walk from there.  (Other waves may meet either parent on their way,
+// both lead to the root.)
 __device__ __forceinline__ void ccl_flag_tile(const CclGeo &q, const CclArrays &a, int tile, const LoopGuard &gd) {
-    const VLG_GLOBAL int32_t *par = glb(a.par);
+    VLG_GLOBAL int32_t *par = glb(a.par);
     const int n = (int)glb(a.cnt)[tile], id0 = tile * q.np + 1;
     bool ok = true;
     for (int k = lane_id(); k < n; k += 64) {
-        if (!(glb(a.flag)[id0 + k] & 2)) continue;
-        const int root = node_root(par, id0 + k, par[id0 + k], gd.cap, ok);
-        if (root != id0 + k) flag_or(glb(a.flag), root, 2u);
+        const uint32_t flag = glb(a.flag)[id0 + k];
+        const int p = par[id0 + k], root = node_root(par, id0 + k, p, gd.cap, ok);
+        if (root != p) par[id0 + k] = root;
+        if ((flag & 2) && root != id0 + k) flag_or_wave(glb(a.flag), root, 2u);
     }
     guard_report(gd, ok);
 }
@@ -529,13 +540,28 @@ __device__ __forceinline__ void ccl_reseed_group(const Geo &g, const CclGeo &q, 
     const Row m = rm.row(lane);
     const uint64_t ss = starts_of(m.conn, rs.row(lane).fg());
     const VLG_GLOBAL uint16_t *lab = glb(a.lab) + (int64_t)by * g.BW + tx * 64;
-    int k = 0;
-    for (uint64_t st = m.starts; st; st &= st - 1, k++) {
-        const int s = __builtin_ctzll(st);
-        if ((k & 3) != wave || !((ss >> s) & 1)) continue;
-        const uint32_t lb = lab[k], x = lb & 0x7FF;
-        uint32_t *at = lb & kLabNode ? &snode[sub][(lb & 0xFF) >> 5] : &sin[sub * TBH + (int)(x >> 6)][(x >> 5) & 1];
-        atomicOr(at, 1u << (lb & 31));
+    // every fourth seeded run of a row, the labels of four at a time
+    uint64_t st = ss;
+    for (int i = 0; i < wave; i++) st &= st - 1;
+    while (st) {
+        uint32_t lb[4];
+        int n = 0;
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            if (st) {
+                lb[j] = lab[__popcll(m.starts & below(__builtin_ctzll(st)))];
+                n++;
+            }
+            st = drop_bits<4>(st);
+        }
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            if (j >= n) break;
+            const uint32_t x = lb[j] & 0x7FF;
+            uint32_t *at = lb[j] & kLabNode ? &snode[sub][(lb[j] & 0xFF) >> 5]
+                                            : &sin[sub * TBH + (int)(x >> 6)][(x >> 5) & 1];
+            atomicOr(at, 1u << (lb[j] & 31));
+        }
     }
     __syncthreads();
     // useed rows
@@ -556,7 +582,7 @@ __device__ __forceinline__ void ccl_reseed_group(const Geo &g, const CclGeo &q, 
         const int t = ty * q.ntx + nx, n = (int)glb(a.cnt)[t], id0 = t * q.np + 1;
         for (int j = tid % TPS; j < n; j += TPS)
             if ((snode[ns][j >> 5] >> (j & 31)) & 1)
-                flag_or(glb(a.flag), node_root(par, id0 + j, par[id0 + j], gd.cap, ok), 2u << user);
+                flag_or_wave(glb(a.flag), node_root(par, id0 + j, par[id0 + j], gd.cap, ok), 2u << user);
     }
     guard_report(gd, ok);
 }
@@ -623,16 +649,26 @@ __device__ __forceinline__ void ccl_gather_group(const Geo &g, const CclGeo &q, 
     }
     __syncthreads();
     const Row m = rm.row(lane);
-    uint64_t zs = 0;
-    int k = 0;
-    for (uint64_t st = m.starts; st; st &= st - 1, k++) {
-        if ((k & 3) != wave) continue;
-        const uint32_t lb = k == wave ? lab0 : k == wave + 4 ? lab1 : lab[k], x = lb & 0x7FF;
+    uint64_t zs = 0, st = m.starts;  // st: the wave's next run is the lowest
+    for (int i = 0; i < wave; i++) st &= st - 1;
+    auto take = [&](uint32_t lb) {
+        if (!st) return;
+        const uint32_t x = lb & 0x7FF;
         bool hit;
         if (lb & kLabNode) hit = (snode[sub][(lb & 0xFF) >> 5] >> (lb & 31)) & 1;
         else if (user == 0) hit = lb & kLabSeed;
         else hit = (sin[sub * TBH + (int)(x >> 6)][(x >> 5) & 1] >> (lb & 31)) & 1;
         if (hit) zs |= st & (0 - st);
+        st = drop_bits<4>(st);
+    };
+    take(lab0);
+    take(lab1);
+    for (int k = wave + 8; st; k += 16) {  // the labels of four runs at a time
+        uint32_t lb[4];
+#pragma unroll
+        for (int j = 0; j < 4; j++) lb[j] = lab[min(k + 4 * j, nblk - 1)];
+#pragma unroll
+        for (int j = 0; j < 4; j++) take(lb[j]);
     }
     if (zs) {
         zs = fill_up(m.conn, zs);
