@@ -88,7 +88,8 @@ typedef struct vlg_formula_stats {
     int64_t steps_fused;    /* kernel steps of the fused schedule */
     int64_t peak_masks;     /* peak live intermediate masks (fused schedule) */
     int64_t launches_fused; /* kernel launches of the fused schedule (batched
-                               Boolean and near steps count once) */
+                               Boolean and near steps count once, a percentile
+                               step as on a large float32 channel) */
     int64_t labellings;     /* connected-component labellings (fused schedule) */
     int64_t labelling_reuse;/* reach-type nodes served by an earlier labelling of
                                the same passable mask */
@@ -250,7 +251,11 @@ int vlg_ccl_labels3(vlg_ctx *ctx, const uint64_t *mask_dev, int depth, int heigh
 
 /* Counters of the last reachability labelling run on ctx (for measurement):
  * union attempts and retry iterations of the cross-tile merge, and the
- * number of kernel launches per labelling. */
+ * number of kernel launches of the last union-find labelling enqueued: the
+ * labelling pass, the merge (several tiles), the pass that flags the roots
+ * (several reach-type nodes use the labelling) and the first node's gather;
+ * vlg_ccl_labels and vlg_ccl_labels3: all launches of the call.  0 before
+ * the first. */
 typedef struct vlg_ccl_counters {
     int64_t merge_unions;
     int64_t merge_retries;

@@ -209,7 +209,12 @@ struct vlg_ctx {
     // pointer-jumping labellings since the counters were last read: main
     // iterations, rounds (reconnect + termination check), kernel launches
     int64_t pj_iters = 0, pj_rounds = 0, pj_launches = 0, pj_labellings = 0;
-    std::map<GraphKey, hipGraphExec_t> graphs;
+    int64_t ccl_launches = 0;       // launches of the last union-find labelling
+    struct Graph {
+        hipGraphExec_t exec;
+        int64_t ccl_launches;       // ccl_launches after it ran
+    };
+    std::map<GraphKey, Graph> graphs;
     // pinned host staging of batch descriptors; `desc_done` marks the end of
     // the last upload from it
     void *desc_host = nullptr;
@@ -222,7 +227,7 @@ struct vlg_ctx {
     void drop_graphs() {
         if (graphs.empty()) return;
         (void)hipStreamSynchronize(stream);
-        for (auto &kv : graphs) (void)hipGraphExecDestroy(kv.second);
+        for (auto &kv : graphs) (void)hipGraphExecDestroy(kv.second.exec);
         graphs.clear();
     }
 };
@@ -249,7 +254,7 @@ struct Layout {
     size_t off_slots = 0, off_stage = 0, off_u8 = 0, off_ccl = 0, off_pct = 0, off_pctst = 0, total = 0;
     size_t lane_bytes = 0;  // labelling workspace of lane l at off_ccl + l * lane_bytes
     bool pj = false;        // pointer-jumping labelling: its arrays (pj_work) start at off_ccl
-    bool vol = false;       // volume labelling: voxel parents (4 B) then flag bytes at off_ccl
+    bool vol = false;       // volume labelling: parents of 2x2x2 blocks (4 B) then flag bytes at off_ccl
     size_t off_cand = 0;    // percentile candidates, cand_cap per rank of a step (0: radix select)
     uint32_t cand_cap = 0;
 };
@@ -410,6 +415,16 @@ CclPlan ccl_plan(const Plan &P) {
     }
     for (auto &r : run) flush(r);
     return c;
+}
+
+// Kernel launches of the plan's last labelling and its first gather: the
+// labelling pass, the merge when there are several tiles, the pass that flags
+// the roots when it has several users (`flags`: it runs then), the gather.
+// none: the plan has none.
+int64_t ccl_launches(const Plan &P, const CclPlan &cp, bool merges, bool flags, int64_t none) {
+    for (size_t si = P.steps.size(); si-- > 0;)
+        if (P.steps[si].kind == SK::CclLocal) return 2 + merges + (cp.multi[si] && flags);
+    return none;
 }
 
 // (ceil(log2 n), ceil(log2 mean pixels per image)) of a batch
@@ -662,6 +677,10 @@ int enqueue_plan(vlg_ctx *c, const Plan &P, const vlg_image *img, const Layout &
     m0.guard = c->guard();
     m0.tbh = tuning_for(c, img->H, img->W).ccl_tbh;
     const CclPlan cp = ccl_plan(P);
+    if (!L.pj) {
+        const bool merges = L.vol ? !vl_one_tile(g, img->S, img->D) : ccl_geo(g, m0.tbh).np > 0;
+        c->ccl_launches = ccl_launches(P, cp, merges, merges || L.vol, c->ccl_launches);
+    }
     const int near_rows = tuned_value(c, VLG_TUNE_NEAR_ROWS, img->H, img->W);
     const int64_t npix = (int64_t)img->H * img->W;
     // pointer-jumping labellings (L.pj): the label array the current
@@ -983,9 +1002,10 @@ int run(vlg_ctx *c, vlg_formula *f, const vlg_image *img, const std::vector<int>
             (void)hipGraphDestroy(graph);
             if (e != hipSuccess) return fail(VLG_EHIP, std::string("graph instantiate: ") + hipGetErrorString(e));
             if (c->graphs.size() >= 64) c->drop_graphs();
-            it = c->graphs.emplace(key, exec).first;
+            it = c->graphs.emplace(key, vlg_ctx::Graph{exec, c->ccl_launches}).first;
         }
-        HIP_TRY(hipGraphLaunch(it->second, c->stream));
+        HIP_TRY(hipGraphLaunch(it->second.exec, c->stream));
+        c->ccl_launches = it->second.ccl_launches;
     } else {
         rc = enqueue_all();
         if (rc != VLG_OK) return rc;
@@ -1164,6 +1184,7 @@ int run_batch(vlg_ctx *c, vlg_formula *f, const vlg_image *const *imgs, const st
     for (int k = 0; k < n; k++) sampled &= lay[k].cand_cap > 0 || geo[k].nwords == 0;
     const CclPlan cp = ccl_plan(P);
     auto enqueue_steps = [&]() -> int {
+        c->ccl_launches = ccl_launches(P, cp, true, true, c->ccl_launches);
         for (size_t si = 0; si < P.steps.size(); si++) {
             const Step &s = P.steps[si];
             hipError_t e = hipSuccess;
@@ -1314,9 +1335,10 @@ int run_batch(vlg_ctx *c, vlg_formula *f, const vlg_image *const *imgs, const st
             (void)hipGraphDestroy(graph);
             if (e != hipSuccess) return fail(VLG_EHIP, std::string("graph instantiate: ") + hipGetErrorString(e));
             if (c->graphs.size() >= 64) c->drop_graphs();
-            it = c->graphs.emplace(key, exec).first;
+            it = c->graphs.emplace(key, vlg_ctx::Graph{exec, c->ccl_launches}).first;
         }
-        HIP_TRY(hipGraphLaunch(it->second, c->stream));
+        HIP_TRY(hipGraphLaunch(it->second.exec, c->stream));
+        c->ccl_launches = it->second.ccl_launches;
     } else {
         rc = enqueue_steps();
         if (rc != VLG_OK) return rc;
@@ -1484,6 +1506,7 @@ int ccl_labels_on(vlg_ctx *c, const Geo &g, const uint64_t *mask_dev, int32_t *l
     m.op[0].ws = scratch;
     HIP_TRY(launch_ccl_labels(c->stream, g, m, (int32_t *)((char *)scratch + ls.off_ncanon),
                               (int32_t *)((char *)scratch + ls.off_icanon), labels_dev));
+    c->ccl_launches = ccl_geo(g, ls.tbh).np > 0 ? 4 : 2;
     return VLG_OK;
 }
 
@@ -1692,6 +1715,7 @@ int vlg_ccl_labels3(vlg_ctx *c, const uint64_t *mask_dev, int depth, int height,
     int *P = (int *)c->ws, *canon = (int *)((char *)c->ws + pb);
     const MRef b{mask_dev, 0ull};
     HIP_TRY(launch_vl_labels(c->stream, g, height, depth, b, P, canon, labels_dev, c->guard()));
+    c->ccl_launches = vl_one_tile(g, height, depth) ? 3 : 4;
     return VLG_OK;
 }
 
@@ -1816,8 +1840,10 @@ int vlg_formula_info(const vlg_formula *cf, vlg_formula_stats *st) {
     st->steps_fused = (int64_t)pf.steps.size();
     st->peak_masks = pf.nslots;
     int64_t launches = 0;
+    const CclPlan cp = ccl_plan(pf);
     for (size_t i = 0; i < pf.steps.size(); i++) {
         if (pf.steps[i].group >= 0 && i > 0 && pf.steps[i - 1].group == pf.steps[i].group) continue;
+        if (pf.steps[i].kind == SK::CclFlag && !cp.multi[i]) continue;  // nothing to launch
         launches += pf.steps[i].kind == SK::Pct ? 7 : 1;
     }
     st->launches_fused = launches;
@@ -2378,7 +2404,7 @@ int vlg_ccl_read_counters(vlg_ctx *c, vlg_ccl_counters *out) {
         out->merge_retries += (int64_t)h[k * kCounterStep + 1];
     }
     HIP_TRY(launch_fill_i64(c->stream, c->counters, kCounterWords, 0));
-    out->launches_per_ccl = 4;
+    out->launches_per_ccl = c->ccl_launches;
     out->pj_labellings = c->pj_labellings;
     out->pj_main_iterations = c->pj_iters;
     out->pj_rounds = c->pj_rounds;

@@ -268,6 +268,7 @@ hipError_t launch_near3(hipStream_t s, const Geo &g, int S, int D, MRef x, int i
 // 26-connected labelling over the runs of 2 x 2 x 2 voxel blocks (CclOp as for
 // images; workspace: 5 bytes per block, at least 5 * 256).
 int64_t vl_nblocks(const Geo &g, int S, int D);
+bool vl_one_tile(const Geo &g, int S, int D);  // (then nothing is merged)
 hipError_t launch_vl_label(hipStream_t s, const Geo &g, int S, int D, const CclOp &o, const LoopGuard &gd);
 hipError_t launch_vl_reseed(hipStream_t s, const Geo &g, int S, int D, const CclOp &o, const LoopGuard &gd);
 hipError_t launch_vl_gather(hipStream_t s, const Geo &g, int S, int D, const CclOp &o, const LoopGuard &gd);

@@ -712,6 +712,8 @@ int64_t vl_nblocks(const Geo &g, int S, int D) {
     return (int64_t)q.BX * q.BY * q.BZ;
 }
 
+bool vl_one_tile(const Geo &g, int S, int D) { return vl_tiles(vl_geo(g, S, D)) <= 1; }
+
 hipError_t launch_vl_label(hipStream_t s, const Geo &g, int S, int D, const CclOp &o, const LoopGuard &gd) {
     if (g.nwords == 0) return hipSuccess;
     if (S < 1 || D < 1 || (int64_t)S * D != g.H) return hipErrorInvalidValue;
