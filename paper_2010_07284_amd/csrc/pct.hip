@@ -82,13 +82,14 @@ enum PctMode : uint32_t { PCT_LIGHT = 0, PCT_HEAVY, PCT_DIRECT };
 // Counts of the pass.  The workgroups of a large single image would all add to
 // the same four addresses when they end (2048 of them: 40 us), so they share
 // kSegs sets of counts and candidate segments, each on a cache line of its
-// own.  A workgroup's first segment is a hash of its index, and a segment
-// that is full passes the rest on to the next: with the index modulo kSegs
-// the segment followed the rows, and an image periodic over 8 to 256 rows
-// filled a few of them and left the others empty.
+// own.  A workgroup starts with the segment that a hash of its index names, its
+// waves go round the segments whenever their queues are full, and what is left
+// of them at its end passes a full segment by: with the index modulo kSegs the
+// segment followed the rows, and an image periodic over 8 to 256 rows filled a
+// few segments and left the others empty.
 struct PctSeg {
-    // ncand: places asked for (beyond the segment's room: passed on); lost:
-    // candidates for which no segment had room
+    // ncand: places asked for, also beyond the segment's room; lost: candidates
+    // (of several segments) that found no room
     uint32_t ncand, below, eqlo, eqhi, lost, pad[27];
 };
 struct PctQ {  // of one rank
@@ -312,10 +313,11 @@ struct WaveSums {  // per wave of a workgroup
     int pieces[kMaxPctSel];
     uint32_t first[kMaxPctSel][kSegs + 1], at[kMaxPctSel][kSegs];
 };
-template <typename T, int M, bool HEAVY, bool NT>
+template <typename T, int M, bool HEAVY, bool NT, int NSEG>
 __device__ __forceinline__ void pct_collect(const Geo &g, const T *img, const PctSel &sel, void *states,
-                                            const Cand &cand, int seg, int64_t i0, int64_t i1,
+                                            const Cand &cand_, int seg, int64_t i0, int64_t i1,
                                             uint32_t (*queue)[kQueue], WaveSums &sums) {
+    const Cand cand{cand_.buf, cand_.cap, NSEG};
     using V = typename Vec4<T>::type;
     constexpr int U = 4;
     constexpr int64_t stride = kThreads * 4;
@@ -326,6 +328,7 @@ __device__ __forceinline__ void pct_collect(const Geo &g, const T *img, const Pc
     uint32_t base[M], width[M], cnt[M];
     uint32_t below[M], eqlo[M], eqhi[M];  // of this lane
     uint32_t inner = 0, heavy = 0;  // bit per rank
+    int flushes = 0;                // of this wave
 #pragma unroll
     for (int j = 0; j < M; j++) {
         const VLG_GLOBAL PctQ *st = qstate(states, sel.slot[j]);
@@ -341,20 +344,16 @@ __device__ __forceinline__ void pct_collect(const Geo &g, const T *img, const Pc
     auto flush = [&](int j) {
         wave_lds_handoff();
         VLG_GLOBAL PctQ *st = qstate(states, sel.slot[j]);
-        uint32_t done = 0;
-        for (int t = 0; t < cand.nseg; t++) {
-            const int s = (seg + t) & (cand.nseg - 1);
-            uint32_t at = 0, room = 0;
-            if (lane == 0) room = cand.reserve(st, s, cnt[j] - done, at);
-            at = __builtin_amdgcn_readfirstlane(at);
-            room = __builtin_amdgcn_readfirstlane(room);
-            VLG_GLOBAL uint32_t *buf = cand.rank(j) + (size_t)s * cand.seg_cap() + at;
-            for (uint32_t i = lane; i < room; i += 64) buf[i] = queue[j][done + i];
-            done += room;
-            if (done == cnt[j]) break;
-        }
-        if (done < cnt[j] && lane == 0)
-            __hip_atomic_fetch_add(&st->seg[seg].lost, cnt[j] - done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        // (the flushes of a wave go round the segments)
+        const int s = (seg + flushes++) & (NSEG - 1);
+        uint32_t at = 0, room = 0;
+        if (lane == 0) room = cand.reserve(st, s, cnt[j], at);
+        at = __builtin_amdgcn_readfirstlane(at);
+        room = __builtin_amdgcn_readfirstlane(room);
+        VLG_GLOBAL uint32_t *buf = cand.rank(j) + (size_t)s * cand.seg_cap() + at;
+        for (uint32_t i = lane; i < room; i += 64) buf[i] = queue[j][i];
+        if (NSEG > 1 && room < cnt[j] && lane == 0)
+            __hip_atomic_fetch_add(&st->seg[s].lost, cnt[j] - room, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         cnt[j] = 0;
         wave_lds_handoff();
     };
@@ -446,11 +445,13 @@ __device__ __forceinline__ void pct_collect(const Geo &g, const T *img, const Pc
         add(&st->eqhi, t[3]);
         sums.at[j][0] = (uint32_t)seg * cand.seg_cap() + at;
         int n = 0;
-        if (done < t[0]) {
+        if (NSEG == 1) {
+            // (each wave stores what fits)
+        } else if (done < t[0]) {
             sums.first[j][0] = 0;
             sums.first[j][n = 1] = done;
-            while (n < cand.nseg && done < t[0]) {
-                const int s = (seg + n) & (cand.nseg - 1);
+            while (n < NSEG && done < t[0]) {
+                const int s = (seg + n) & (NSEG - 1);
                 done += cand.reserve(q, s, t[0] - done, at);
                 sums.at[j][n] = (uint32_t)s * cand.seg_cap() + at;
                 sums.first[j][++n] = done;
@@ -464,6 +465,13 @@ __device__ __forceinline__ void pct_collect(const Geo &g, const T *img, const Pc
     for (int j = 0; j < M; j++) {
         uint32_t w0 = 0;  // this wave's first candidate among the workgroup's
         for (int w = 0; w < wave; w++) w0 += sums.cnt[w][j];
+        if (NSEG == 1) {
+            const uint32_t at = sums.at[j][0] + w0;
+            VLG_GLOBAL uint32_t *buf = cand.rank(j);
+            for (uint32_t i = lane; i < cnt[j]; i += 64)
+                if (at + i < cand.cap) buf[at + i] = queue[j][i];
+            continue;
+        }
         const int pieces = __builtin_amdgcn_readfirstlane(sums.pieces[j]);
         if (pieces == 0) {  // all in one
             VLG_GLOBAL uint32_t *buf = cand.rank(j) + sums.at[j][0] + w0;
@@ -478,7 +486,7 @@ __device__ __forceinline__ void pct_collect(const Geo &g, const T *img, const Pc
     __syncthreads();  // the next unit of a persistent workgroup reuses the LDS
 }
 
-template <typename T, int M, bool NT>
+template <typename T, int M, bool NT, int NSEG>
 __device__ __forceinline__ void pct_collect_range(const Geo &g, const T *img, const PctSel &sel, void *states,
                                                   const Cand &cand, int seg, int64_t i0, int64_t i1,
                                                   uint32_t (*queue)[kQueue], WaveSums &sums) {
@@ -486,8 +494,8 @@ __device__ __forceinline__ void pct_collect_range(const Geo &g, const T *img, co
     bool heavy = false;
     for (int j = 0; j < M; j++)
         heavy |= __builtin_amdgcn_readfirstlane(qstate(states, sel.slot[j])->mode) == PCT_HEAVY;
-    if (heavy) pct_collect<T, M, true, NT>(g, img, sel, states, cand, seg, i0, i1, queue, sums);
-    else pct_collect<T, M, false, NT>(g, img, sel, states, cand, seg, i0, i1, queue, sums);
+    if (heavy) pct_collect<T, M, true, NT, NSEG>(g, img, sel, states, cand, seg, i0, i1, queue, sums);
+    else pct_collect<T, M, false, NT, NSEG>(g, img, sel, states, cand, seg, i0, i1, queue, sums);
 }
 
 // Where a rank stands after the pass (the same in every thread): a key known
@@ -502,8 +510,11 @@ struct PctFound {
 };
 template <typename T>
 __device__ __forceinline__ PctFound pct_found(const Geo &g, const VLG_GLOBAL PctQ *st, const Cand &cand) {
-    // (scalars: what follows from them is the same in every lane)
+    // (scalars: what follows from them is the same in every lane; the loads first)
     auto scalar = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); };
+    const int lane = lane_id();
+    const VLG_GLOBAL PctSeg *seg = &st->seg[lane < cand.nseg ? lane : 0];
+    uint32_t c = seg->ncand, bl = seg->below, el = seg->eqlo, eh = seg->eqhi, ls = seg->lost;
     const uint32_t mode = scalar(st->mode), lo = scalar(st->lo), hi = scalar(st->hi), k = scalar(st->k);
     const bool heavy = mode == PCT_HEAVY;
     const uint32_t width = heavy ? hi - lo - 2 : hi - lo;
@@ -511,18 +522,10 @@ __device__ __forceinline__ PctFound pct_found(const Geo &g, const VLG_GLOBAL Pct
     if (mode == PCT_DIRECT) return channel;
     PctFound f{PCT_KNOWN, lo, 0, heavy ? lo + 1 : lo, 0, 0, scalar(st->ties) != 0, 0};
     // sums over the segments
-    const int lane = lane_id();
-    uint32_t c = 0, bl = 0, el = 0, eh = 0;
-    bool lost = false;
-    if (lane < cand.nseg) {
-        const VLG_GLOBAL PctSeg *s = &st->seg[lane];
-        f.held = min((uint32_t)s->ncand, cand.seg_cap());
-        c = f.held + s->lost;
-        bl = s->below;
-        el = s->eqlo;
-        eh = s->eqhi;
-        lost = s->lost != 0;
-    }
+    if (lane >= cand.nseg) c = bl = el = eh = ls = 0;
+    f.held = min(c, cand.seg_cap());
+    const bool lost = cand.nseg > 1 ? ls != 0 : c > f.held;
+    if (cand.nseg > 1) c = f.held + ls;
     const bool over = __any(lost);
 #pragma unroll
     for (int d = 1; d < kSegs; d <<= 1) {
@@ -810,15 +813,15 @@ __global__ __launch_bounds__(kSelThreads) void k_pct_bracket(uint32_t n, PctSel 
     pct_bracket_wg<F32>(n, sel, ranks, states, cand);
 }
 
-template <typename T, int M, bool NT>
+template <typename T, int M, bool NT, int NSEG>
 __global__ __launch_bounds__(kThreads) void k_pct_collect(Geo g, const T *img, PctSel sel, void *states, Cand cand) {
     __shared__ uint32_t queue[kThreads / 64][M][kQueue];
     __shared__ WaveSums sums;
     const int64_t n = (int64_t)g.H * g.wpr * 64, chunks = (n + kThreads * 4 - 1) / (kThreads * 4);
     const int64_t per = (chunks + gridDim.x - 1) / gridDim.x * (kThreads * 4);
     const int64_t i0 = (int64_t)blockIdx.x * per, i1 = i0 + per < n ? i0 + per : n;
-    const int seg = (int)((blockIdx.x * 0x9E3779B1u) >> 28) & (cand.nseg - 1);
-    pct_collect_range<T, M, NT>(g, img, sel, states, cand, seg, i0, i1, queue[threadIdx.x >> 6], sums);
+    const int seg = (int)((blockIdx.x * 0x9E3779B1u) >> 28) & (NSEG - 1);
+    pct_collect_range<T, M, NT, NSEG>(g, img, sel, states, cand, seg, i0, i1, queue[threadIdx.x >> 6], sums);
 }
 
 // (blockIdx.x: the part, blockIdx.y: the rank)
@@ -880,14 +883,16 @@ __global__ __launch_bounds__(kSelThreads) void kb_pct_bracket(BatchArgs a, PctSe
     }
 }
 
+// (the waves per SIMD that the queues of two and of three ranks leave room for;
+// with five for three ranks the pass of a batch takes 193 us, not 185)
 template <typename T, int M, bool NT>
-__global__ __launch_bounds__(kThreads) void kb_pct_collect(BatchArgs a, int chan, PctSel sel) {
+__global__ __launch_bounds__(kThreads, M == 2 ? 7 : M == 3 ? 6 : 1) void kb_pct_collect(BatchArgs a, int chan, PctSel sel) {
     __shared__ uint32_t queue[kThreads / 64][M][kQueue];
     __shared__ WaveSums sums;
     VLG_BATCH_LOOP(a) {
         VLG_BATCH_IMG(a)
         const int64_t n = (int64_t)d.g.H * d.g.wpr * 64, i0 = (u_ - a.prefix[ii]) * kPctUnit;
-        pct_collect_range<T, M, NT>(d.g, bchan<T>(d, chan), sel, d.ws + d.off_pctst, bcand(d), 0, i0,
+        pct_collect_range<T, M, NT, 1>(d.g, bchan<T>(d, chan), sel, d.ws + d.off_pctst, bcand(d), 0, i0,
                                     min(i0 + kPctUnit, n), queue[threadIdx.x >> 6], sums);
     }
 }
@@ -905,7 +910,7 @@ __global__ __launch_bounds__(kSelThreads) void kb_pct_candidates(BatchArgs a, in
 }
 
 template <typename T>
-__global__ __launch_bounds__(kSelThreads) void kb_pct_list(BatchArgs a, int chan, PctSel sel) {
+__global__ __launch_bounds__(kSelThreads, 8) void kb_pct_list(BatchArgs a, int chan, PctSel sel) {
     __shared__ uint32_t h[2048], found[2];
     const int j = (int)blockIdx.y;
     VLG_BATCH_LOOP(a) {
@@ -927,7 +932,7 @@ __global__ __launch_bounds__(kSelThreads) void kb_pct_refine(BatchArgs a, int ch
 }
 
 template <typename T>
-__global__ __launch_bounds__(kSelThreads) void kb_pct_pick(BatchArgs a, int chan, PctSel sel) {
+__global__ __launch_bounds__(kSelThreads, 8) void kb_pct_pick(BatchArgs a, int chan, PctSel sel) {
     __shared__ uint32_t h[2048], found[2];
     const int j = (int)blockIdx.y;
     VLG_BATCH_LOOP(a) {
@@ -958,8 +963,9 @@ hipError_t percentile_sampled(hipStream_t s, const Geo &g, const T *img, const P
     if (npix > kDirectPixels) {
         const bool nt = n * (int64_t)sizeof(T) > kStreamBytes;
 #define K(M)                                                                                              \
-    if (nt) k_pct_collect<T, M, true><<<grid, kThreads, 0, s>>>(g, img, sel, states, cand);               \
-    else k_pct_collect<T, M, false><<<grid, kThreads, 0, s>>>(g, img, sel, states, cand)
+    if (nt) k_pct_collect<T, M, true, kSegs><<<grid, kThreads, 0, s>>>(g, img, sel, states, cand);        \
+    else if (cand.nseg > 1) k_pct_collect<T, M, false, kSegs><<<grid, kThreads, 0, s>>>(g, img, sel, states, cand); \
+    else k_pct_collect<T, M, false, 1><<<grid, kThreads, 0, s>>>(g, img, sel, states, cand)
         VLG_BY_RANKS(sel.n, K)
 #undef K
     }
