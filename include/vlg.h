@@ -329,9 +329,10 @@ int vlg_profile_batch(vlg_ctx *ctx, const vlg_formula *f, const vlg_image *const
  * on the context's stream.  A merge or flag step repeated alone would find
  * its work done, so for those the repeated unit starts at the labelling's
  * tile-local pass, and the same unit without the step is timed too and
- * subtracted.  *avg_ms receives the mean time of one launch of the step,
- * *bytes its algorithmic bytes (as in vlg_profile).  Synchronises the
- * stream.  VLG_EINVAL when the schedule has no such step or labels with the
+ * subtracted (a labelling with one user has no flag pass to launch: its
+ * "ccl_flag" is noise around 0).  *avg_ms receives the mean time of one launch
+ * of the step, *bytes its algorithmic bytes (as in vlg_profile).  Synchronises
+ * the stream.  VLG_EINVAL when the schedule has no such step or labels with the
  * pointer-jumping schedule. */
 int vlg_profile_step(vlg_ctx *ctx, const vlg_formula *f, const vlg_image *img, const char *kind, int reps,
                      double *avg_ms, double *bytes);

@@ -318,13 +318,14 @@ hipError_t launch_pj_labels(hipStream_t s, const Geo &g, const PjWork &w, int at
 // ------------------------------------------------------------------ segments
 // A segment: consecutive Boolean and near steps of the fused schedule run by
 // one kernel.  A workgroup takes a tile of TR rows x TW words of the image,
-// extended by `halo` rows above and below and one word left and right, and
-// keeps every mask of the segment for that extended tile in LDS registers:
-// operands from outside the segment are loaded once, results that are read
-// later are stored once, and everything else never leaves LDS.  After d near
-// steps along a path a register is exact except in its d outermost rows (and
-// the outermost d bits of the two halo words), so with halo >= the deepest
-// near chain the tile itself is exact.
+// extended by `halo` rows above and below and some columns left and right (wide
+// tiles: a word; lane tiles, one word wide: 32 bits), and keeps every mask of
+// the segment for that extended tile in LDS registers: operands from outside
+// the segment are loaded once, results that are read later are stored once,
+// and everything else never leaves LDS.  After d near steps along a path a
+// register is exact except in its d outermost rows (and the outermost d bits of
+// its columns left and right), so with halo >= the deepest near chain the tile
+// itself is exact.
 constexpr int kSegMaxIns = 64;
 constexpr int kSegMaxRegs = 16;
 constexpr int kSegMaxPtrs = 32;

@@ -377,7 +377,8 @@ __global__ void k_fill_i64(unsigned long long *p, int n, unsigned long long v) {
 // Persistent: workgroup u-loop over the launch's global units.  Units per image:
 //   BK_WORDS  256 mask words (atoms: four 64-word wave tasks)
 //   BK_LOGIC  1024 mask words (Boolean steps)
-//   BK_NEAR   four near bands (64 words wide, kBatchNearRows rows high)
+//   BK_NEAR   256 word columns of bands (kBatchNearRows rows high, numbered
+//             through all bands of the image, see near_band)
 //   BK_TILES  one group of labelling tiles (64 block rows of tiles side by side)
 //   BK_MERGE  two tiles (two waves each)  BK_FLAG   four tiles (one per wave)
 //   BK_UNPACK 16384 output bytes
