@@ -212,7 +212,7 @@ struct vlg_ctx {
     int64_t ccl_launches = 0;       // launches of the last union-find labelling
     struct Graph {
         hipGraphExec_t exec;
-        int64_t ccl_launches;       // ccl_launches after it ran
+        int64_t ccl_launches;       // of its last labelling; -1: it has none
     };
     std::map<GraphKey, Graph> graphs;
     // pinned host staging of batch descriptors; `desc_done` marks the end of
@@ -415,6 +415,12 @@ CclPlan ccl_plan(const Plan &P) {
     }
     for (auto &r : run) flush(r);
     return c;
+}
+
+bool labels(const Plan &P) {
+    for (const Step &s : P.steps)
+        if (s.kind == SK::CclLocal) return true;
+    return false;
 }
 
 // Kernel launches of the plan's last labelling and its first gather: the
@@ -1002,10 +1008,10 @@ int run(vlg_ctx *c, vlg_formula *f, const vlg_image *img, const std::vector<int>
             (void)hipGraphDestroy(graph);
             if (e != hipSuccess) return fail(VLG_EHIP, std::string("graph instantiate: ") + hipGetErrorString(e));
             if (c->graphs.size() >= 64) c->drop_graphs();
-            it = c->graphs.emplace(key, vlg_ctx::Graph{exec, c->ccl_launches}).first;
+            it = c->graphs.emplace(key, vlg_ctx::Graph{exec, labels(P) ? c->ccl_launches : -1}).first;
         }
         HIP_TRY(hipGraphLaunch(it->second.exec, c->stream));
-        c->ccl_launches = it->second.ccl_launches;
+        if (it->second.ccl_launches >= 0) c->ccl_launches = it->second.ccl_launches;
     } else {
         rc = enqueue_all();
         if (rc != VLG_OK) return rc;
@@ -1335,10 +1341,10 @@ int run_batch(vlg_ctx *c, vlg_formula *f, const vlg_image *const *imgs, const st
             (void)hipGraphDestroy(graph);
             if (e != hipSuccess) return fail(VLG_EHIP, std::string("graph instantiate: ") + hipGetErrorString(e));
             if (c->graphs.size() >= 64) c->drop_graphs();
-            it = c->graphs.emplace(key, vlg_ctx::Graph{exec, c->ccl_launches}).first;
+            it = c->graphs.emplace(key, vlg_ctx::Graph{exec, labels(P) ? c->ccl_launches : -1}).first;
         }
         HIP_TRY(hipGraphLaunch(it->second.exec, c->stream));
-        c->ccl_launches = it->second.ccl_launches;
+        if (it->second.ccl_launches >= 0) c->ccl_launches = it->second.ccl_launches;
     } else {
         rc = enqueue_steps();
         if (rc != VLG_OK) return rc;

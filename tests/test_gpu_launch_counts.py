@@ -45,6 +45,24 @@ def test_counts():
         assert launches(ctx) == 3 + merges
 
 
+def test_graph_without_labelling():
+    """Its replay leaves the count of the last labelling as it is."""
+    ctx = vlg.create()
+    one, two, none = (vlg.compile_formula(ctx, s) for s in (ONE, TWO, ATOMS + 'output "x" a | c'))
+    im = vlg.load_image(ctx, np.random.default_rng(2).integers(0, 256, (300, 400), dtype=np.uint8))
+    vlg.set_mode(ctx, "graph")
+    # (`two` first: the workspace, and with it the graphs, stays)
+    calls = ((two, 4), (none, 4), (one, 3), (none, 3), (two, 4), (none, 4))
+    outs = {f: vlg.check_all(ctx, f, im) for f in (two, one, none)}
+    for f, want in calls:
+        vlg.check_all(ctx, f, im, outs=outs[f])
+        assert launches(ctx) == want
+    outs = {f: vlg.check_batch(ctx, f, [im, im]) for f in (two, one, none)}
+    for f, want in calls:
+        vlg.check_batch(ctx, f, [im, im], outs=outs[f])
+        assert launches(ctx) == want
+
+
 def test_formula_info():
     ctx = vlg.create()
     info = [vlg.formula_info(vlg.compile_formula(ctx, s)) for s in (ONE, TWO)]
