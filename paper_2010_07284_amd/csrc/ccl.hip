@@ -764,20 +764,21 @@ __global__ __launch_bounds__(kThreads) void k_ccl_canon(Geo g, CclMulti m, int32
     bool ok = true;
     for (int k0 = 0; k0 < n; k0 += 64) {
         const int id = id0 + k0 + lane;
-        int r = -1, v = 0;
+        int r = id, v = 0, c = 0;
         if (k0 + lane < n) {
+            v = canon[id];
             r = node_root(par, id, par[id], m.guard.cap, ok);
-            if (r == id) r = -1;
-            else v = canon[id];
+            if (r != id) c = __hip_atomic_load(&canon[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
-        // one atomicMin per distinct root of the wave, and none when the root
-        // already holds a smaller index (a giant component would otherwise
-        // serialise every wave on one address)
-        uint64_t pending = __ballot(r >= 0);
-        while (pending) {
+        // one atomicMin for all of the wave's nodes of one root (a giant
+        // component would otherwise serialise every wave on one address), none
+        // where the root already holds a smaller index; after two roots every
+        // lane by itself (a round trip per root of many small components)
+        uint64_t pending = __ballot(r != id && v < c);
+        for (int t = 0; t < 2 && pending; t++) {
             const int leader = __builtin_ctzll(pending);  // wave-uniform
             const int r0 = __builtin_amdgcn_readlane(r, leader);
-            const bool mine = r == r0;
+            const bool mine = r == r0 && r != id;
             pending &= ~__ballot(mine);
             int least = mine ? v : 0x7fffffff;
 #pragma unroll
@@ -785,6 +786,8 @@ __global__ __launch_bounds__(kThreads) void k_ccl_canon(Geo g, CclMulti m, int32
             if (lane == leader && least < __hip_atomic_load(&canon[r0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
                 __hip_atomic_fetch_min(&canon[r0], least, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
+        if (((pending >> lane) & 1) && v < __hip_atomic_load(&canon[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+            __hip_atomic_fetch_min(&canon[r], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     guard_report(m.guard, ok);
 }
